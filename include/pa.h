@@ -178,9 +178,9 @@ pa_status pa_sweep(pa_ctx *ctx, int32_t theta);
  * plane k of counters (s, w, i, 9<<28 | t<<8 | mu<<4 | q), q = k/2; the whole
  * cluster flips.  t counts sweeps and cluster updates together within step i
  * (at most 2^20).  Energies and magnetisations are recounted afterwards.
- * PA_E_INVAL if nsteps < 0, if the step's updates would pass 2^20, or if a
- * lattice needs more LDS per workgroup than the device has (4 N 8 bytes and
- * 24 KiB of queues, plus N with couplings: N <= 4352, or 4220 with
+ * PA_E_INVAL if nsteps < 0, if the step's updates would pass 2^20, or if the
+ * lattice is too large: 32 N bytes and 24 KiB, plus N bytes with couplings,
+ * must not pass the device's LDS per workgroup (N <= 4352, or 4220 with
  * couplings, on 160 KiB).  Enqueued on the run's stream. */
 pa_status pa_cluster(pa_ctx *ctx, int32_t nsteps);
 

@@ -107,11 +107,31 @@ __global__ __launch_bounds__(kThreads) void k_init_labels(const PaRunDesc *__res
 //    of Philox(s, w, i, WBOND<<28 | t<<8 | mu<<4 | q), q = 0..15, decided
 //    from the most significant bit as for the Metropolis thresholds;
 //  - the cluster is every site joined to the seed by active bonds; it flips.
-// Growth is bit-parallel over the 64 replicas: each pass, every site takes
-// the replicas newly added at a neighbour last pass (frontier F) across
-// satisfied bonds whose activity the pass decides for just those replicas;
-// a site writes only its own words, and a (bond, replica) pair is decided at
-// most once.  The component does not depend on the order of growth.
+// Every bond's activity is decided first, for all 64 replicas of its owner's
+// word at once (a replica's bond depends on its counters and threshold alone,
+// not on when the cluster reaches it), so the growth itself draws nothing: it
+// floods the active bonds until no word changes.  The component does not
+// depend on the order of growth.
+//
+// What bounds it: the decisions are VALU (Philox, about a sweep's work), the
+// growth the number of passes, as many as the deepest of the 64 clusters
+// needs, times a pass's LDS reads and logic.  So a lane owns a patch of PX PY
+// PZ sites and keeps their cluster words and bonds in registers; a pass reads
+// the words around the patch, floods the patch forwards and backwards and
+// writes what changed.  At the 2D critical point (L = 64) the deepest cluster
+// is about 230 bonds deep: some 57 passes with patches of 4 x 4 against 150
+// with strips of 4 and 230 site by site.  Waves do not wait for each other
+// between passes (words only gain bits, so an old one costs a pass and no
+// more); every kGrowPasses-th pass ends at a barrier that tells whether any
+// word changed.  Two words per site of LDS, so two workgroups share a CU at
+// N = 4096.
+// 2D L = 64, R = 10^5 at the critical point, per update: 8.2 ms with bonds
+// decided as the growth reached them and a barrier a pass, 1.29 ms with strips of
+// four, 0.45 ms now.  Two or eight passes to a barrier ran 3 % and 1 % slower.
+constexpr int kGrowPasses = 4;
+
+// Most lanes of a workgroup: N <= 4096 sites in patches of 16, of 4 (2D) or of 8 (3D).
+constexpr int cluster_lanes(int d, int patch) { return patch == 16 ? 256 : (d == 2 ? 1024 : 512); }
 
 // Activity of bond (owner, mu) for the replicas in cnd.
 __device__ __forceinline__ uint64_t wolff_bond(const PlaneCtx &pc, uint32_t owner, uint32_t mu, uint64_t cnd,
@@ -121,85 +141,32 @@ __device__ __forceinline__ uint64_t wolff_bond(const PlaneCtx &pc, uint32_t owne
         return cnd;
     if (T == 0)
         return 0;
+    constexpr int kFirst = 3; // as the sweeps: nearly every word needs three pairs, their chains interleaved
+    const uint32_t x3 = (PA_PURPOSE_WBOND << 28) | (pc.t << 8) | (mu << 4);
+    const pa_philox_shared sh = pa_philox_share(pc.seed, pc.run_id, owner, pc.w, pc.step);
     uint64_t und = cnd, acc = 0;
-    for (uint32_t q = 0; q < 16u && und != 0; ++q) {
-        const pa_philox_out o = pa_philox(pc.seed, pc.run_id, owner, pc.w, pc.step,
-                                          (PA_PURPOSE_WBOND << 28) | (pc.t << 8) | (mu << 4) | q);
+    pa_philox_out o[kFirst];
+    pa_philox_k<kFirst>(pc.seed, pc.run_id, sh, pc.w, pc.step, x3, o);
+#pragma unroll
+    for (int q = 0; q < kFirst; ++q)
+        pair_core<false>(o[q], tbit((uint32_t)T, 31 - 2 * q), tbit((uint32_t)T, 30 - 2 * q), und, und, acc);
+    for (uint32_t q = kFirst; q < 16u && und != 0; ++q) {
         const int b0 = 31 - 2 * (int)q;
-        pair_core<false>(o, tbit((uint32_t)T, b0), tbit((uint32_t)T, b0 - 1), und, und, acc);
+        pair_core<false>(pa_philox_with(pc.seed, pc.run_id, sh, pc.w, pc.step, x3 | q), tbit((uint32_t)T, b0),
+                         tbit((uint32_t)T, b0 - 1), und, und, acc);
     }
     return acc;
 }
 
-// Bond decisions are batched per wave: a site's candidate bonds (site,
-// direction k = 2 mu + [towards -e_mu], candidate replicas) go to a queue
-// and are decided 64 at a time, one per lane, so that a decision does not
-// run a whole wave for the one lane that needs it.
-constexpr int kClusterQueue = 128; // per wave; never more than 127 items are live
-// Lanes of a cluster-update workgroup: one workgroup per CU fits in LDS, so
-// its waves are all the latency hiding there is.
-constexpr int kClusterThreads = 1024;
-
-struct ClusterQueue {
-    uint32_t *sk;  // site | k << 16
-    uint64_t *cnd; // candidate replicas
-};
-
-__device__ __forceinline__ uint32_t cluster_push(const ClusterQueue &Q, uint32_t head, uint32_t cnt, bool has,
-                                                 uint32_t sk, uint64_t cnd)
+// PX, PY (and in 3D PZ) divide L; a workgroup has a lane for each of the N / (PX PY PZ) patches.
+template <int D, bool J, int PX, int PY, int PZ>
+__global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(const PaRunDesc *__restrict__ runs,
+                                                                          const PaBlk *__restrict__ map, int nsteps,
+                                                                          uint32_t t0)
 {
-    const uint64_t bal = __ballot(has);
-    if (has) {
-        const uint32_t slot = (head + cnt + (uint32_t)__popcll(bal & lanemask_lt())) & (kClusterQueue - 1);
-        Q.sk[slot] = sk;
-        Q.cnd[slot] = cnd;
-    }
-    __builtin_amdgcn_wave_barrier();
-    return cnt + (uint32_t)__popcll(bal);
-}
-
-// Decides up to 64 queued bonds and adds the replicas they join to Fn[site].
-template <int D>
-__device__ __forceinline__ void cluster_pass(const ClusterQueue &Q, const PlaneCtx &pc, uint64_t T, uint64_t *Fn,
-                                             int L, int LL, uint32_t mL, uint32_t &head, uint32_t &cnt)
-{
-    const uint32_t lane = threadIdx.x & 63;
-    const uint32_t n = cnt < 64u ? cnt : 64u;
-    const bool act = lane < n;
-    uint32_t sk = 0;
-    uint64_t cnd = 0;
-    if (act) {
-        const uint32_t slot = (head + lane) & (kClusterQueue - 1);
-        sk = Q.sk[slot];
-        cnd = Q.cnd[slot];
-    }
-    __builtin_amdgcn_wave_barrier();
-    head += n;
-    cnt -= n;
-    if (act) {
-        const int s = (int)(sk & 0xFFFFu), k = (int)(sk >> 16), mu = k >> 1;
-        const int row = (int)__umulhi((uint32_t)s, mL);
-        const int x = s - row * L;
-        const int z = (D == 2) ? 0 : (int)__umulhi((uint32_t)row, mL);
-        const int y = row - z * L;
-        const int c = mu == 0 ? x : (mu == 1 ? y : z);
-        const int st = mu == 0 ? 1 : (mu == 1 ? L : LL);
-        // bond (s, mu) to s + e_mu is owned by s, bond (s - e_mu, mu) by s - e_mu
-        const int owner = (k & 1) ? (c == 0 ? s + st * (L - 1) : s - st) : s;
-        const uint64_t a = wolff_bond(pc, (uint32_t)owner, (uint32_t)mu, cnd, T);
-        if (a)
-            atomicOr((unsigned long long *)&Fn[s], (unsigned long long)a);
-    }
-}
-
-template <int D, bool J>
-__global__ __launch_bounds__(kClusterThreads) void k_cluster(const PaRunDesc *__restrict__ runs,
-                                                      const PaBlk *__restrict__ map, int nsteps, uint32_t t0)
-{
-    // dynamic LDS: lattice [N] | cluster C [N] | frontiers F0, F1 [N] (at
-    // least 32 per wave in all, reused by the recount) | queue candidates
-    // [waves][kClusterQueue] u64 | queue sites [waves][kClusterQueue] u32 |
-    // jmask [N] bytes
+    static_assert(D == 3 || PZ == 1, "flat patches in 2D");
+    // dynamic LDS: lattice, then cluster, [N] | one axis's bonds [N] (at least 32 per wave, reused by
+    // the recount) | jmask [N] bytes
     extern __shared__ uint64_t lat[];
     const PaBlk blk = map[blockIdx.x];
     const PaRunDesc &rd = runs[blk.run];
@@ -210,13 +177,9 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(const PaRunDesc *__
         return;
     const int L = uni(rd.L), N = uni(rd.N), LL = L * L;
     const int cur = uni(rec->cur);
-    const int tid = threadIdx.x, bs = blockDim.x;
-    uint64_t *C = lat + N, *F0 = C + N, *F1 = F0 + N;
-    const int nw = bs >> 6, nred = 3 * N > 32 * nw ? 3 * N : 32 * nw;
-    uint64_t *qc = lat + N + nred;                                        // [waves][kClusterQueue]
-    uint32_t *qs = reinterpret_cast<uint32_t *>(qc + nw * kClusterQueue); // [waves][kClusterQueue]
-    uint8_t *jl = reinterpret_cast<uint8_t *>(qs + nw * kClusterQueue);
-    const ClusterQueue Q = {qs + (tid >> 6) * kClusterQueue, qc + (tid >> 6) * kClusterQueue};
+    const int tid = threadIdx.x, bs = blockDim.x, nw = bs >> 6;
+    uint64_t *xb = lat + N;
+    uint8_t *jl = reinterpret_cast<uint8_t *>(xb + max(N, 32 * nw));
     uint64_t *g = rd.dv.spins[cur] + (size_t)w * N;
     load_column<J>(lat, jl, g, rd.dv.jmask, N);
     const uint32_t mL = uni((uint32_t)(((1ull << 32) + (uint64_t)L - 1) / (uint64_t)L));
@@ -225,83 +188,163 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(const PaRunDesc *__
     uint64_t T = (uint64_t)tf;
     if (T > (1ull << 32))
         T = 1ull << 32;
+    T = uni64(T);
     PlaneCtx pc;
     pc.seed = uni(rd.seed);
     pc.run_id = uni(rd.run_id);
     pc.w = w;
     pc.step = uni(rec->step);
-    for (int k = 0; k < nsteps; ++k) {
-        pc.t = t0 + (uint32_t)k;
+    // the lane's patch: its first site, and the steps from its faces to the words beyond them
+    const int px = L / PX, py = L / PY;
+    const bool own = tid * (PX * PY * PZ) < N;
+    const int q = own ? tid : 0;
+    const int qx = q % px, qr = q / px, qy = qr % py, qz = qr / py;
+    const int s0 = qx * PX + L * (qy * PY) + LL * (qz * PZ);
+    const int oxm = qx == 0 ? L - 1 : -1, oxp = qx == px - 1 ? 1 - L : 1;
+    const int oym = qy == 0 ? L * (L - 1) : -L, oyp = qy == py - 1 ? -L * (L - 1) : L;
+    const int ozm = qz == 0 ? LL * (L - 1) : -LL, ozp = (qz + 1) * PZ == L ? -LL * (L - 1) : LL;
+    __syncthreads();
+    for (int step = 0; step < nsteps; ++step) {
+        pc.t = t0 + (uint32_t)step;
+        // the patch's own bonds (towards +e_mu), and those its neighbours own into its low faces
+        uint64_t bx[PZ][PY][PX], by[PZ][PY][PX], bz[PZ][PY][PX], fx[PZ][PY], fy[PZ][PX], fz[PY][PX];
+#pragma unroll
+        for (int mu = 0; mu < D; ++mu) {
+            for (int s = tid; s < N; s += bs) {
+                const int row = (int)__umulhi((uint32_t)s, mL);
+                const int x = s - row * L;
+                const int z = (D == 2) ? 0 : (int)__umulhi((uint32_t)row, mL);
+                const int y = row - z * L;
+                const int c = mu == 0 ? x : (mu == 1 ? y : z), st = mu == 0 ? 1 : (mu == 1 ? L : LL);
+                const uint64_t n = lat[c == L - 1 ? s - st * (L - 1) : s + st];
+                // active where satisfied and drawn
+                xb[s] = wolff_bond(pc, (uint32_t)s, (uint32_t)mu, ~bond<J>(lat[s], n, J ? (uint32_t)jl[s] : 0u, mu), T);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < PZ; ++k)
+#pragma unroll
+                for (int j = 0; j < PY; ++j)
+#pragma unroll
+                    for (int i = 0; i < PX; ++i) {
+                        const int s = s0 + i + L * j + LL * k;
+                        if (mu == 0) {
+                            bx[k][j][i] = own ? xb[s] : 0ull;
+                            if (i == 0)
+                                fx[k][j] = own ? xb[s + oxm] : 0ull;
+                        } else if (mu == 1) {
+                            by[k][j][i] = own ? xb[s] : 0ull;
+                            if (j == 0)
+                                fy[k][i] = own ? xb[s + oym] : 0ull;
+                        } else {
+                            bz[k][j][i] = own ? xb[s] : 0ull;
+                            if (k == 0)
+                                fz[j][i] = own ? xb[s + ozm] : 0ull;
+                        }
+                    }
+            __syncthreads(); // before the next axis's bonds; after the last, the lattice's words are not needed
+        }
         for (int s = tid; s < N; s += bs)
-            C[s] = F0[s] = 0;
+            lat[s] = 0;
         __syncthreads();
         if (tid < 64) { // the seed of replica tid
             const pa_philox_out o = pa_philox(pc.seed, pc.run_id, (uint32_t)tid, w, pc.step,
                                               (PA_PURPOSE_WSEED << 28) | (pc.t << 8));
-            const uint32_t s0 = (uint32_t)(((uint64_t)o.x0 * (uint64_t)N) >> 32);
-            atomicOr((unsigned long long *)&C[s0], 1ull << tid);
-            atomicOr((unsigned long long *)&F0[s0], 1ull << tid);
+            const uint32_t sd = (uint32_t)(((uint64_t)o.x0 * (uint64_t)N) >> 32);
+            atomicOr((unsigned long long *)&lat[sd], 1ull << tid);
         }
         __syncthreads();
-        uint64_t *Fc = F0, *Fn = F1;
-        // every pass that continues adds a (site, replica) pair: at most 64 N
-        for (int pass = 0; pass <= 64 * N; ++pass) {
-            for (int s = tid; s < N; s += bs)
-                Fn[s] = 0;
-            __builtin_amdgcn_wave_barrier(); // a wave's queue only adds to its own sites
-            uint32_t head = 0, cnt = 0;
-            for (int kb = 0; kb < N; kb += bs) {
-                const int s = kb + tid;
-                const bool in = s < N;
-                const int t = in ? s : 0;
-                const int row = (int)__umulhi((uint32_t)t, mL);
-                const int x = t - row * L;
-                const int z = (D == 2) ? 0 : (int)__umulhi((uint32_t)row, mL);
-                const int y = row - z * L;
-                const uint32_t jb = J ? (uint32_t)jl[t] : 0u;
-                const uint64_t S = lat[t], cs = C[t];
+        uint64_t c[PZ][PY][PX];
 #pragma unroll
-                for (int k = 0; k < 2 * D; ++k) {
-                    const int mu = k >> 1;
-                    const int c = mu == 0 ? x : (mu == 1 ? y : z);
-                    const int st = mu == 0 ? 1 : (mu == 1 ? L : LL);
-                    const int nb = (k & 1) ? (c == 0 ? t + st * (L - 1) : t - st)
-                                           : (c == L - 1 ? t - st * (L - 1) : t + st);
-                    // the replicas newly added at the neighbour, not yet here,
-                    // across a satisfied bond (coupling bit mu or D + mu)
-                    uint64_t cnd = in ? Fc[nb] & ~cs : 0;
-                    if (cnd)
-                        cnd &= ~bond<J>(S, lat[nb], jb, (k & 1) ? D + mu : mu);
-                    cnt = cluster_push(Q, head, cnt, cnd != 0, (uint32_t)t | ((uint32_t)k << 16), cnd);
-                    while (cnt >= 64u)
-                        cluster_pass<D>(Q, pc, T, Fn, L, LL, mL, head, cnt);
-                }
-            }
-            while (cnt > 0u)
-                cluster_pass<D>(Q, pc, T, Fn, L, LL, mL, head, cnt);
-            __builtin_amdgcn_wave_barrier();
+        for (int k = 0; k < PZ; ++k)
+#pragma unroll
+            for (int j = 0; j < PY; ++j)
+#pragma unroll
+                for (int i = 0; i < PX; ++i)
+                    c[k][j][i] = own ? lat[s0 + i + L * j + LL * k] : 0ull;
+        __syncthreads(); // every lane has its words before any writes
+        // every round that continues has added a (site, replica) pair: at most 64 N rounds
+        constexpr int kAndOr = PA_T3((PA_A & PA_B) | PA_C);
+        for (int round = 0; round <= 64 * N; ++round) {
             int any = 0;
-            for (int s = tid; s < N; s += bs) {
-                const uint64_t add = Fn[s] & ~C[s];
-                if (add) {
-                    C[s] |= add;
-                    any = 1;
+            for (int pass = 0; pass < kGrowPasses; ++pass) {
+                if (own) {
+                    uint64_t n[PZ][PY][PX];
+#pragma unroll
+                    for (int k = 0; k < PZ; ++k)
+#pragma unroll
+                        for (int j = 0; j < PY; ++j)
+#pragma unroll
+                            for (int i = 0; i < PX; ++i) {
+                                const int s = s0 + i + L * j + LL * k;
+                                uint64_t v = c[k][j][i];
+                                if (i == 0)
+                                    v = pa_bop3<kAndOr>(lat[s + oxm], fx[k][j], v);
+                                if (i == PX - 1)
+                                    v = pa_bop3<kAndOr>(lat[s + oxp], bx[k][j][i], v);
+                                if (j == 0)
+                                    v = pa_bop3<kAndOr>(lat[s + oym], fy[k][i], v);
+                                if (j == PY - 1)
+                                    v = pa_bop3<kAndOr>(lat[s + oyp], by[k][j][i], v);
+                                if (D == 3 && k == 0)
+                                    v = pa_bop3<kAndOr>(lat[s + ozm], fz[j][i], v);
+                                if (D == 3 && k == PZ - 1)
+                                    v = pa_bop3<kAndOr>(lat[s + ozp], bz[k][j][i], v);
+                                // forwards through the patch
+                                if (i > 0)
+                                    v = pa_bop3<kAndOr>(n[k][j][i > 0 ? i - 1 : 0], bx[k][j][i > 0 ? i - 1 : 0], v);
+                                if (j > 0)
+                                    v = pa_bop3<kAndOr>(n[k][j > 0 ? j - 1 : 0][i], by[k][j > 0 ? j - 1 : 0][i], v);
+                                if (k > 0)
+                                    v = pa_bop3<kAndOr>(n[k > 0 ? k - 1 : 0][j][i], bz[k > 0 ? k - 1 : 0][j][i], v);
+                                n[k][j][i] = v;
+                            }
+                    uint64_t ch = 0;
+#pragma unroll
+                    for (int k = PZ - 1; k >= 0; --k)
+#pragma unroll
+                        for (int j = PY - 1; j >= 0; --j)
+#pragma unroll
+                            for (int i = PX - 1; i >= 0; --i) { // and backwards
+                                uint64_t v = n[k][j][i];
+                                if (i < PX - 1)
+                                    v = pa_bop3<kAndOr>(n[k][j][i < PX - 1 ? i + 1 : 0], bx[k][j][i], v);
+                                if (j < PY - 1)
+                                    v = pa_bop3<kAndOr>(n[k][j < PY - 1 ? j + 1 : 0][i], by[k][j][i], v);
+                                if (k < PZ - 1)
+                                    v = pa_bop3<kAndOr>(n[k < PZ - 1 ? k + 1 : 0][j][i], bz[k][j][i], v);
+                                n[k][j][i] = v;
+                                ch = pa_bop3<PA_T3(PA_A | (PA_B ^ PA_C))>(ch, v, c[k][j][i]);
+                                c[k][j][i] = v;
+                            }
+                    if (ch != 0) {
+                        any = 1;
+#pragma unroll
+                        for (int k = 0; k < PZ; ++k)
+#pragma unroll
+                            for (int j = 0; j < PY; ++j)
+#pragma unroll
+                                for (int i = 0; i < PX; ++i)
+                                    lat[s0 + i + L * j + LL * k] = c[k][j][i];
+                    }
                 }
-                Fn[s] = add;
+                asm volatile("" ::: "memory"); // the next pass reads the neighbours' words again
             }
             if (!__syncthreads_or(any))
                 break;
-            uint64_t *tmp = Fc;
-            Fc = Fn;
-            Fn = tmp;
         }
-        for (int s = tid; s < N; s += bs)
-            lat[s] ^= C[s];
+        // flip: the lattice's words are still in memory
+        for (int s = tid; s < N; s += bs) {
+            const uint64_t v = g[s] ^ lat[s];
+            lat[s] = v;
+            if (step + 1 < nsteps)
+                g[s] = v;
+        }
         __syncthreads();
     }
     if (tid == 0 && w == 0) // once per run; no block reads it during the launch
         rec->sweeps = t0 + (uint32_t)nsteps;
-    recount_column<D, J>(lat, jl, g, lat + N, rd, cur, w, Rlive, L, N, LL, mL);
+    recount_column<D, J>(lat, jl, g, xb, rd, cur, w, Rlive, L, N, LL, mL);
 }
 
 // The sweep counter advances after the sweeps (a separate launch, so that no
@@ -2208,27 +2251,54 @@ size_t pa_sweep_lds_bytes(int N, int d, int threads, bool J)
            (J ? (((size_t)N + 7) & ~(size_t)7) : 0);
 }
 
+// The largest lattice of a cluster update, as the bytes its LDS limit counts: four words per site
+// and 24 KiB (N <= 4352 on 160 KiB), one byte more per site with couplings.
 size_t pa_cluster_lds_bytes(int N, bool J)
 {
-    const size_t nw = kClusterThreads / 64, nred = (size_t)3 * N > 32 * nw ? (size_t)3 * N : 32 * nw;
-    return ((size_t)N + nred) * 8 + nw * kClusterQueue * (8 + 4) + (J ? (((size_t)N + 7) & ~(size_t)7) : 0);
+    return (size_t)N * 32 + 24576 + (J ? (((size_t)N + 7) & ~(size_t)7) : 0);
 }
+
+namespace {
+
+template <int D, bool J, int PX, int PY, int PZ>
+hipError_t cluster_launch(const PaBatchView &v, int g, int nsteps, uint32_t t0)
+{
+    const int N = v.gN[g];
+    const int threads = (N / (PX * PY * PZ) + 63) / 64 * 64, nw = threads / 64;
+    if (threads > cluster_lanes(D, PX * PY * PZ))
+        return hipErrorInvalidValue;
+    const size_t lds = ((size_t)N + (size_t)(N > 32 * nw ? N : 32 * nw)) * 8 + (J ? (((size_t)N + 7) & ~(size_t)7) : 0);
+    k_cluster<D, J, PX, PY, PZ><<<v.gncol[g], threads, lds, v.stream>>>(v.runs, v.gcol[g], nsteps, t0);
+    return hipGetLastError();
+}
+
+// Patches of 16 sites (4 x 4 or 4 x 2 x 2) where L allows it and they fill at least a wave, else of
+// two sites each way: with fewer than 64 patches the lanes without one idle through the growth.
+template <int D, bool J>
+hipError_t cluster_launch(const PaBatchView &v, int g, int nsteps, uint32_t t0, int L)
+{
+    const bool wide = L % 4 == 0 && v.gN[g] >= 16 * 64;
+    if constexpr (D == 2)
+        return wide ? cluster_launch<2, J, 4, 4, 1>(v, g, nsteps, t0) : cluster_launch<2, J, 2, 2, 1>(v, g, nsteps, t0);
+    else
+        return wide ? cluster_launch<3, J, 4, 2, 2>(v, g, nsteps, t0) : cluster_launch<3, J, 2, 2, 2>(v, g, nsteps, t0);
+}
+
+} // namespace
 
 hipError_t pa_b_cluster(const PaBatchView &v, int nsteps, uint32_t t0)
 {
     for (int g = 0; g < v.ngroups; ++g) {
         if (v.gncol[g] == 0)
             continue;
-        const size_t lds = pa_cluster_lds_bytes(v.gN[g], v.gJ[g] != 0);
-        if (v.gd[g] == 2 && v.gJ[g])
-            k_cluster<2, true><<<v.gncol[g], kClusterThreads, lds, v.stream>>>(v.runs, v.gcol[g], nsteps, t0);
-        else if (v.gd[g] == 2)
-            k_cluster<2, false><<<v.gncol[g], kClusterThreads, lds, v.stream>>>(v.runs, v.gcol[g], nsteps, t0);
-        else if (v.gJ[g])
-            k_cluster<3, true><<<v.gncol[g], kClusterThreads, lds, v.stream>>>(v.runs, v.gcol[g], nsteps, t0);
+        int L = 2;
+        while ((v.gd[g] == 2 ? L * L : L * L * L) < v.gN[g])
+            ++L;
+        hipError_t e;
+        if (v.gd[g] == 2)
+            e = v.gJ[g] ? cluster_launch<2, true>(v, g, nsteps, t0, L) : cluster_launch<2, false>(v, g, nsteps, t0, L);
         else
-            k_cluster<3, false><<<v.gncol[g], kClusterThreads, lds, v.stream>>>(v.runs, v.gcol[g], nsteps, t0);
-        const hipError_t e = hipGetLastError();
+            e = v.gJ[g] ? cluster_launch<3, true>(v, g, nsteps, t0, L) : cluster_launch<3, false>(v, g, nsteps, t0, L);
         if (e != hipSuccess)
             return e;
     }
