@@ -575,37 +575,247 @@ __device__ Overlap rule_overlap(const uint32_t *__restrict__ hist, int hmin, int
 
 __device__ __forceinline__ bool qualifies(const Overlap &o, uint64_t A) { return (o.num << 32) >= (pa_u128)A * o.den; }
 
-__global__ __launch_bounds__(kRuleThreads) void k_rule(const PaRunDesc *__restrict__ runs, double alpha_star,
-                                                       double dbeta_max, int iterations, int bisect)
+// Sum of v over the wave in every lane, for lane values below 2^26 (the sum
+// stays below 2^32): butterflies by lane permutations within rows of 16, then
+// by exchanges of whole rows and halves.
+__device__ __forceinline__ uint32_t wave_sum_26(uint32_t v)
 {
-    __shared__ uint64_t su[16];
-    __shared__ uint64_t wcache[kRuleCache];
+    v += xlane<1>(v);
+    v += xlane<2>(v);
+    v += xlane<4>(v);
+    v += xlane<8>(v);
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = a[0] + a[1];
+    const auto c = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return uni(c[0] + c[1]);
+}
+
+// A wave's sum of lane values below 2^(26 LIMBS), in 26-bit limbs.
+template <int LIMBS>
+__device__ __forceinline__ pa_u128 wave_sum_u128(pa_u128 v)
+{
+    pa_u128 t = 0;
+#pragma unroll
+    for (int k = 0; k < LIMBS; ++k)
+        t += (pa_u128)wave_sum_26((uint32_t)(v >> (26 * k)) & 0x3FFFFFFu) << (26 * k);
+    return t;
+}
+
+// The rule's search.  An overlap is a sum over some hundred populated levels:
+// little work, so one evaluation at a time by the whole workgroup spent its
+// time on the barriers of the block sums.  Here each of kRuleWaves waves
+// evaluates a point of its own, with no barrier, and the workgroup takes
+// several halvings a round: either the seven midpoints of the next three
+// halvings (a tree, right whatever the outcome), or the midpoints of the next
+// seven along the path to the secant root of the overlap between lo and hi,
+// used as far as the outcomes follow that path.  The path is tried once the
+// bracket has shrunk and dropped for a round when it gained less than a tree
+// would (below about 2^-40 of dbeta_max the integer weights make the overlap
+// a staircase); 60 halvings take about 12 rounds.  The result is the plain bisection's, bit for bit.
+// Above kRuleLevels levels the evaluations bound the search and the whole
+// workgroup takes one at a time.
+// 3D L = 8, R = 10^5 (about 400 levels, 60 halvings): 258 -> 41 us.
+constexpr int kRuleWaves = 8;
+constexpr int kRuleLevels = 2048, kRuleHeld = 16; // held: levels per lane whose weights stay in registers
+
+struct RuleLds {
+    uint64_t su[16];
+    uint64_t wcache[kRuleCache];
+    uint32_t count[kRuleLevels]; // replicas per level
+    // the points of a round (two rounds' worth: one barrier a round): their overlaps, what those
+    // exceed the target by, and whether they qualify
+    double x[2][kRuleWaves], f[2][kRuleWaves];
+    pa_u128 num[2][kRuleWaves], den[2][kRuleWaves];
+    uint32_t ok[2][kRuleWaves];
+};
+
+struct RuleSearch {
+    RuleLds *l;
+    const uint32_t *hist;
+    int hmin, nlev, buf;
+    uint64_t R, A;
+    bool waves; // a wave per point
+
+    // Starts a search over the run's populated levels (all threads).
+    __device__ __forceinline__ RuleSearch(RuleLds *lds, const PaRunDesc &rd, const PaRecord *rec, double alpha_star)
+        : l(lds), hist(rd.dv.hist), buf(0)
+    {
+        const int DN = rd.d * rd.N;
+        hmin = (rec->emin + DN) >> 2;
+        nlev = uni(((rec->emax + DN) >> 2) - hmin + 1);
+        R = uni64(rec->Rcur);
+        A = uni64((uint64_t)rint(ldexp(alpha_star, 32)));
+        waves = nlev <= kRuleLevels;
+        if (waves)
+            for (int k = threadIdx.x; k < nlev; k += blockDim.x)
+                l->count[k] = hist[hmin + k];
+        __syncthreads();
+    }
+
+    // The wave's overlap at x (the same in every lane).
+    __device__ Overlap wave_overlap(double x) const
+    {
+        const int lane = threadIdx.x & 63;
+        uint64_t W[kRuleHeld], s = 0;
+        uint32_t n[kRuleHeld];
+#pragma unroll
+        for (int i0 = 0; i0 < kRuleHeld; i0 += 4) // four levels at a time: independent chains
+            if (64 * i0 < nlev)
+#pragma unroll
+                for (int i = i0; i < i0 + 4; ++i) {
+                    const int k = 64 * i + lane;
+                    W[i] = pa_weight(x, 4 * k);
+                    n[i] = k < nlev ? l->count[k] : 0u;
+                    s += (uint64_t)n[i] * W[i];
+                }
+        for (int k = 64 * kRuleHeld + lane; k < nlev; k += 64)
+            s += (uint64_t)l->count[k] * pa_weight(x, 4 * k);
+        const uint64_t S = (uint64_t)wave_sum_u128<3>(s);
+        pa_u128 a = 0;
+#pragma unroll
+        for (int i0 = 0; i0 < kRuleHeld; i0 += 4)
+            if (64 * i0 < nlev)
+#pragma unroll
+                for (int i = i0; i < i0 + 4; ++i) {
+                    const uint64_t RW = R * W[i];
+                    a += (pa_u128)n[i] * (RW < S ? RW : S);
+                }
+        for (int k = 64 * kRuleHeld + lane; k < nlev; k += 64) {
+            const uint64_t RW = R * pa_weight(x, 4 * k);
+            a += (pa_u128)l->count[k] * (RW < S ? RW : S);
+        }
+        Overlap o;
+        o.num = wave_sum_u128<4>(a); // below 2^88: counts below 2^24, S below 2^64
+        o.den = (pa_u128)R * S;
+        return o;
+    }
+
+    // One round: wave v's overlap at its x (NaN: none) into slot v; afterwards slot(v), x(v) hold them.
+    __device__ __forceinline__ void round(double x)
+    {
+        const int v = threadIdx.x >> 6;
+        buf ^= 1;
+        if (x == x) {
+            const Overlap o = wave_overlap(x);
+            const double f = excess(o);
+            const bool ok = qualifies(o, A);
+            if ((threadIdx.x & 63) == 0) {
+                l->x[buf][v] = x;
+                l->f[buf][v] = f;
+                l->ok[buf][v] = ok ? 1u : 0u;
+                l->num[buf][v] = o.num;
+                l->den[buf][v] = o.den;
+            }
+        }
+        __syncthreads();
+    }
+
+    __device__ __forceinline__ Overlap slot(int v) const { return {l->num[buf][v], l->den[buf][v]}; }
+
+    // Prepares the overlaps at up to kRuleWaves points, to be read by at() before the next round.
+    template <int n>
+    __device__ __forceinline__ void points(const double (&x)[n])
+    {
+        static_assert(n <= kRuleWaves, "a wave per point");
+        if (!waves)
+            return;
+        double mine = __longlong_as_double(-1ll);
+#pragma unroll
+        for (int k = 0; k < n; ++k)
+            if (k == (int)(threadIdx.x >> 6))
+                mine = x[k];
+        round(mine);
+    }
+
+    // The overlap at x, prepared as point k (without a wave per point: computed now).
+    __device__ __forceinline__ Overlap at(int k, double x)
+    {
+        return waves ? slot(k) : rule_overlap(hist, hmin, nlev, R, x, l->wcache, l->su);
+    }
+
+    __device__ __forceinline__ double excess(const Overlap &o) const
+    {
+        return u128_to_double(o.num) / u128_to_double(o.den) - (double)A * (1.0 / 4294967296.0);
+    }
+
+    // `iterations` halvings of [lo, hi] keeping lo qualified: lo (overlap olo) qualifies, hi (ohi) does not.
+    __device__ void bisect(double &lo, Overlap &olo, double hi, const Overlap &ohi, int iterations)
+    {
+        const int v = threadIdx.x >> 6;
+        double flo = excess(olo), fhi = excess(ohi);
+        bool path = false;
+        for (int it = 0; it < iterations;) {
+            const double mid = 0.5 * (lo + hi);
+            if (mid == lo || mid == hi)
+                break; // nothing lies between: every further halving keeps lo
+            if (!waves) {
+                const Overlap om = rule_overlap(hist, hmin, nlev, R, mid, l->wcache, l->su);
+                if (qualifies(om, A)) {
+                    lo = mid;
+                    olo = om;
+                } else {
+                    hi = mid;
+                }
+                ++it;
+                continue;
+            }
+            // this wave's point: midpoint v (1..7) of the tree, in heap order, or the v-th along the path
+            const double root = lo + (hi - lo) * (flo / (flo - fhi));
+            double a = lo, b = hi, x = __longlong_as_double(-1ll);
+            if (v > 0) {
+                const int depth = path ? v - 1 : 31 - __builtin_clz(v);
+                for (int d = 0; d < depth; ++d) {
+                    const double m = 0.5 * (a + b);
+                    const bool up = path ? m <= root : ((v >> (depth - 1 - d)) & 1) != 0;
+                    a = up ? m : a;
+                    b = up ? b : m;
+                }
+                x = 0.5 * (a + b);
+            }
+            round(x);
+            int n = 1, gained = 0, kept = 0;
+            for (const int most = path ? kRuleWaves - 1 : 3; gained < most && it < iterations;) {
+                const double m = l->x[buf][n], f = l->f[buf][n];
+                const bool ok = l->ok[buf][n] != 0u;
+                ++gained;
+                ++it;
+                if (ok) {
+                    lo = m;
+                    flo = f;
+                    kept = n;
+                } else {
+                    hi = m;
+                    fhi = f;
+                }
+                if (path && ok != (m <= root))
+                    break;
+                n = path ? n + 1 : 2 * n + (ok ? 1 : 0);
+            }
+            if (kept)
+                olo = slot(kept);
+            path = path ? gained >= 3 : true;
+        }
+    }
+};
+
+__global__ __launch_bounds__(kRuleWaves * 64) void k_rule(const PaRunDesc *__restrict__ runs, double alpha_star,
+                                                          double dbeta_max, int iterations, int bisect)
+{
+    __shared__ RuleLds lds;
     const PaRunDesc &rd = runs[blockIdx.x];
     PaRecord *rec = rd.dv.rec;
     if (frozen(rec))
         return;
-    const int DN = rd.d * rd.N;
-    const int hmin = (rec->emin + DN) >> 2, hmax = (rec->emax + DN) >> 2;
-    const int nlev = hmax - hmin + 1;
-    const uint64_t R = rec->Rcur;
-    const uint64_t A = (uint64_t)rint(ldexp(alpha_star, 32));
-    const Overlap top = rule_overlap(rd.dv.hist, hmin, nlev, R, dbeta_max, wcache, su);
+    RuleSearch rs(&lds, rd, rec, alpha_star);
+    const double xs[1] = {dbeta_max};
+    rs.points(xs);
+    const Overlap top = rs.at(0, dbeta_max);
     double best = dbeta_max;
     Overlap obest = top;
-    if (bisect && !qualifies(top, A)) {
-        double lo = 0.0, hi = dbeta_max;
+    if (bisect && !qualifies(top, rs.A)) {
+        best = 0.0;
         obest.num = obest.den = 1; // alpha(0) = 1
-        for (int it = 0; it < iterations; ++it) {
-            const double mid = 0.5 * (lo + hi);
-            const Overlap om = rule_overlap(rd.dv.hist, hmin, nlev, R, mid, wcache, su);
-            if (qualifies(om, A)) {
-                lo = mid;
-                obest = om;
-            } else {
-                hi = mid;
-            }
-        }
-        best = lo;
+        rs.bisect(best, obest, dbeta_max, top, iterations);
     }
     if (threadIdx.x == 0) {
         rec->rule_dbeta = best;
@@ -667,23 +877,17 @@ __global__ __launch_bounds__(kRuleThreads) void k_features(const PaRunDesc *__re
 // the lower end qualified.  Where neither applies (or c <= 0) the rule itself
 // decides: the bisection of k_rule over [0, dbeta_max] (the fallback).
 // Every value returned has alpha >= alpha*, tested exactly.
-__global__ __launch_bounds__(kRuleThreads) void k_check_candidate(const PaRunDesc *__restrict__ runs,
-                                                                  double alpha_star, double dbeta_max, int iterations,
-                                                                  double bracket, int refine)
+__global__ __launch_bounds__(kRuleWaves * 64) void k_check_candidate(const PaRunDesc *__restrict__ runs,
+                                                                     double alpha_star, double dbeta_max,
+                                                                     int iterations, double bracket, int refine)
 {
-    __shared__ uint64_t su[16];
-    __shared__ uint64_t wcache[kRuleCache];
+    __shared__ RuleLds lds;
     const PaRunDesc &rd = runs[blockIdx.x];
     PaRecord *rec = rd.dv.rec;
     if (frozen(rec))
         return;
-    const int DN = rd.d * rd.N;
-    const int hmin = (rec->emin + DN) >> 2, hmax = (rec->emax + DN) >> 2;
-    const int nlev = hmax - hmin + 1;
-    const uint64_t R = rec->Rcur;
-    const uint64_t A = (uint64_t)rint(ldexp(alpha_star, 32));
+    RuleSearch rs(&lds, rd, rec, alpha_star);
     const double cand = rec->cand_dbeta;
-    auto overlap = [&](double db) { return rule_overlap(rd.dv.hist, hmin, nlev, R, db, wcache, su); };
     auto publish = [&](double db, const Overlap &o, uint32_t fb) {
         if (threadIdx.x == 0) {
             rec->rule_dbeta = db;
@@ -691,63 +895,46 @@ __global__ __launch_bounds__(kRuleThreads) void k_check_candidate(const PaRunDes
             rec->fallback = fb;
         }
     };
+    // the candidate and the points that may be asked for next, in one round:
+    // the bracket's top and bottom, and the rule's first
+    const double up = bracket * cand < dbeta_max ? bracket * cand : dbeta_max;
+    const double xs[4] = {cand, up, cand / bracket, dbeta_max};
+    rs.points(xs);
     if (cand > 0.0) {
-        const Overlap oc = overlap(cand);
-        const bool ok = qualifies(oc, A);
+        const Overlap oc = rs.at(0, cand);
+        const bool ok = qualifies(oc, rs.A);
         if (ok && (refine == 0 || cand >= dbeta_max)) {
             publish(cand, oc, 0u);
             return;
         }
         if (refine > 0) {
-            double lo = cand, hi = cand;
-            Overlap olo = oc;
-            bool bracketed = false;
+            double lo = ok ? cand : xs[2], hi = ok ? up : cand;
+            Overlap olo = oc, ohi = oc;
+            bool bracketed = true;
             if (ok) {
-                hi = bracket * cand < dbeta_max ? bracket * cand : dbeta_max;
-                const Overlap oh = overlap(hi);
-                if (qualifies(oh, A)) {
-                    publish(hi, oh, 0u);
+                ohi = rs.at(1, up);
+                if (qualifies(ohi, rs.A)) {
+                    publish(up, ohi, 0u);
                     return;
                 }
-                bracketed = true;
             } else {
-                lo = cand / bracket;
-                olo = overlap(lo);
-                bracketed = qualifies(olo, A);
+                olo = rs.at(2, lo);
+                bracketed = qualifies(olo, rs.A);
             }
             if (bracketed) {
-                for (int it = 0; it < refine; ++it) {
-                    const double mid = 0.5 * (lo + hi);
-                    const Overlap om = overlap(mid);
-                    if (qualifies(om, A)) {
-                        lo = mid;
-                        olo = om;
-                    } else {
-                        hi = mid;
-                    }
-                }
+                rs.bisect(lo, olo, hi, ohi, refine);
                 publish(lo, olo, 0u);
                 return;
             }
         }
     }
-    const Overlap top = overlap(dbeta_max);
+    const Overlap top = rs.at(3, dbeta_max);
     double best = dbeta_max;
     Overlap obest = top;
-    if (!qualifies(top, A)) {
-        double lo = 0.0, hi = dbeta_max;
+    if (!qualifies(top, rs.A)) {
+        best = 0.0;
         obest.num = obest.den = 1;
-        for (int it = 0; it < iterations; ++it) {
-            const double mid = 0.5 * (lo + hi);
-            const Overlap om = overlap(mid);
-            if (qualifies(om, A)) {
-                lo = mid;
-                obest = om;
-            } else {
-                hi = mid;
-            }
-        }
-        best = lo;
+        rs.bisect(best, obest, dbeta_max, top, iterations);
     }
     publish(best, obest, 1u);
 }
@@ -2397,7 +2584,7 @@ hipError_t pa_b_rule(const PaBatchView &v, double alpha_star, double dbeta_max, 
     hipError_t e = hist_launch(v, hist_state);
     if (e != hipSuccess)
         return e;
-    k_rule<<<v.nruns, kRuleThreads, 0, v.stream>>>(v.runs, alpha_star, dbeta_max, iterations, bisect);
+    k_rule<<<v.nruns, kRuleWaves * 64, 0, v.stream>>>(v.runs, alpha_star, dbeta_max, iterations, bisect);
     return hipGetLastError();
 }
 
@@ -2414,7 +2601,7 @@ hipError_t pa_b_features(const PaBatchView &v, int hist_state)
 hipError_t pa_b_check_candidate(const PaBatchView &v, double alpha_star, double dbeta_max, int iterations,
                                 double bracket, int refine)
 {
-    k_check_candidate<<<v.nruns, kRuleThreads, 0, v.stream>>>(v.runs, alpha_star, dbeta_max, iterations, bracket,
+    k_check_candidate<<<v.nruns, kRuleWaves * 64, 0, v.stream>>>(v.runs, alpha_star, dbeta_max, iterations, bracket,
                                                               refine);
     return hipGetLastError();
 }
