@@ -1494,7 +1494,7 @@ static uint64_t mlp_layout(int max_samples, char *base, PaMlpDev *d)
         off += round256(bytes);
         return p;
     };
-    const uint64_t n = (uint64_t)max_samples, h = PA_MLP_HIDDEN;
+    const uint64_t n = (uint64_t)max_samples;
     PaMlpDev m{};
     m.P = (float *)take(4ull * PA_MLP_PARAMS);
     m.M = (float *)take(4ull * PA_MLP_PARAMS);
@@ -1503,13 +1503,9 @@ static uint64_t mlp_layout(int max_samples, char *base, PaMlpDev *d)
     m.norm = (PaMlpNorm *)take(sizeof(PaMlpNorm));
     m.X = (float *)take(4 * n * 8);
     m.Y = (float *)take(4 * n);
-    m.Xn = (float *)take(4 * n * 8);
-    m.H1 = (float *)take(4 * n * h);
-    m.H2 = (float *)take(4 * n * h);
-    m.D1 = (float *)take(4 * n * h);
-    m.D2 = (float *)take(4 * n * h);
-    m.dY = (float *)take(4 * n);
-    m.r2 = (float *)take(4 * n);
+    const uint64_t parts = (uint64_t)pa_mlp_parts(max_samples);
+    m.part = (float *)take(4 * parts * PA_MLP_PARAMS);
+    m.lpart = (double *)take(8 * parts);
     m.loss = (double *)take(8);
     m.pred = (float *)take(4 * n);
     if (d)

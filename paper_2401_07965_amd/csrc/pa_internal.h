@@ -158,7 +158,8 @@ struct PaMlpDev {
     float *P, *M, *V, *G;   // parameters, Adam moments, last gradient
     PaMlpNorm *norm;
     float *X, *Y;           // training data [n][8], [n]
-    float *Xn, *H1, *H2, *D1, *D2, *dY, *r2; // per-sample work
+    float *part;            // [pa_mlp_parts(max_samples)][PA_MLP_PARAMS] partial gradients
+    double *lpart;          // partial losses
     double *loss;
     float *pred;            // predictions [n]
     hipStream_t stream;
@@ -230,6 +231,7 @@ hipError_t pa_launch_overlap(const PaRunDesc *a, const PaRunDesc *b, int N, uint
 hipError_t pa_b_features(const PaBatchView &v, int hist_state);
 hipError_t pa_b_check_candidate(const PaBatchView &v, double alpha_star, double dbeta_max, int iterations,
                                 double bracket, int refine);
+int pa_mlp_parts(int n); // workgroups of a training pass over n samples
 hipError_t pa_mlp_launch_grad(const PaMlpDev &m, int n, int adam, int t, float lr);
 hipError_t pa_mlp_launch_predict(const PaMlpDev &m, const float *X, int n, float *out);
 hipError_t pa_mlp_launch_propose(const PaBatchView &v, const PaMlpDev &m, double dbeta_max);

@@ -1,8 +1,8 @@
 // The learned temperature-step model on gfx950: an 8 -> 64 -> 64 -> 1 tanh
 // network that proposes ln(dbeta) from population statistics.  Training in
-// float32 (forward/backward per sample, then one thread per parameter summing
-// its gradient over the samples in a fixed order, then Adam), inference in
-// bfloat16 (weights and layer inputs rounded to bfloat16, float32 sums).
+// float32 (forward and backward pass and the gradient of a tile of samples on
+// the float32 matrix units, partial gradients per workgroup added in a fixed
+// order, then Adam), inference in bfloat16 (weights and layer inputs rounded to bfloat16, float32 sums).
 // Parameter vector: W1[64][8], b1[64], W2[64][64], b2[64], W3[64], b3.
 #include "pa_device.h"
 #include "pa_internal.h"
@@ -21,97 +21,209 @@ __device__ __forceinline__ float bf16r(float x)
     return __uint_as_float(u & 0xFFFF0000u);
 }
 
-// One thread per sample: forward pass and the backward pass down to the
-// pre-activations; activations and their error signals go to global memory
-// for the per-parameter gradient sums.
-__global__ __launch_bounds__(256) void k_mlp_fwdbwd(const float *__restrict__ P, const PaMlpNorm *__restrict__ nm,
-                                                    const float *__restrict__ X, const float *__restrict__ Y, int n,
-                                                    float *__restrict__ Xn, float *__restrict__ H1,
-                                                    float *__restrict__ H2, float *__restrict__ D1,
-                                                    float *__restrict__ D2, float *__restrict__ dY,
-                                                    float *__restrict__ r2)
+// Training pass over tiles of 16 samples, one workgroup of four waves per tile
+// at a time; every layer is a product of float32 16 x 16 x 4 matrix operations
+// (A: lane l holds row l % 16 of column l / 16; B: column l % 16 of row l / 16;
+// result: lane l, element i is row 4 (l / 16) + i of column l % 16).  Wave v
+// owns hidden units 16 v .. 16 v + 15 of both layers: it keeps its rows and
+// its columns of W2 in registers for the launch, and its unit's activations
+// and error signals are the results of its own products, so only the operands
+// of the next product pass through LDS.  The gradient stays in accumulators
+// over the workgroup's tiles.
+// What bounds it: latency, at the sizes the model is trained on.  A launch per
+// pass used to take one sample per thread through global memory, one thread
+// per parameter then summed over all samples, and one thread the loss:
+// n = 2000 135 + 485 + 81 us per pass, now 9.4 + 7.1.
+constexpr int kTileN = 16, kLd = 68; // samples per tile; LDS row stride (16 rows x 4 columns on 64 banks)
+constexpr int kMaxParts = 256;       // workgroups, and partial gradients, of a pass at most
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x4 mfma(float a, float b, f32x4 c)
 {
-    __shared__ float sp[PA_MLP_PARAMS];
-    for (int k = threadIdx.x; k < PA_MLP_PARAMS; k += blockDim.x)
-        sp[k] = P[k];
-    __syncthreads();
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n)
-        return;
-    float x[8];
-    for (int k = 0; k < 8; ++k) {
-        x[k] = (X[i * 8 + k] - nm->x_mean[k]) / nm->x_std[k];
-        Xn[i * 8 + k] = x[k];
-    }
-    const float yn = (Y[i] - nm->y_mean) / nm->y_std;
-    float *h1 = H1 + (size_t)i * kH, *h2 = H2 + (size_t)i * kH;
-    for (int a = 0; a < kH; ++a) {
-        float z = sp[ob1 + a];
-        for (int k = 0; k < 8; ++k)
-            z += sp[oW1 + a * 8 + k] * x[k];
-        h1[a] = tanhf(z);
-    }
-    float yh = sp[ob3];
-    for (int a = 0; a < kH; ++a) {
-        float z = sp[ob2 + a];
-        for (int b = 0; b < kH; ++b)
-            z += sp[oW2 + a * kH + b] * h1[b];
-        const float h = tanhf(z);
-        h2[a] = h;
-        yh += sp[oW3 + a] * h;
-    }
-    const float res = yh - yn;
-    const float dy = res / (float)n;
-    dY[i] = dy;
-    r2[i] = res * res;
-    float *d2 = D2 + (size_t)i * kH, *d1 = D1 + (size_t)i * kH;
-    for (int a = 0; a < kH; ++a)
-        d2[a] = dy * sp[oW3 + a] * (1.0f - h2[a] * h2[a]);
-    for (int b = 0; b < kH; ++b) {
-        float s = 0.0f;
-        for (int a = 0; a < kH; ++a)
-            s += d2[a] * sp[oW2 + a * kH + b];
-        d1[b] = s * (1.0f - h1[b] * h1[b]);
-    }
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// One thread per parameter: its gradient as a sum over the samples in order;
-// then (adam != 0) one Adam step, t counting from 1.
-__global__ __launch_bounds__(256) void k_mlp_update(float *__restrict__ P, float *__restrict__ Mm,
-                                                    float *__restrict__ Vv, float *__restrict__ G,
-                                                    const float *__restrict__ Xn, const float *__restrict__ H1,
-                                                    const float *__restrict__ H2, const float *__restrict__ D1,
-                                                    const float *__restrict__ D2, const float *__restrict__ dY, int n,
-                                                    int adam, int t, float lr)
+// Sum over the 16 lanes of a row in every lane of it (the order is fixed).
+__device__ __forceinline__ float row_sum(float v)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= PA_MLP_PARAMS)
-        return;
-    float g = 0.0f;
-    if (p < ob1) {
-        const int a = (p - oW1) / 8, k = (p - oW1) % 8;
-        for (int i = 0; i < n; ++i)
-            g += D1[(size_t)i * kH + a] * Xn[i * 8 + k];
-    } else if (p < oW2) {
-        const int a = p - ob1;
-        for (int i = 0; i < n; ++i)
-            g += D1[(size_t)i * kH + a];
-    } else if (p < ob2) {
-        const int a = (p - oW2) / kH, b = (p - oW2) % kH;
-        for (int i = 0; i < n; ++i)
-            g += D2[(size_t)i * kH + a] * H1[(size_t)i * kH + b];
-    } else if (p < oW3) {
-        const int a = p - ob2;
-        for (int i = 0; i < n; ++i)
-            g += D2[(size_t)i * kH + a];
-    } else if (p < ob3) {
-        const int a = p - oW3;
-        for (int i = 0; i < n; ++i)
-            g += dY[i] * H2[(size_t)i * kH + a];
-    } else {
-        for (int i = 0; i < n; ++i)
-            g += dY[i];
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1)
+        v += __shfl_xor(v, m, 64);
+    return v;
+}
+
+__global__ __launch_bounds__(256) void k_mlp_grad(const float *__restrict__ P, const PaMlpNorm *__restrict__ nm,
+                                                  const float *__restrict__ X, const float *__restrict__ Y, int n,
+                                                  float *__restrict__ part, double *__restrict__ lpart)
+{
+    __shared__ float xs[kTileN][kLd];  // standardised inputs, then a column of ones and zeros up to 16
+    __shared__ float h1s[kTileN][kLd];
+    __shared__ float d1s[kTileN][kLd];
+    __shared__ float d2s[kTileN][kLd];
+    __shared__ float yp[4][kTileN]; // the waves' parts of the output
+    __shared__ float yn[kTileN];
+    __shared__ double ls[4];
+    const int tid = threadIdx.x, v = tid >> 6, l = tid & 63, c = l & 15, r = l >> 4;
+    const int u = 16 * v + c; // this lane's hidden unit
+    float w1[2], w2r[16], w2c[16];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        w1[k] = P[oW1 + u * 8 + 4 * k + r];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        w2r[k] = P[oW2 + u * kH + 4 * k + r];   // W2[u][.]: into layer 2
+        w2c[k] = P[oW2 + (4 * k + r) * kH + u]; // W2[.][u]: back to layer 1
     }
+    const float b1 = P[ob1 + u], b2 = P[ob2 + u], w3 = P[oW3 + u], b3 = P[ob3];
+    f32x4 g1 = {0, 0, 0, 0}, g2[4] = {g1, g1, g1, g1}; // dW1 and db1 (column 8), dW2
+    float gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f;
+    double loss = 0.0;
+    for (int t0 = blockIdx.x * kTileN; t0 < n; t0 += gridDim.x * kTileN) {
+        __syncthreads(); // the previous tile's operands have been read
+        {
+            const int s = tid >> 4, k = tid & 15, i = t0 + s;
+            float x = 0.0f;
+            if (i < n && k < 8)
+                x = (X[(size_t)i * 8 + k] - nm->x_mean[k]) / nm->x_std[k];
+            xs[s][k] = k == 8 ? 1.0f : x;
+            if (k == 0)
+                yn[s] = i < n ? (Y[i] - nm->y_mean) / nm->y_std : 0.0f;
+        }
+        __syncthreads();
+        f32x4 h1 = {b1, b1, b1, b1};
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            h1 = mfma(xs[c][4 * k + r], w1[k], h1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            h1[i] = tanhf(h1[i]);
+            h1s[4 * r + i][u] = h1[i];
+        }
+        __syncthreads();
+        f32x4 h2 = {b2, b2, b2, b2};
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            h2 = mfma(h1s[c][4 * k + r], w2r[k], h2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            h2[i] = tanhf(h2[i]);
+            const float y = row_sum(w3 * h2[i]);
+            if (c == 0)
+                yp[v][4 * r + i] = y;
+        }
+        __syncthreads();
+        f32x4 d2;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int s = 4 * r + i;
+            const float yh = ((yp[0][s] + yp[1][s]) + (yp[2][s] + yp[3][s])) + b3;
+            const float res = t0 + s < n ? yh - yn[s] : 0.0f; // samples past the end: no error
+            const float dy = res / (float)n;
+            if (v == 0 && c == 0)
+                loss += (double)(res * res);
+            d2[i] = dy * w3 * (1.0f - h2[i] * h2[i]);
+            d2s[s][u] = d2[i];
+            gb2 += d2[i];
+            gw3 += dy * h2[i];
+            gb3 += dy;
+        }
+        __syncthreads();
+        f32x4 d1 = {0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            d1 = mfma(d2s[c][4 * k + r], w2c[k], d1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            d1s[4 * r + i][u] = d1[i] * (1.0f - h1[i] * h1[i]);
+        __builtin_amdgcn_wave_barrier(); // a wave reads back its own columns only
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int s = 4 * k + r;
+            const float a = d2s[s][u];
+            g1 = mfma(d1s[s][u], xs[s][c], g1);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                g2[t] = mfma(a, h1s[s][16 * t + c], g2[t]);
+        }
+    }
+    // this workgroup's gradient
+    float *G = part + (size_t)blockIdx.x * PA_MLP_PARAMS;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int a = 16 * v + 4 * r + i;
+        if (c < 8)
+            G[oW1 + a * 8 + c] = g1[i];
+        if (c == 8)
+            G[ob1 + a] = g1[i];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            G[oW2 + a * kH + 16 * t + c] = g2[t][i];
+    }
+    gb2 += __shfl_xor(gb2, 16, 64);
+    gb2 += __shfl_xor(gb2, 32, 64);
+    gw3 += __shfl_xor(gw3, 16, 64);
+    gw3 += __shfl_xor(gw3, 32, 64);
+    gb3 += __shfl_xor(gb3, 16, 64);
+    gb3 += __shfl_xor(gb3, 32, 64);
+    if (r == 0) {
+        G[ob2 + u] = gb2;
+        G[oW3 + u] = gw3;
+    }
+    if (tid == 0)
+        G[ob3] = gb3;
+    if (v == 0 && c == 0)
+        ls[r] = loss;
+    __syncthreads();
+    if (tid == 0)
+        lpart[blockIdx.x] = (ls[0] + ls[1]) + (ls[2] + ls[3]);
+}
+
+// Adds the partial gradients (a thread every fourth of them, then the four in
+// order; the last workgroup adds the loss), then (adam != 0) one Adam step, t
+// counting from 1.
+constexpr int kUpdParams = 64; // parameters per workgroup
+
+__global__ __launch_bounds__(4 * kUpdParams) void k_mlp_update(float *__restrict__ P, float *__restrict__ Mm,
+                                                               float *__restrict__ Vv, float *__restrict__ G,
+                                                               const float *__restrict__ part,
+                                                               const double *__restrict__ lpart, int nparts, int n,
+                                                               double *__restrict__ loss, int adam, int t, float lr)
+{
+    __shared__ float sg[4][kUpdParams];
+    const int j = threadIdx.x & (kUpdParams - 1), q = threadIdx.x / kUpdParams;
+    if (blockIdx.x == gridDim.x - 1) {
+        if (threadIdx.x < 64) {
+            double s = 0.0;
+            for (int k = threadIdx.x; k < nparts; k += 64)
+                s += lpart[k];
+            s = pa_wave_sum_f64(s);
+            if (threadIdx.x == 0)
+                *loss = 0.5 * s / (double)n;
+        }
+        return;
+    }
+    const int p = blockIdx.x * kUpdParams + j;
+    float g = 0.0f;
+    if (p < PA_MLP_PARAMS) {
+        int k = q;
+        for (; k + 28 < nparts; k += 32) { // eight loads in flight
+            float x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                x[i] = part[(size_t)(k + 4 * i) * PA_MLP_PARAMS + p];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                g += x[i];
+        }
+        for (; k < nparts; k += 4)
+            g += part[(size_t)k * PA_MLP_PARAMS + p];
+    }
+    sg[q][j] = g;
+    __syncthreads();
+    if (q != 0 || p >= PA_MLP_PARAMS)
+        return;
+    g = (sg[0][j] + sg[1][j]) + (sg[2][j] + sg[3][j]);
     G[p] = g;
     if (adam) {
         const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
@@ -122,16 +234,6 @@ __global__ __launch_bounds__(256) void k_mlp_update(float *__restrict__ P, float
         const float mh = m / (1.0f - powf(b1, (float)t));
         const float vh = v / (1.0f - powf(b2, (float)t));
         P[p] = P[p] - lr * mh / (sqrtf(vh) + eps);
-    }
-}
-
-__global__ void k_mlp_loss(const float *__restrict__ r2, int n, double *loss)
-{
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        double s = 0.0;
-        for (int i = 0; i < n; ++i)
-            s += (double)r2[i];
-        *loss = 0.5 * s / (double)n;
     }
 }
 
@@ -198,13 +300,18 @@ __global__ __launch_bounds__(64) void k_mlp_propose(const PaRunDesc *__restrict_
 
 } // namespace
 
+int pa_mlp_parts(int n)
+{
+    const int tiles = (int)(((int64_t)n + kTileN - 1) / kTileN);
+    return tiles < kMaxParts ? tiles : kMaxParts;
+}
+
 hipError_t pa_mlp_launch_grad(const PaMlpDev &m, int n, int adam, int t, float lr)
 {
-    const int blocks = (n + 255) / 256;
-    k_mlp_fwdbwd<<<blocks, 256, 0, m.stream>>>(m.P, m.norm, m.X, m.Y, n, m.Xn, m.H1, m.H2, m.D1, m.D2, m.dY, m.r2);
-    k_mlp_update<<<(PA_MLP_PARAMS + 255) / 256, 256, 0, m.stream>>>(m.P, m.M, m.V, m.G, m.Xn, m.H1, m.H2, m.D1,
-                                                                    m.D2, m.dY, n, adam, t, lr);
-    k_mlp_loss<<<1, 64, 0, m.stream>>>(m.r2, n, m.loss);
+    const int parts = pa_mlp_parts(n);
+    k_mlp_grad<<<parts, 256, 0, m.stream>>>(m.P, m.norm, m.X, m.Y, n, m.part, m.lpart);
+    k_mlp_update<<<(PA_MLP_PARAMS + kUpdParams - 1) / kUpdParams + 1, 4 * kUpdParams, 0, m.stream>>>(
+        m.P, m.M, m.V, m.G, m.part, m.lpart, parts, n, m.loss, adam, t, lr);
     return hipGetLastError();
 }
 
