@@ -571,7 +571,8 @@ pa_status make_batch(const pa_config *cfgs, int32_t nruns, int32_t max_points, v
     for (int g = 0; g < b->v.ngroups; ++g)
         up(b->v.gcol[g], t.gcol[g].data(), sizeof(PaBlk) * t.gcol[g].size());
     for (int m = 0; m < nruns; ++m)
-        up(b->hdesc[m].dv.jmask, b->jmask[m].data(), b->jmask[m].size());
+        if (geo[m].J) // ferromagnets' kernels read no bond masks
+            up(b->hdesc[m].dv.jmask, b->jmask[m].data(), b->jmask[m].size());
     if (e == hipSuccess)
         e = launch_init(b);
     if (e == hipSuccess)
@@ -583,11 +584,13 @@ pa_status make_batch(const pa_config *cfgs, int32_t nruns, int32_t max_points, v
     return PA_OK;
 }
 
-pa_status fetch_records(Batch *b, const char *where)
+// Run m's record once the batch's stream has drained (one copy: reading one
+// run of a batch fetched every run's record, 1024 copies of 1.8 us each and
+// their launches for a batch of 1024).
+pa_status fetch_record(Batch *b, int m, const char *where)
 {
-    hipError_t e = hipSuccess;
-    for (int m = 0; m < b->M && e == hipSuccess; ++m)
-        e = hipMemcpyAsync(b->hrec + m, b->hdesc[m].dv.rec, sizeof(PaRecord), hipMemcpyDeviceToHost, b->v.stream);
+    hipError_t e =
+        hipMemcpyAsync(b->hrec + m, b->hdesc[m].dv.rec, sizeof(PaRecord), hipMemcpyDeviceToHost, b->v.stream);
     if (e == hipSuccess)
         e = hipStreamSynchronize(b->v.stream);
     if (e != hipSuccess)
@@ -612,7 +615,7 @@ pa_status status_error(Batch *b, uint32_t st)
 // deferred pa_resample reports the failure that froze it.
 pa_status ctx_records(Batch *b, const char *where)
 {
-    pa_status s = fetch_records(b, where);
+    pa_status s = fetch_record(b, 0, where);
     if (s != PA_OK)
         return s;
     if (b->hrec[0].status & PA_ST_FROZEN)
@@ -640,7 +643,7 @@ pa_status export_run(Batch *b, int m, pa_host_state *st)
     const hipError_t eg = settle_spins(b);
     if (eg != hipSuccess)
         return hip_fail(b, eg, "export");
-    pa_status s = fetch_records(b, "export");
+    pa_status s = fetch_record(b, m, "export");
     if (s != PA_OK)
         return s;
     const PaRecord &r = b->hrec[m];
@@ -881,7 +884,7 @@ pa_status pa_log_weights(pa_ctx *c, double *out, int32_t *weighted_out)
     Batch *b = &c->b;
     if (!out)
         return fail(b, PA_E_INVAL, "out is NULL");
-    pa_status s = fetch_records(b, "pa_log_weights");
+    pa_status s = fetch_record(b, 0, "pa_log_weights");
     if (s != PA_OK)
         return s;
     const PaRecord &r = b->hrec[0];
@@ -981,7 +984,7 @@ pa_status pa_import_state(pa_ctx *c, const pa_host_state *st)
         if (E < -DN || E > DN || ((E + DN) & 1) || M < -N || M > N)
             return fail(b, PA_E_INVAL, "energy or magnetisation out of range");
     }
-    pa_status s = fetch_records(b, "pa_import_state");
+    pa_status s = fetch_record(b, 0, "pa_import_state");
     if (s != PA_OK)
         return s;
     const int64_t R = st->R;
