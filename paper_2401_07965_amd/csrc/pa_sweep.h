@@ -139,17 +139,20 @@ __device__ __forceinline__ uint64_t tbit(uint32_t t, int b)
 }
 
 // The threshold bit on one plane of every undecided replica, from the
-// classes' bits t4, t8, t12 on that plane (masks).  The undecided replicas
-// all belong to the drawing classes, which are disjoint, so on them
-// Tp = m4 ? t4 : t8 in 2D and m4 ? t4 : (m8 ? t8 : t12) in 3D; the value on
-// other replicas is never used.
+// classes' bits t4, t8, t12 on that plane (masks).  Two words tell the classes
+// apart on the undecided replicas (their values elsewhere are never used): in
+// 2D m4 (u = 1 unsatisfied bond: dE = 4, else 8); in 3D m8, the parity of u
+// (u = 1: dE = 8), and where it is even m4 (u = 2: dE = 4, else u = 0: 12).
+// Telling them apart on the undecided replicas alone takes 4 operations fewer
+// per half-word than the classes' exact masks.
 template <int D>
 __device__ __forceinline__ uint64_t plane_threshold_m(uint64_t m4, uint64_t m8, uint64_t t4, uint64_t t8,
                                                       uint64_t t12)
 {
     constexpr int kSel = PA_T3((PA_A & PA_B) | (~PA_A & PA_C));
-    const uint64_t t = D == 2 ? t8 : pa_bop3<kSel>(m8, t8, t12);
-    return pa_bop3<kSel>(m4, t4, t);
+    if (D == 2)
+        return pa_bop3<kSel>(m4, t4, t8);
+    return pa_bop3<kSel>(m8, t8, pa_bop3<kSel>(m4, t4, t12));
 }
 
 // The same on plane (bit) b.  `last` is the last class's bit (T8_b in 2D,
@@ -255,16 +258,16 @@ struct WaveQueue {
     const uint32_t *tt;      // threshold-bit masks per plane pair (apply_pair_queued)
 };
 
-__device__ __forceinline__ uint64_t lanemask_lt() { return (1ull << (threadIdx.x & 63)) - 1ull; }
-
-// Appends this lane's item if `has`; returns the new item count (wave-uniform).
+// Appends this lane's item if `has` (bal: the wave's lanes that have one); returns the new item
+// count (wave-uniform).
 template <int D>
-__device__ __forceinline__ uint32_t queue_push(const WaveQueue &Q, uint32_t head, uint32_t cnt, bool has,
+__device__ __forceinline__ uint32_t queue_push(const WaveQueue &Q, uint32_t head, uint32_t cnt, bool has, uint64_t bal,
                                                uint32_t sq, uint64_t und, uint64_t m4, uint64_t m8)
 {
-    const uint64_t bal = __ballot(has);
     if (has) {
-        const uint32_t slot = (head + cnt + (uint32_t)__popcll(bal & lanemask_lt())) & (kQueue - 1);
+        const uint32_t slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)bal, head + cnt)) &
+                              (kQueue - 1);
         Q.sq[slot] = sq;
         Q.und[slot] = und;
         Q.m4[slot] = m4;
@@ -304,8 +307,9 @@ __device__ __forceinline__ void queue_pass(const WaveQueue &Q, const PlaneCtx &p
         apply_pair_queued<D>(Q.tt, metro_philox(pc, s, q), q, m4, m8, und, acc);
         lat[s] ^= acc;
     }
-    const bool again = act && und != 0 && q + 1 < 16;
-    cnt = queue_push<D>(Q, head, cnt, again, s | ((q + 1) << 16), und, m4, m8);
+    // (a lane without an item has und = 0)
+    const bool open = und != 0, more = q < 15u;
+    cnt = queue_push<D>(Q, head, cnt, open && more, __ballot(open) & __ballot(more), s | ((q + 1) << 16), und, m4, m8);
 }
 
 // The last items of a colour: up to 64 at a time, each lane taking its
@@ -481,6 +485,7 @@ __device__ __forceinline__ uint32_t sweep_columns(uint64_t *lat, const uint8_t *
     // Philox evaluations: the wave's count of site and queue passes
     // (wave-uniform) and this lane's count of its end-of-colour items
     uint32_t wcalls = 0, calls = 0;
+    const bool sure = (sure4 | sure8 | sure12) != 0;
     for (int tt = 0; tt < theta; ++tt) {
         pc.t = t0 + (uint32_t)tt;
         for (int c = 0; c < 2; ++c) {
@@ -555,40 +560,38 @@ __device__ __forceinline__ uint32_t sweep_columns(uint64_t *lat, const uint8_t *
                     // a_k: bond k unsatisfied (S ^ neighbour ^ [J = -1])
                     const uint64_t a0 = bond<J>(S, n0, jb, 0), a1 = bond<J>(S, n1, jb, D);
                     const uint64_t a2 = bond<J>(S, n2, jb, 1), a3 = bond<J>(S, n3, jb, D + 1);
-                    // u = number of unsatisfied bonds among 2d; dE = 4(d - u)
-                    uint64_t m12;
+                    // u = number of unsatisfied bonds among 2d; dE = 4(d - u); u >= d is
+                    // always accepted, the classes below draw
                     if (D == 2) {
-                        // pair sums s and carries c of (a0, a1) and (a2, a3); without
-                        // couplings S cancels from the sums and each carry is one
-                        // three-input operation on S and the neighbours
-                        constexpr int kBoth = PA_T3((PA_A ^ PA_B) & (PA_A ^ PA_C));
-                        const uint64_t s0 = J ? a0 ^ a1 : n0 ^ n1, s1 = J ? a2 ^ a3 : n2 ^ n3;
-                        const uint64_t c0 = J ? a0 & a1 : pa_bop3<kBoth>(S, n0, n1);
-                        const uint64_t c1 = J ? a2 & a3 : pa_bop3<kBoth>(S, n2, n3);
-                        const uint64_t cc = c0 | c1;
-                        always = pa_bop3<PA_T3(PA_A | (PA_B & PA_C))>(cc, s0, s1); // u >= 2
-                        m4 = pa_bop3<PA_T3((PA_A ^ PA_B) & ~PA_C)>(s0, s1, cc);    // u == 1
-                        m8 = pa_bop3<PA_T3(~(PA_A | PA_B | PA_C))>(s0, s1, cc);    // u == 0
-                        m12 = 0;
+                        // sum and carry of the first three bonds (without couplings from
+                        // the neighbour words: S passes through both), then the fourth:
+                        // u >= 2 iff the carry, or the sum with it; below, u = 1 iff either
+                        if (J) {
+                            const uint64_t sA = pa_bop3<kXor3>(a0, a1, a2), cA = pa_bop3<kMaj>(a0, a1, a2);
+                            always = pa_bop3<PA_T3(PA_A | (PA_B & PA_C))>(cA, sA, a3);
+                            m4 = sA ^ a3;
+                        } else {
+                            const uint64_t sA = pa_bop3<kXor3>(n0, n1, n2), cA = pa_bop3<kMaj>(n0, n1, n2);
+                            const uint64_t both = pa_bop3<PA_T3((PA_A ^ PA_B) & (PA_A ^ PA_C))>(S, sA, n3);
+                            always = pa_bop3<PA_T3(PA_A | (PA_B ^ PA_C))>(both, cA, S);
+                            m4 = sA ^ n3;
+                        }
                     } else {
+                        // sums and carries of three bonds each, u = 2 (cA + cB) + sA + sB:
+                        // u >= 3 iff both carries, or one and a sum
                         const uint64_t a4 = bond<J>(S, n4, jb, 2), a5 = bond<J>(S, n5, jb, 5);
-                        // three-bond sums and carries, then u = 2 (cA + cB + lc) + ls
                         const uint64_t sA = pa_bop3<kXor3>(a0, a1, a2), cA = pa_bop3<kMaj>(a0, a1, a2);
                         const uint64_t sB = pa_bop3<kXor3>(a3, a4, a5), cB = pa_bop3<kMaj>(a3, a4, a5);
-                        const uint64_t ls = sA ^ sB, lc = sA & sB;
-                        const uint64_t maj = pa_bop3<kMaj>(cA, cB, lc);  // cA + cB + lc >= 2
-                        const uint64_t odd = pa_bop3<kXor3>(cA, cB, lc); // ... is odd
-                        const uint64_t none = pa_bop3<PA_T3(~(PA_A | PA_B | PA_C))>(cA, cB, lc);
-                        always = pa_bop3<PA_T3(PA_A | (PA_B & PA_C))>(maj, odd, ls); // u >= 3
-                        m4 = pa_bop3<PA_T3(~PA_A & PA_B & ~PA_C)>(maj, odd, ls);     // u == 2
-                        m8 = none & ls;                                               // u == 1
-                        m12 = none & ~ls;                                             // u == 0
+                        always = pa_bop3<kMaj>(cA, cB, sA | sB);
+                        m8 = sA ^ sB;
+                        m4 = pa_bop3<PA_T3(PA_A | PA_B | PA_C)>(cA, cB, sA);
                     }
-                    if (ALL) { // every class draws: the rest of the word (~always) is undecided
-                        acc = always;
-                    } else {
-                        acc = always | (m4 & sure4) | (m8 & sure8) | (m12 & sure12);
-                        und = (m4 & draw4) | (m8 & draw8) | (m12 & draw12);
+                    acc = always;
+                    if (!ALL) { // of the rest of the word (~always), the classes that draw
+                        und = pa_bop3<PA_T3(~PA_A & PA_B)>(always, plane_threshold_m<D>(m4, m8, draw4, draw8, draw12),
+                                                           0ull);
+                        if (sure) // some class accepts outright (beta = 0)
+                            acc |= plane_threshold_m<D>(m4, m8, sure4, sure8, sure12);
                     }
                 }
                 // the first kInlinePairs plane pairs of the site: their Philox
@@ -637,7 +640,9 @@ __device__ __forceinline__ uint32_t sweep_columns(uint64_t *lat, const uint8_t *
                 if (!RAGGED || k < nh)
                     lat[s] = S ^ acc;
                 // an item still undecided has taken all inline pairs
-                cnt = queue_push<D>(Q, head, cnt, und != 0, s | ((uint32_t)kInlinePairs << 16), und, m4, m8);
+                const bool left = und != 0;
+                cnt = queue_push<D>(Q, head, cnt, left, __ballot(left), s | ((uint32_t)kInlinePairs << 16), und, m4,
+                                    m8);
                 while (cnt >= 64u)
                     queue_pass<D>(Q, pc, lat, head, cnt, wcalls);
             };
