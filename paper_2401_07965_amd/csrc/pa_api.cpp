@@ -153,6 +153,7 @@ uint64_t carve_run(const Geometry &g, char *base, PaDev *dv)
         d.label[k] = (uint32_t *)take(slots * 4);
     }
     d.jmask = (uint8_t *)take((uint64_t)g.N);
+    d.sites = (uint32_t *)take((uint64_t)g.N * 4);
     d.hist = (uint32_t *)take((uint64_t)g.H * 4);
     d.wtab = (uint64_t *)take((uint64_t)g.H * 8);
     d.r = (uint32_t *)take(slots * 4);
@@ -410,6 +411,7 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
             d.L = geo[m].L;
             d.N = geo[m].N;
             d.H = geo[m].H;
+            d.J = geo[m].J;
             d.R0 = geo[m].R;
             d.cap = geo[m].cap;
             d.dv = devs[m];
@@ -573,6 +575,8 @@ pa_status make_batch(const pa_config *cfgs, int32_t nruns, int32_t max_points, v
     for (int m = 0; m < nruns; ++m)
         if (geo[m].J) // ferromagnets' kernels read no bond masks
             up(b->hdesc[m].dv.jmask, b->jmask[m].data(), b->jmask[m].size());
+    if (e == hipSuccess)
+        e = pa_b_sites(b->v);
     if (e == hipSuccess)
         e = launch_init(b);
     if (e == hipSuccess)

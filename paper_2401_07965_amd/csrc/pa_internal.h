@@ -112,6 +112,7 @@ struct PaDev {
     int32_t *E[2], *M[2];
     uint32_t *label[2];
     uint8_t *jmask; // per site: bit mu = J(s,mu) is -1, bit d+mu = J(s-e_mu,mu) is -1
+    uint32_t *sites; // [N] site words in the order of the sweeps' walk (pa_sweep.h)
     uint32_t *hist; // [H] replicas per energy level h = (E + dN) / 4
     uint64_t *wtab; // [H] integer weight per level above the lowest
     uint32_t *r, *anc;
@@ -130,6 +131,7 @@ struct PaDev {
 
 struct PaRunDesc {
     int d, L, N, H;
+    int J; // 1: couplings given
     uint32_t seed, run_id;
     int64_t R0, cap;
     PaDev dv;
@@ -197,6 +199,7 @@ struct PaBatchView {
 };
 
 // launchers (pa_kernels.hip); each returns the first launch error
+hipError_t pa_b_sites(const PaBatchView &v); // every run's site table (once, after the bond masks are in place)
 hipError_t pa_b_init(const PaBatchView &v);
 // t0: sweeps already done at this beta; gather: the populations' spins may
 // still be in the other buffer (PaRecord::gather), taken in by the sweep

@@ -67,6 +67,21 @@ __global__ void k_init_rec(const PaRunDesc *__restrict__ runs)
     rec->ess = (double)rd.R0;
 }
 
+// The site words of the sweeps' table walk, one workgroup per run: word c N/2
+// + k is site k of colour c (row = y + L z = k div (L/2), x = 2 (k mod L/2) +
+// (y + z + c) mod 2).
+__global__ __launch_bounds__(kThreads) void k_sites(const PaRunDesc *__restrict__ runs)
+{
+    const PaRunDesc &rd = runs[blockIdx.x];
+    const int L = rd.L, half = L >> 1, nh = rd.N >> 1;
+    for (int i = threadIdx.x; i < rd.N; i += blockDim.x) {
+        const int c = i >= nh ? 1 : 0, k = i - c * nh;
+        const int row = k / half, z = row / L, y = row - z * L;
+        const int x = 2 * (k - row * half) + ((y + z + c) & 1), s = x + L * row;
+        rd.dv.sites[i] = site_word(s, rd.J ? (uint32_t)rd.dv.jmask[s] : 0u, x, y, L);
+    }
+}
+
 // Replica 64w+b, site s: bit b of x0 | x1<<32 of Philox(s, w, 0, INIT<<28).
 __global__ __launch_bounds__(kThreads) void k_init_spins(const PaRunDesc *__restrict__ runs,
                                                          const PaBlk *__restrict__ map)
@@ -181,7 +196,9 @@ __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(cons
     uint64_t *xb = lat + N;
     uint8_t *jl = reinterpret_cast<uint8_t *>(xb + max(N, 32 * nw));
     uint64_t *g = rd.dv.spins[cur] + (size_t)w * N;
-    load_column<J>(lat, jl, g, rd.dv.jmask, N);
+    load_column(lat, g, N);
+    if (J)
+        load_jmask(jl, rd.dv.jmask, N);
     const uint32_t mL = uni((uint32_t)(((1ull << 32) + (uint64_t)L - 1) / (uint64_t)L));
     const double p = 1.0 - pa_exp(-(2.0 * rec->beta));
     const double tf = floor(ldexp(p, 32));
@@ -344,7 +361,7 @@ __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(cons
     }
     if (tid == 0 && w == 0) // once per run; no block reads it during the launch
         rec->sweeps = t0 + (uint32_t)nsteps;
-    recount_column<D, J>(lat, jl, g, xb, rd, cur, w, Rlive, L, N, LL, mL);
+    recount_column<D, J>(lat, [&](int t, int, int, int) -> uint32_t { return jl[t]; }, g, xb, rd, cur, w, Rlive, L, N, LL, mL);
 }
 
 // The sweep counter advances after the sweeps (a separate launch, so that no
@@ -2413,6 +2430,38 @@ __global__ __launch_bounds__(kThreads) void k_philox_probe(uint32_t *__restrict_
     out[t] = acc;
 }
 
+constexpr int kLdsPerCu = 163840, kWavesPerCu = 16; // gfx950 LDS; four sweep waves per SIMD (<= 128 VGPRs)
+
+// Dynamic LDS of a sweep workgroup with walk `walk`.
+size_t sweep_lds(int N, int d, int threads, bool J, int walk)
+{
+    const size_t sites = walk == kWalkTable ? (size_t)N * 4 : (J ? (((size_t)N + 7) & ~(size_t)7) : 0);
+    return (size_t)N * 8 + (size_t)(threads / 64) * kQueue * (3 * 8 + 4) +
+           (size_t)(d == 2 ? ttab_words<2>() : ttab_words<3>()) * 4 + sites;
+}
+
+// Sweep waves per CU for that LDS.
+int sweep_waves(size_t lds, int threads)
+{
+    const int w = threads / 64, blocks = (int)(kLdsPerCu / lds);
+    return (blocks < kWavesPerCu / w ? blocks : kWavesPerCu / w) * w;
+}
+
+// The walk a sweep of this shape takes: coordinates that stay from pass to
+// pass where the workgroup size allows it, else the site table unless its LDS
+// costs resident waves (a wave lost costs more than the index arithmetic).
+int sweep_walk(int N, int d, int threads, bool J)
+{
+    int L = 2;
+    while ((d == 2 ? L * L : L * L * L) < N)
+        ++L;
+    if (threads % (d == 2 ? L : L * L) == 0)
+        return d == 3 && (L * L / 2) % 64 == 0 ? kWalkZ : kWalkFix;
+    const size_t plain = sweep_lds(N, d, threads, J, kWalkIndex), table = sweep_lds(N, d, threads, J, kWalkTable);
+    return table <= (size_t)kLdsPerCu && sweep_waves(table, threads) >= sweep_waves(plain, threads) ? kWalkTable
+                                                                                                    : kWalkIndex;
+}
+
 // Whether group g's sweeps take in the spins a resampling left in the other
 // buffer (their column load gathers them) or a k_gather_spins pass of the
 // resampling moves them: the gather in the load keeps the workgroup off the
@@ -2423,12 +2472,8 @@ __global__ __launch_bounds__(kThreads) void k_philox_probe(uint32_t *__restrict_
 // a resampling and the sweep after it.
 bool sweep_gathers(const PaBatchView &v, int g)
 {
-    constexpr int kLdsPerCu = 163840, kWavesPerCu = 16; // gfx950 LDS; four waves per SIMD (<= 128 VGPRs)
-    const int threads = v.gthreads[g], w = threads / 64;
-    int blocks = (int)(kLdsPerCu / pa_sweep_lds_bytes(v.gN[g], v.gd[g], threads, v.gJ[g] != 0));
-    if (blocks > kWavesPerCu / w)
-        blocks = kWavesPerCu / w;
-    return blocks * w >= kWavesPerCu;
+    const int threads = v.gthreads[g];
+    return sweep_waves(pa_sweep_lds_bytes(v.gN[g], v.gd[g], threads, v.gJ[g] != 0), threads) >= kWavesPerCu;
 }
 
 hipError_t sweep_launch(const PaBatchView &v, int g, int theta, int threads, uint32_t t0, hipStream_t st,
@@ -2437,14 +2482,15 @@ hipError_t sweep_launch(const PaBatchView &v, int g, int theta, int threads, uin
     if (v.gncol[g] == 0)
         return hipSuccess;
     const size_t lds = pa_sweep_lds_bytes(v.gN[g], v.gd[g], threads, v.gJ[g] != 0);
+    const int walk = sweep_walk(v.gN[g], v.gd[g], threads, v.gJ[g] != 0);
     if (gather && !sweep_gathers(v, g)) // gathered after the resampling
         gather = 0;
     if (v.gd[g] == 3)
-        return pa_sweep3_launch(v.runs, v.gcol[g], v.gncol[g], threads, lds, st, v.gJ[g] != 0, theta, t0, gather);
+        return pa_sweep3_launch(v.runs, v.gcol[g], v.gncol[g], threads, lds, st, v.gJ[g] != 0, theta, t0, gather, walk);
     if (v.gJ[g])
-        k_sweep<2, true><<<v.gncol[g], threads, lds, st>>>(v.runs, v.gcol[g], theta, t0, gather);
+        k_sweep<2, true><<<v.gncol[g], threads, lds, st>>>(v.runs, v.gcol[g], theta, t0, gather, walk);
     else
-        k_sweep<2, false><<<v.gncol[g], threads, lds, st>>>(v.runs, v.gcol[g], theta, t0, gather);
+        k_sweep<2, false><<<v.gncol[g], threads, lds, st>>>(v.runs, v.gcol[g], theta, t0, gather, walk);
     return hipGetLastError();
 }
 
@@ -2453,9 +2499,7 @@ hipError_t sweep_launch(const PaBatchView &v, int g, int theta, int threads, uin
 // ====================================================================== launchers
 size_t pa_sweep_lds_bytes(int N, int d, int threads, bool J)
 {
-    return (size_t)N * 8 + (size_t)(threads / 64) * kQueue * (3 * 8 + 4) +
-           (size_t)(d == 2 ? ttab_words<2>() : ttab_words<3>()) * 4 +
-           (J ? (((size_t)N + 7) & ~(size_t)7) : 0);
+    return sweep_lds(N, d, threads, J, sweep_walk(N, d, threads, J));
 }
 
 // The largest lattice of a cluster update, as the bytes its LDS limit counts: four words per site
@@ -2521,6 +2565,12 @@ hipError_t pa_query_lds(int *max_lds)
     if (e == hipSuccess)
         *max_lds = v;
     return e;
+}
+
+hipError_t pa_b_sites(const PaBatchView &v)
+{
+    k_sites<<<v.nruns, kThreads, 0, v.stream>>>(v.runs);
+    return hipGetLastError();
 }
 
 hipError_t pa_b_init(const PaBatchView &v)

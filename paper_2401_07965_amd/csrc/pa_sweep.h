@@ -354,8 +354,9 @@ __device__ __forceinline__ void queue_drain(const WaveQueue &Q, const PlaneCtx &
 // partial counts in red[32 per wave]): E = 2U - dN, M = N - 2 n_down.  Also
 // writes the lattice back to g.  Per-lane counts stay below 2^8: at most
 // ceil(N / blockDim) sites per lane, d bonds each (the launch checks).
-template <int D, bool J>
-__device__ __forceinline__ void recount_column(const uint64_t *lat, const uint8_t *jl, uint64_t *g, uint64_t *red,
+// jbits(t, x, y, z): site t's bond bits (bit mu: to s + e_mu).
+template <int D, bool J, typename JBits>
+__device__ __forceinline__ void recount_column(const uint64_t *lat, JBits jbits, uint64_t *g, uint64_t *red,
                                                const PaRunDesc &rd, int cur, uint32_t w, int64_t Rlive, int L,
                                                int N, int LL, uint32_t mL)
 {
@@ -371,7 +372,7 @@ __device__ __forceinline__ void recount_column(const uint64_t *lat, const uint8_
                 const int x = t - row * L;
                 const int z = (D == 2) ? 0 : (int)__umulhi((uint32_t)row, mL);
                 const int y = row - z * L;
-                const uint32_t jb = J ? (uint32_t)jl[t] : 0u;
+                const uint32_t jb = J ? jbits(t, x, y, z) : 0u;
                 S[h] = lat[t];
                 e[h][0] = bond<J>(S[h], lat[x == L - 1 ? t - (L - 1) : t + 1], jb, 0);
                 e[h][1] = bond<J>(S[h], lat[y == L - 1 ? t - L * (L - 1) : t + L], jb, 1);
@@ -447,27 +448,55 @@ struct SweepGeom {
     uint32_t mhalf, mL; // ceil(2^32 / half), ceil(2^32 / L)
 };
 
+// What the walk over a colour's sites uses:
+//  - kWalkZ, kWalkFix: coordinates that stay from pass to pass (below);
+//  - kWalkTable: a table in LDS with one word per site in the order of the
+//    walk (colour c, k): 8 s in bits 0..16, its bond bits from bit 17 (as in
+//    jmask), and from bit 23 whether x, y are last, first (x last, x first, y
+//    last, y first);
+//  - kWalkIndex: coordinates computed from k at every site.
+// The table takes half the index arithmetic of kWalkIndex (its word is loaded
+// a pass ahead) for 4 N bytes of LDS in place of N; sweep_walk uses it where
+// no resident wave is lost to those.  3D glass L = 10, 128 lanes, beta 0.15
+// and 3: 6631 and 7408 -> 6822 and 7654 attempts/ns.
+constexpr int kWalkIndex = 0, kWalkTable = 1, kWalkFix = 2, kWalkZ = 3;
+constexpr int kSiteJ = 17, kSiteEdge = 23;
+
+__device__ __forceinline__ uint32_t site_word(int s, uint32_t jb, int x, int y, int L)
+{
+    return ((uint32_t)s << 3) | (jb << kSiteJ) | (x == L - 1 ? 1u << kSiteEdge : 0u) |
+           (x == 0 ? 2u << kSiteEdge : 0u) | (y == L - 1 ? 4u << kSiteEdge : 0u) | (y == 0 ? 8u << kSiteEdge : 0u);
+}
+
+// Word at byte offset b of the lattice.
+__device__ __forceinline__ uint64_t lat_at(const uint64_t *lat, uint32_t b)
+{
+    return *reinterpret_cast<const uint64_t *>(reinterpret_cast<const char *>(lat) + b);
+}
+
 // Site k of colour c (k < N/2): row = y + L z = k div (L/2), x = 2 (k mod L/2)
 // + (y + z + c) mod 2.  Colour-c sites are independent and each one's random
 // bits are keyed by its site index, so the order in which lanes visit them
-// does not change any result.  FIX: the workgroup size is a multiple of L
+// does not change any result.  FIX (kWalkFix, kWalkZ): the workgroup size is a multiple of L
 // (2D) or L^2 (3D), so from one iteration to the next a lane's site moves by
 // 2 * blockDim sites along y (2D) or z (3D) and its other coordinates stay:
 // their neighbour offsets are computed once per colour.
 // zp: the number of leading inline plane pairs on which every drawing class's
 // threshold has 0 bits (their planes lie above the largest threshold): there
 // a differing bit can only reject, so such a pair decides as und &= ~(P0 | P1).
-// ZU (3D, FIX): every wave's sites share their z in each pass (L^2 / 2 colour
+// kWalkZ (3D): FIX, and every wave's sites share their z in each pass (L^2 / 2 colour
 // sites per z plane, a multiple of 64), so the z neighbours' offsets are
 // wave-uniform: +-L^2, or across the periodic boundary when the wave's
 // plane is the last or the first.
 // Returns the Philox evaluations, summed over the wave's lanes.
-template <int D, bool J, bool ALL, bool FIX, bool ZU = false>
-__device__ __forceinline__ uint32_t sweep_columns(uint64_t *lat, const uint8_t *jl, const SweepGeom &G, PlaneCtx pc,
-                                                  const WaveQueue &Q, int theta, uint32_t t0, uint64_t sure4,
-                                                  uint64_t sure8, uint64_t sure12, uint64_t draw4, uint64_t draw8,
-                                                  uint64_t draw12, int zp)
+template <int D, bool J, bool ALL, int WALK>
+__device__ __forceinline__ uint32_t sweep_columns(uint64_t *lat, const uint8_t *jl, const uint32_t *tab,
+                                                  const SweepGeom &G, PlaneCtx pc, const WaveQueue &Q, int theta,
+                                                  uint32_t t0, uint64_t sure4, uint64_t sure8, uint64_t sure12,
+                                                  uint64_t draw4, uint64_t draw8, uint64_t draw12, int zp)
 {
+    constexpr bool FIX = WALK >= kWalkFix, ZU = WALK == kWalkZ, TAB = WALK == kWalkTable;
+    constexpr int kJ0 = TAB ? kSiteJ : 0; // the first bond bit
     const int L = G.L, N = G.N, half = G.half, nh = G.nh, LL = G.LL;
     const uint32_t mhalf = G.mhalf, mL = G.mL;
     const int tid = threadIdx.x, bs = blockDim.x;
@@ -491,6 +520,7 @@ __device__ __forceinline__ uint32_t sweep_columns(uint64_t *lat, const uint8_t *
         for (int c = 0; c < 2; ++c) {
             uint32_t head = 0, cnt = 0;
             int sf = 0, oxp = 0, oxm = 0, oyp = 0, oym = 0;
+            uint32_t next = TAB ? tab[c * nh + min(tid, nh - 1)] : 0u; // the next pass's site word
             if (FIX) { // the lane's first site, and the offsets that stay
                 const int row = half > 1 ? (int)__umulhi((uint32_t)tid, mhalf) : tid;
                 const int m = tid - row * half;
@@ -514,7 +544,28 @@ __device__ __forceinline__ uint32_t sweep_columns(uint64_t *lat, const uint8_t *
                 uint32_t s = 0;
                 if (!RAGGED || k < nh) {
                     uint64_t n0, n1, n2, n3, n4 = 0, n5 = 0;
-                    if (FIX) {
+                    uint32_t jb = 0;
+                    if (TAB) {
+                        jb = next;
+                        next = tab[c * nh + min(k + bs, nh - 1)];
+                        const uint32_t b = jb & ((1u << kSiteJ) - 1u), L8 = 8u * (uint32_t)L, LL8 = 8u * (uint32_t)LL,
+                                       N8 = 8u * (uint32_t)N;
+                        auto edge = [&](int i, uint32_t d) { // d where edge bit i is set
+                            return (uint32_t)__builtin_amdgcn_sbfe((int)jb, (uint32_t)(kSiteEdge + i), 1u) & d;
+                        };
+                        s = b >> 3;
+                        n0 = lat_at(lat, b + edge(0, 0u - L8) + 8u);
+                        n1 = lat_at(lat, b + edge(1, L8) - 8u);
+                        if (D == 2) { // y is the last coordinate: modulo N
+                            n2 = lat_at(lat, min(b + L8, b + L8 - N8));
+                            n3 = lat_at(lat, min(b - L8, b - L8 + N8));
+                        } else {
+                            n2 = lat_at(lat, b + edge(2, 0u - LL8) + L8);
+                            n3 = lat_at(lat, b + edge(3, LL8) - L8);
+                            n4 = lat_at(lat, min(b + LL8, b + LL8 - N8));
+                            n5 = lat_at(lat, min(b - LL8, b - LL8 + N8));
+                        }
+                    } else if (FIX) {
                         s = (uint32_t)sf;
                         n0 = lat[sf + oxp];
                         n1 = lat[sf + oxm];
@@ -555,11 +606,12 @@ __device__ __forceinline__ uint32_t sweep_columns(uint64_t *lat, const uint8_t *
                             n5 = lat[z == 0 ? s + LL * (L - 1) : s - LL];
                         }
                     }
-                    const uint32_t jb = J ? (uint32_t)jl[s] : 0u;
+                    if (J && !TAB)
+                        jb = jl[s];
                     S = lat[s];
                     // a_k: bond k unsatisfied (S ^ neighbour ^ [J = -1])
-                    const uint64_t a0 = bond<J>(S, n0, jb, 0), a1 = bond<J>(S, n1, jb, D);
-                    const uint64_t a2 = bond<J>(S, n2, jb, 1), a3 = bond<J>(S, n3, jb, D + 1);
+                    const uint64_t a0 = bond<J>(S, n0, jb, kJ0), a1 = bond<J>(S, n1, jb, kJ0 + D);
+                    const uint64_t a2 = bond<J>(S, n2, jb, kJ0 + 1), a3 = bond<J>(S, n3, jb, kJ0 + D + 1);
                     // u = number of unsatisfied bonds among 2d; dE = 4(d - u); u >= d is
                     // always accepted, the classes below draw
                     if (D == 2) {
@@ -579,7 +631,7 @@ __device__ __forceinline__ uint32_t sweep_columns(uint64_t *lat, const uint8_t *
                     } else {
                         // sums and carries of three bonds each, u = 2 (cA + cB) + sA + sB:
                         // u >= 3 iff both carries, or one and a sum
-                        const uint64_t a4 = bond<J>(S, n4, jb, 2), a5 = bond<J>(S, n5, jb, 5);
+                        const uint64_t a4 = bond<J>(S, n4, jb, kJ0 + 2), a5 = bond<J>(S, n5, jb, kJ0 + 5);
                         const uint64_t sA = pa_bop3<kXor3>(a0, a1, a2), cA = pa_bop3<kMaj>(a0, a1, a2);
                         const uint64_t sB = pa_bop3<kXor3>(a3, a4, a5), cB = pa_bop3<kMaj>(a3, a4, a5);
                         always = pa_bop3<kMaj>(cA, cB, sA | sB);
@@ -692,19 +744,20 @@ __device__ __forceinline__ void stage_to_lds(T *dst, const __attribute__((addres
     stage_rounds<T, 2>(dst, src, n, b0, false);
 }
 
-// A column's N words (16 bytes per load) and, with couplings, its N bond
-// masks (4 bytes per load) into LDS.  N is a multiple of 4 (L even); g is
-// 32-byte and jm 256-byte aligned.
-template <bool J>
-__device__ __forceinline__ void load_column(uint64_t *lat, uint8_t *jl, const uint64_t *g, const uint8_t *jm,
-                                            int N)
+// A column's N words (16 bytes per load) into LDS.  N is a multiple of 4 (L
+// even); g is 32-byte aligned.
+__device__ __forceinline__ void load_column(uint64_t *lat, const uint64_t *g, int N)
 {
     typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
     stage_to_lds<u64x2>(reinterpret_cast<u64x2 *>(lat), (const __attribute__((address_space(1))) u64x2 *)g,
                         N >> 1);
-    if (J)
-        stage_to_lds<uint32_t>(reinterpret_cast<uint32_t *>(jl),
-                               (const __attribute__((address_space(1))) uint32_t *)jm, N >> 2);
+}
+
+// The N bond masks (4 bytes per load, 256-byte aligned) into LDS.
+__device__ __forceinline__ void load_jmask(uint8_t *jl, const uint8_t *jm, int N)
+{
+    stage_to_lds<uint32_t>(reinterpret_cast<uint32_t *>(jl), (const __attribute__((address_space(1))) uint32_t *)jm,
+                           N >> 2);
 }
 
 // Destination word column w takes the bits of its 64 ancestors.  Bit b comes
@@ -816,10 +869,10 @@ __device__ __forceinline__ void gather_sites(const uint64_t *src, int N, const G
 template <int D, bool J>
 __global__ __launch_bounds__(kSweepMaxThreads) void k_sweep(const PaRunDesc *__restrict__ runs,
                                                             const PaBlk *__restrict__ map, int theta, uint32_t t0,
-                                                            int gather)
+                                                            int gather, int walk)
 {
     // dynamic LDS: lattice [N] u64 | queues [waves][3][kQueue] u64 | queue sites [waves][kQueue] u32 |
-    // threshold-bit table [16][4 or 8] u32 | jmask [N]
+    // threshold-bit table [16][4 or 8] u32 | site table [N] u32 (kWalkTable), else jmask [N]
     extern __shared__ uint64_t lat[];
     const PaBlk blk = map[blockIdx.x];
     const PaRunDesc &rd = runs[blk.run];
@@ -835,7 +888,9 @@ __global__ __launch_bounds__(kSweepMaxThreads) void k_sweep(const PaRunDesc *__r
     uint64_t *qbase = lat + N + (size_t)(tid >> 6) * 3 * kQueue;
     uint32_t *qsites = reinterpret_cast<uint32_t *>(lat + N + (size_t)nwaves * 3 * kQueue);
     uint32_t *ttab = qsites + (size_t)nwaves * kQueue;
-    uint8_t *jl = reinterpret_cast<uint8_t *>(ttab + ttab_words<D>());
+    uint32_t *tab = ttab + ttab_words<D>();
+    uint8_t *jl = reinterpret_cast<uint8_t *>(tab);
+    const bool table = walk == kWalkTable;
     uint64_t *g = rd.dv.spins[cur] + (size_t)w * N;
     const uint64_t T4 = uni64(rec->T[0]), T8 = uni64(rec->T[1]), T12 = uni64(rec->T[2]);
     if (tid < 16) { // the threshold-bit masks of plane pair tid
@@ -858,12 +913,13 @@ __global__ __launch_bounds__(kSweepMaxThreads) void k_sweep(const PaRunDesc *__r
         __syncthreads();
         pa_u64x2 *dst = reinterpret_cast<pa_u64x2 *>(lat);
         gather_sites(rd.dv.spins[cur ^ 1], N, G, [&](int p, pa_u64x2 v) { dst[p] = v; });
-        if (J)
-            stage_to_lds<uint32_t>(reinterpret_cast<uint32_t *>(jl),
-                                   (const __attribute__((address_space(1))) uint32_t *)rd.dv.jmask, N >> 2);
     } else {
-        load_column<J>(lat, jl, g, rd.dv.jmask, N);
+        load_column(lat, g, N);
     }
+    if (table)
+        stage_to_lds<uint32_t>(tab, (const __attribute__((address_space(1))) uint32_t *)rd.dv.sites, N);
+    else if (J)
+        load_jmask(jl, rd.dv.jmask, N);
     __syncthreads();
 
     const uint64_t two32 = 1ull << 32;
@@ -889,32 +945,29 @@ __global__ __launch_bounds__(kSweepMaxThreads) void k_sweep(const PaRunDesc *__r
     const WaveQueue Q = {qsites + (size_t)(tid >> 6) * kQueue, qbase, qbase + kQueue, qbase + 2 * kQueue, ttab};
     const SweepGeom G = {L, N, half, nh, LL, mhalf, mL};
     const bool all_draw = draw4 != 0 && draw8 != 0 && (D == 2 || draw12 != 0);
-    const bool fix = bs % (D == 2 ? L : LL) == 0;
     // leading planes on which every drawing class's threshold bit is 0: the
     // leading zeros of their thresholds' or (each drawing threshold is < 2^32)
     const uint32_t tor = (uint32_t)((T4 & draw4) | (T8 & draw8) | (D == 3 ? (T12 & draw12) : 0ull));
     const int zp = uni(min(kInlinePairs, (tor ? (int)__builtin_clz(tor) : 32) / 2));
-    // 3D fixed-axis walk with every wave inside one z plane per pass
-    const bool zu = D == 3 && fix && (LL / 2) % 64 == 0;
     uint32_t calls;
-    if (all_draw && zu)
-        calls = sweep_columns<D, J, true, true, D == 3>(lat, jl, G, pc, Q, theta, t0, sure4, sure8, sure12, draw4,
-                                                        draw8, draw12, zp);
-    else if (all_draw && fix)
-        calls = sweep_columns<D, J, true, true>(lat, jl, G, pc, Q, theta, t0, sure4, sure8, sure12, draw4, draw8,
-                                                draw12, zp);
-    else if (all_draw)
-        calls = sweep_columns<D, J, true, false>(lat, jl, G, pc, Q, theta, t0, sure4, sure8, sure12, draw4, draw8,
-                                                 draw12, zp);
-    else if (zu)
-        calls = sweep_columns<D, J, false, true, D == 3>(lat, jl, G, pc, Q, theta, t0, sure4, sure8, sure12, draw4,
-                                                         draw8, draw12, zp);
-    else if (fix)
-        calls = sweep_columns<D, J, false, true>(lat, jl, G, pc, Q, theta, t0, sure4, sure8, sure12, draw4, draw8,
-                                                 draw12, zp);
+    auto sweep = [&](auto all, auto wk) {
+        calls = sweep_columns<D, J, decltype(all)::value, decltype(wk)::value>(lat, jl, tab, G, pc, Q, theta, t0, sure4,
+                                                                              sure8, sure12, draw4, draw8, draw12, zp);
+    };
+    auto with_walk = [&](auto all) {
+        if (D == 3 && walk == kWalkZ)
+            sweep(all, std::integral_constant<int, D == 3 ? kWalkZ : kWalkFix>{});
+        else if (walk == kWalkFix)
+            sweep(all, std::integral_constant<int, kWalkFix>{});
+        else if (table)
+            sweep(all, std::integral_constant<int, kWalkTable>{});
+        else
+            sweep(all, std::integral_constant<int, kWalkIndex>{});
+    };
+    if (all_draw)
+        with_walk(std::true_type{});
     else
-        calls = sweep_columns<D, J, false, false>(lat, jl, G, pc, Q, theta, t0, sure4, sure8, sure12, draw4, draw8,
-                                                  draw12, zp);
+        with_walk(std::false_type{});
 
     // after the sweeps the queue region is free: per-wave partial counts of the measurement
     if (theta > 0) {
@@ -928,11 +981,17 @@ __global__ __launch_bounds__(kSweepMaxThreads) void k_sweep(const PaRunDesc *__r
             rec->attempts += (unsigned long long)theta * (unsigned long long)N * (unsigned long long)Rlive;
         }
     }
-    recount_column<D, J>(lat, jl, g, lat + N, rd, cur, w, Rlive, L, N, LL, mL);
+    auto jbits = [&](int t, int x, int y, int z) -> uint32_t {
+        if (!table)
+            return jl[t];
+        const int c = (x + y + z) & 1, k = (y + L * z) * half + (x >> 1); // the site's place in the walk
+        return (tab[c * nh + k] >> kSiteJ) & 63u;
+    };
+    recount_column<D, J>(lat, jbits, g, lat + N, rd, cur, w, Rlive, L, N, LL, mL);
 }
 
 } // namespace
 
 // Launches k_sweep<3, J> (defined in pa_sweep3.hip).
 hipError_t pa_sweep3_launch(const PaRunDesc *runs, const PaBlk *map, int nblocks, int threads, size_t lds,
-                            hipStream_t st, bool J, int theta, uint32_t t0, int gather);
+                            hipStream_t st, bool J, int theta, uint32_t t0, int gather, int walk);
