@@ -2485,13 +2485,15 @@ hipError_t sweep_launch(const PaBatchView &v, int g, int theta, int threads, uin
     const int walk = sweep_walk(v.gN[g], v.gd[g], threads, v.gJ[g] != 0);
     if (gather && !sweep_gathers(v, g)) // gathered after the resampling
         gather = 0;
+    // more than 16 waves to a CU only for small workgroups (see k_sweep4)
+    const int w = threads / 64, blocks = (int)(kLdsPerCu / lds);
+    const bool four = w > 2 || blocks * w <= kWavesPerCu;
     if (v.gd[g] == 3)
-        return pa_sweep3_launch(v.runs, v.gcol[g], v.gncol[g], threads, lds, st, v.gJ[g] != 0, theta, t0, gather, walk);
-    if (v.gJ[g])
-        k_sweep<2, true><<<v.gncol[g], threads, lds, st>>>(v.runs, v.gcol[g], theta, t0, gather, walk);
-    else
-        k_sweep<2, false><<<v.gncol[g], threads, lds, st>>>(v.runs, v.gcol[g], theta, t0, gather, walk);
-    return hipGetLastError();
+        return pa_sweep3_launch(v.runs, v.gcol[g], v.gncol[g], threads, lds, st, v.gJ[g] != 0, theta, t0, gather, walk,
+                                four);
+    return v.gJ[g] ? sweep_start<2, true>(v.runs, v.gcol[g], v.gncol[g], threads, lds, st, theta, t0, gather, walk, four)
+                   : sweep_start<2, false>(v.runs, v.gcol[g], v.gncol[g], threads, lds, st, theta, t0, gather, walk,
+                                           four);
 }
 
 } // namespace

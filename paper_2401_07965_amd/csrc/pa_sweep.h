@@ -348,10 +348,71 @@ __device__ __forceinline__ void queue_drain(const WaveQueue &Q, const PlaneCtx &
     }
 }
 
+// One level of the reduction below: adds the partner lane's planes (o) to c,
+// PL planes in, PL + 1 out.
+template <int PL>
+__device__ __forceinline__ void count_add(uint32_t (&c)[14], const uint32_t (&o)[14])
+{
+    uint32_t carry = 0;
+#pragma unroll
+    for (int k = 0; k < PL; ++k) {
+        const uint32_t sum = pa_bop3<kXor3>(c[k], o[k], carry);
+        carry = pa_bop3<kMaj>(c[k], o[k], carry);
+        c[k] = sum;
+    }
+    c[PL] = carry;
+}
+
+// Wave sums of two bit-sliced counters (per-lane counts below 2^8): lane l gets
+// the 14 planes of a (l even) or b (l odd) for replicas 0..31 (bit 1 of l clear)
+// or 32..63.  The lanes share the work: the first exchange leaves each lane
+// one of the counters, the second one half of its replicas, and only then do
+// all planes go through the remaining four levels, as 32-bit words.  About a
+// third of the instructions of a 64-bit butterfly per counter (which were 2.7 %
+// of a sweep launch at 3D L = 10, theta = 10, and more on small lattices).
+__device__ __forceinline__ void wave_count2(const uint64_t (&a)[8], const uint64_t (&b)[8], uint32_t (&c)[14])
+{
+    const bool odd = (threadIdx.x & 1) != 0, up = (threadIdx.x & 2) != 0;
+    uint64_t s[9], carry = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint64_t keep = odd ? b[k] : a[k], send = odd ? a[k] : b[k];
+        const uint64_t o = ((uint64_t)xlane<1>((uint32_t)(send >> 32)) << 32) | xlane<1>((uint32_t)send);
+        s[k] = pa_bop3<kXor3>(keep, o, carry);
+        carry = pa_bop3<kMaj>(keep, o, carry);
+    }
+    s[8] = carry;
+    uint32_t o[14];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const uint32_t lo = (uint32_t)s[k], hi = (uint32_t)(s[k] >> 32);
+        c[k] = up ? hi : lo;
+        o[k] = xlane<2>(up ? lo : hi);
+    }
+    count_add<9>(c, o);
+    // the lanes of a row that agree in their two low bits: rotations by 8 and 4
+#pragma unroll
+    for (int k = 0; k < 10; ++k)
+        o[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c[k], 0x128, 0xF, 0xF, false);
+    count_add<10>(c, o);
+#pragma unroll
+    for (int k = 0; k < 11; ++k)
+        o[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c[k], 0x124, 0xF, 0xF, false);
+    count_add<11>(c, o);
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+        o[k] = xlane<16>(c[k]);
+    count_add<12>(c, o);
+#pragma unroll
+    for (int k = 0; k < 13; ++k)
+        o[k] = xlane<32>(c[k]);
+    count_add<13>(c, o);
+}
+
 // Recount of a column after its updates: each replica's unsatisfied-bond
 // count U and number of down spins, bit-sliced (forward bonds once each, two
 // sites per pass added with full adders, then a wave butterfly and the waves'
-// partial counts in red[32 per wave]): E = 2U - dN, M = N - 2 n_down.  Also
+// partial counts in red (32 words per wave)): E = 2U - dN, M = N - 2 n_down.  Also
 // writes the lattice back to g.  Per-lane counts stay below 2^8: at most
 // ceil(N / blockDim) sites per lane, d bonds each (the launch checks).
 // jbits(t, x, y, z): site t's bond bits (bit mu: to s + e_mu).
@@ -403,34 +464,24 @@ __device__ __forceinline__ void recount_column(const uint64_t *lat, JBits jbits,
         }
         vadd2_at<0>(vm, S[0], S[1]);
     }
-    // the two bit-sliced counts reduced one after the other (fewer live registers)
     const int wave = tid >> 6, lane = tid & 63, nw = bs >> 6;
-    {
-        uint64_t c[16];
+    uint32_t *red32 = reinterpret_cast<uint32_t *>(red); // [wave][bond counts, down spins][half][16 planes]
+    uint32_t c[14];
+    wave_count2(ve, vm, c);
+    if (lane < 4)
 #pragma unroll
-        for (int k = 0; k < 16; ++k)
-            c[k] = k < 8 ? ve[k] : 0;
-        wave_vsum16(c);
-        if (lane == 0)
-#pragma unroll
-            for (int k = 0; k < 16; ++k)
-                red[wave * 32 + k] = c[k];
-#pragma unroll
-        for (int k = 0; k < 16; ++k)
-            c[k] = k < 8 ? vm[k] : 0;
-        wave_vsum16(c);
-        if (lane == 0)
-#pragma unroll
-            for (int k = 0; k < 16; ++k)
-                red[wave * 32 + 16 + k] = c[k];
-    }
+        for (int k = 0; k < 14; ++k)
+            red32[wave * 64 + (lane & 1) * 32 + (lane >> 1) * 16 + k] = c[k];
     __syncthreads();
     if (wave == 0) {
         uint32_t U = 0, nd = 0;
-        for (int v = 0; v < nw; ++v)
-            for (int k = 0; k < 16; ++k) {
-                U += (uint32_t)((red[v * 32 + k] >> lane) & 1u) << k;
-                nd += (uint32_t)((red[v * 32 + 16 + k] >> lane) & 1u) << k;
+        const uint32_t *p = red32 + (lane >> 5) * 16; // this replica's half
+        const uint32_t bit = (uint32_t)lane & 31u;
+        for (int v = 0; v < nw; ++v, p += 64)
+#pragma unroll
+            for (int k = 0; k < 14; ++k) {
+                U += __builtin_amdgcn_ubfe(p[k], bit, 1u) << k;
+                nd += __builtin_amdgcn_ubfe(p[32 + k], bit, 1u) << k;
             }
         const int64_t r = 64 * (int64_t)w + lane;
         if (r < Rlive) {
@@ -867,9 +918,8 @@ __device__ __forceinline__ void gather_sites(const uint64_t *src, int N, const G
 // M = N - 2 n_down.  theta = 0 only measures.  J: the run has +-J couplings
 // (per-site bond masks in LDS); without, every bond is ferromagnetic.
 template <int D, bool J>
-__global__ __launch_bounds__(kSweepMaxThreads) void k_sweep(const PaRunDesc *__restrict__ runs,
-                                                            const PaBlk *__restrict__ map, int theta, uint32_t t0,
-                                                            int gather, int walk)
+__device__ __forceinline__ void sweep_column(const PaRunDesc *__restrict__ runs, const PaBlk *__restrict__ map,
+                                             int theta, uint32_t t0, int gather, int walk)
 {
     // dynamic LDS: lattice [N] u64 | queues [waves][3][kQueue] u64 | queue sites [waves][kQueue] u32 |
     // threshold-bit table [16][4 or 8] u32 | site table [N] u32 (kWalkTable), else jmask [N]
@@ -990,8 +1040,41 @@ __global__ __launch_bounds__(kSweepMaxThreads) void k_sweep(const PaRunDesc *__r
     recount_column<D, J>(lat, jbits, g, lat + N, rd, cur, w, Rlive, L, N, LL, mL);
 }
 
+// The kernel in two register allocations.  Its registers would allow 5 (3D) to
+// 7 (2D) waves per SIMD.  Where LDS holds fewer workgroups than that, they
+// spread unevenly over the SIMDs (3D L = 10: 8 workgroups of two waves per CU
+// ran 6 % slower than with at most four waves to a SIMD), so k_sweep4 claims
+// registers for four; k_sweep runs where LDS lets more than 16 waves of one or
+// two-wave workgroups share a CU (3D L = 8 5 % faster than with four to a
+// SIMD, 2D L = 16 5 %).
+template <int D, bool J>
+__global__ __launch_bounds__(kSweepMaxThreads) void k_sweep(const PaRunDesc *__restrict__ runs,
+                                                            const PaBlk *__restrict__ map, int theta, uint32_t t0,
+                                                            int gather, int walk)
+{
+    sweep_column<D, J>(runs, map, theta, t0, gather, walk);
+}
+
+template <int D, bool J>
+__global__ __launch_bounds__(kSweepMaxThreads) __attribute__((amdgpu_waves_per_eu(3, 4))) void k_sweep4(
+    const PaRunDesc *__restrict__ runs, const PaBlk *__restrict__ map, int theta, uint32_t t0, int gather, int walk)
+{
+    sweep_column<D, J>(runs, map, theta, t0, gather, walk);
+}
+
+template <int D, bool J>
+hipError_t sweep_start(const PaRunDesc *runs, const PaBlk *map, int nblocks, int threads, size_t lds, hipStream_t st,
+                       int theta, uint32_t t0, int gather, int walk, bool four)
+{
+    if (four)
+        k_sweep4<D, J><<<nblocks, threads, lds, st>>>(runs, map, theta, t0, gather, walk);
+    else
+        k_sweep<D, J><<<nblocks, threads, lds, st>>>(runs, map, theta, t0, gather, walk);
+    return hipGetLastError();
+}
+
 } // namespace
 
-// Launches k_sweep<3, J> (defined in pa_sweep3.hip).
+// Launches the 3D sweeps (defined in pa_sweep3.hip); four: k_sweep4.
 hipError_t pa_sweep3_launch(const PaRunDesc *runs, const PaBlk *map, int nblocks, int threads, size_t lds,
-                            hipStream_t st, bool J, int theta, uint32_t t0, int gather, int walk);
+                            hipStream_t st, bool J, int theta, uint32_t t0, int gather, int walk, bool four);

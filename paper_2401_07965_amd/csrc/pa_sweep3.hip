@@ -5,11 +5,8 @@
 #include "pa_sweep.h"
 
 hipError_t pa_sweep3_launch(const PaRunDesc *runs, const PaBlk *map, int nblocks, int threads, size_t lds,
-                            hipStream_t st, bool J, int theta, uint32_t t0, int gather, int walk)
+                            hipStream_t st, bool J, int theta, uint32_t t0, int gather, int walk, bool four)
 {
-    if (J)
-        k_sweep<3, true><<<nblocks, threads, lds, st>>>(runs, map, theta, t0, gather, walk);
-    else
-        k_sweep<3, false><<<nblocks, threads, lds, st>>>(runs, map, theta, t0, gather, walk);
-    return hipGetLastError();
+    return J ? sweep_start<3, true>(runs, map, nblocks, threads, lds, st, theta, t0, gather, walk, four)
+             : sweep_start<3, false>(runs, map, nblocks, threads, lds, st, theta, t0, gather, walk, four);
 }
