@@ -1797,14 +1797,17 @@ __global__ __launch_bounds__(kThreads) void k_gather_meta(const PaRunDesc *__res
 // with the energies, magnetisations and labels (every run's spins move now).
 // Otherwise: after the commit, the spins a resampling left for the sweeps
 // (PaRecord::gather), from the other buffer into the current one.
+// kGatherThreads lanes with up to eight site pairs each: an item's bookkeeping
+// (its scalars and branches) is spread over 16 words a lane; 256 lanes
+// with four or eight pairs ran 2 % and 15 % slower at 3D L = 16, R = 10^6,
+// dbeta = 0.01.
+constexpr int kGatherThreads = 128;
 template <bool PRE>
-__global__ __launch_bounds__(kThreads) void k_gather_spins(const PaRunDesc *__restrict__ runs,
+__global__ __launch_bounds__(kGatherThreads) void k_gather_spins(const PaRunDesc *__restrict__ runs,
                                                            const PaBlk *__restrict__ map)
 {
-    __shared__ uint64_t g_mask[64];
-    __shared__ uint32_t g_word[64];
-    __shared__ int g_shift[64];
-    __shared__ int s_ngroups;
+    __shared__ uint32_t g_word[64], g_code[64], g_mask[64];
+    __shared__ int g_n;
     // an output word takes bits of the source words its ancestors lie in, the
     // same words as its neighbours: neighbouring words go to one XCD
     const PaBlk blk = map[xcd_contiguous(blockIdx.x, gridDim.x)];
@@ -1828,12 +1831,16 @@ __global__ __launch_bounds__(kThreads) void k_gather_spins(const PaRunDesc *__re
             rd.dv.label[cur ^ 1][d] = rd.dv.label[cur][a];
         }
     }
-    const GatherGroups G = {g_mask, g_word, g_shift, &s_ngroups};
-    gather_groups(rd.dv.anc, w, R, G);
+    const GatherItems G = {g_word, g_code, g_mask, &g_n};
+    gather_items(rd.dv.anc, w, R, G);
     __syncthreads();
     __attribute__((address_space(1))) pa_u64x2 *dst =
         (__attribute__((address_space(1))) pa_u64x2 *)(rd.dv.spins[from ^ 1] + (size_t)w * N);
-    gather_sites(rd.dv.spins[from], N, G, [&](int p, pa_u64x2 v) { dst[p] = v; });
+    auto put = [&](int p, pa_u64x2 v) { dst[p] = v; };
+    if (N > 8 * (int)blockDim.x) // more than four site pairs per thread
+        gather_sites<8>(rd.dv.spins[from], N, G, put);
+    else
+        gather_sites<4>(rd.dv.spins[from], N, G, put);
 }
 
 // A kept population takes its new log-weights x_j + m (m = 0 if it was uniform).
@@ -2596,7 +2603,7 @@ hipError_t pa_b_gather(const PaBatchView &v)
 {
     for (int g = 0; g < v.ngroups; ++g)
         if (v.gncol[g] && sweep_gathers(v, g))
-            k_gather_spins<false><<<v.gncol[g], kThreads, 0, v.stream>>>(v.runs, v.gcol[g]);
+            k_gather_spins<false><<<v.gncol[g], kGatherThreads, 0, v.stream>>>(v.runs, v.gcol[g]);
     return hipGetLastError();
 }
 
@@ -2725,13 +2732,13 @@ hipError_t pa_b_resample(const PaBatchView &v, int scheme, int freeze, int kq, b
     if (any)
         k_gather_meta<<<v.nrep, kThreads, 0, v.stream>>>(v.runs, v.rep);
     else
-        k_gather_spins<true><<<v.ncol, kThreads, 0, v.stream>>>(v.runs, v.col);
+        k_gather_spins<true><<<v.ncol, kGatherThreads, 0, v.stream>>>(v.runs, v.col);
     if (kq >= 0)
         k_keep<<<v.nrep, kThreads, 0, v.stream>>>(v.runs, v.rep);
     k_commit<<<v.nruns, kThreads, 0, v.stream>>>(v.runs, freeze, any ? 0 : 1);
     for (int g = 0; any && g < v.ngroups; ++g)
         if (v.gncol[g] && !sweep_gathers(v, g))
-            k_gather_spins<false><<<v.gncol[g], kThreads, 0, v.stream>>>(v.runs, v.gcol[g]);
+            k_gather_spins<false><<<v.gncol[g], kGatherThreads, 0, v.stream>>>(v.runs, v.gcol[g]);
     return hipGetLastError();
 }
 

@@ -811,103 +811,160 @@ __device__ __forceinline__ void load_jmask(uint8_t *jl, const uint8_t *jm, int N
                            N >> 2);
 }
 
-// Destination word column w takes the bits of its 64 ancestors.  Bit b comes
-// from bit (a_b & 63) of source word a_b >> 6, i.e. from that word shifted by
-// delta_b = (a_b & 63) - b.  Bits sharing (source word, delta) form one group:
-// one shift, mask and or per group per site.  Ancestors are non-decreasing, so
-// delta moves by one per dropped or repeated replica and a column has few
-// groups (fewer than its runs of consecutive ancestors), listed in order of
-// source word.  The group lists live in LDS.
-struct GatherGroups {
-    uint64_t *mask; // [64]
-    uint32_t *word; // [64]
-    int *shift;     // [64]
+// Destination word column w takes the bits of its 64 ancestors: bit b comes
+// from bit a_b & 63 of source word a_b >> 6.  The bits of a destination half
+// (32 of them) are listed as items of two instructions per site each:
+//  - bits that share the source word and the distance (a_b & 63) - b are one
+//    window of that word, shifted into place (one funnel shift) and masked;
+//    ancestors are non-decreasing, so the distance moves by one per dropped or
+//    repeated replica and a half has few;
+//  - kCopies or more copies of one ancestor are one source bit, spread over
+//    their mask (one signed bit-field extract), where windows would take an
+//    item per copy.
+// The gather moves memory, but windows of whole 64-bit words alone took more
+// time than the memory where few replicas take most copies (45 of them per
+// word at sd(tau) = 2.2 in its logarithm, against 18 items of half the width):
+// 3D L = 16, R = 10^6, dbeta = 0.02 410 -> 240 us, dbeta = 0.01 238 -> 235 (a
+// copy of the same bytes takes 226), dbeta = 0.005 200 -> 208.  The item lists
+// live in LDS, in order of source word.
+struct GatherItems {
+    uint32_t *word; // [64] source word
+    uint32_t *code; // [64] kind | shift << 8
+    uint32_t *mask; // [64] bits of the destination half
     int *n;         // [1]
 };
+constexpr int kCopies = 4;
+// Item kinds (+ kItemHigh: into the high half): the window from the two halves
+// of the source word, from its high half, from its low half; a bit of its low
+// half, of its high half.
+constexpr uint32_t kItemBoth = 0, kItemHi = 1, kItemLo = 2, kItemBitLo = 3, kItemBitHi = 4, kItemHigh = 8;
 
-// Wave 0 lists the groups of destination word w (replicas 64 w + b below R,
+// Wave 0 lists the items of destination word w (replicas 64 w + b below R,
 // ancestors anc); the caller synchronises the workgroup before they are read.
-__device__ __forceinline__ void gather_groups(const uint32_t *anc, uint32_t w, int64_t R, const GatherGroups &G)
+__device__ __forceinline__ void gather_items(const uint32_t *anc, uint32_t w, int64_t R, const GatherItems &G)
 {
     if (threadIdx.x >= 64)
         return;
-    const int b = threadIdx.x;
+    const int b = threadIdx.x, h = b >> 5;
     const int64_t d = 64 * (int64_t)w + b;
     const bool valid = d < R;
-    const uint32_t a = valid ? anc[d] : 0u;
+    const uint32_t a = valid ? anc[d] : 0xFFFFFFFFu; // (past the population: not equal to an ancestor)
     const uint32_t q = a >> 6;
     const int dl = (int)(a & 63u) - b;
+    // the run of copies of this ancestor within the half: [first, last]
+    const uint32_t prev = (uint32_t)__shfl_up((int)a, 1, 64);
+    const uint64_t starts = __ballot((b & 31) == 0 || a != prev);
+    const uint64_t upto = (2ull << b) - 1ull; // bits 0..b (b = 63: all)
+    const int first = 63 - __clzll((long long)(starts & upto));
+    const uint64_t above = starts & ~upto;
+    const int last = above ? __ffsll((long long)above) - 2 : 63;
+    const bool copies = last - first + 1 >= kCopies;
+    const uint64_t run = ((2ull << last) - 1ull) & ~((1ull << first) - 1ull);
+    const int win = 32 * h + dl; // the window starts at this bit of the source word
+    const uint32_t sb = a & 63u;
+    const uint32_t kind = copies ? (sb < 32u ? kItemBitLo : kItemBitHi)
+                                 : (win < 0 ? kItemLo : (win < 32 ? kItemBoth : kItemHi));
+    const uint32_t sh = copies ? sb & 31u : (uint32_t)win & 31u;
+    const uint32_t code = kind | (h ? kItemHigh : 0u) | (sh << 8);
     uint64_t rem = __ballot(valid);
-    int ng = 0;
-    while (rem) { // wave-uniform: one group per pass, led by the lowest remaining lane
+    int n = 0;
+    while (rem) { // wave-uniform: one item per pass, led by the lowest remaining lane
         const int l = __ffsll((long long)rem) - 1;
-        const uint32_t ql = (uint32_t)__shfl((int)q, l, 64);
-        const int dll = __shfl(dl, l, 64);
-        const uint64_t m = __ballot(valid && q == ql && dl == dll);
+        const uint32_t ql = (uint32_t)__builtin_amdgcn_readlane((int)q, l);
+        const uint32_t cl = (uint32_t)__builtin_amdgcn_readlane((int)code, l);
+        const int dll = __builtin_amdgcn_readlane(dl, l), hl = l >> 5;
+        uint64_t m;
+        if (__builtin_amdgcn_readlane((int)copies, l)) // (the lowest lane of its run)
+            m = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(run >> 32), l) << 32) |
+                (uint32_t)__builtin_amdgcn_readlane((int)run, l);
+        else
+            m = __ballot(valid && !copies && q == ql && dl == dll && h == hl);
         if (b == 0) {
-            G.word[ng] = ql;
-            G.shift[ng] = dll;
-            G.mask[ng] = m;
+            G.word[n] = ql;
+            G.code[n] = cl;
+            G.mask[n] = (uint32_t)(hl ? m >> 32 : m);
         }
         rem &= ~m;
-        ++ng;
+        ++n;
     }
     if (b == 0)
-        *G.n = ng;
+        *G.n = n;
 }
 
 typedef uint64_t pa_u64x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t pa_u32x4 __attribute__((ext_vector_type(4))); // two sites' words, low half first
 
 // Every thread: the destination word's sites from the source words (column
 // sw at src + sw N), kP site pairs at a time with one 16-byte load each, in
 // flight together (a lane past the end loads the last pair again and stores
 // nothing: no load under a branch); store(p, v) keeps site pair p.
-template <typename Store>
-__device__ __forceinline__ void gather_sites(const uint64_t *src, int N, const GatherGroups &G, Store store)
+template <int kP, typename Store>
+__device__ __forceinline__ void gather_sites(const uint64_t *src, int N, const GatherItems &G, Store store)
 {
-    typedef const __attribute__((address_space(1))) pa_u64x2 g_u64x2;
-    constexpr int kP = 4;
-    const int ng = uni(*G.n);
+    typedef const __attribute__((address_space(1))) pa_u32x4 g_u32x4;
+    constexpr int kPut = PA_T3((PA_A & PA_B) | PA_C);
+    const int n = uni(*G.n), lane = threadIdx.x & 63;
+    // lane i of every wave holds item i; they are read across lanes, so whole
+    // waves stay in the loop below, lanes past the last pair too
+    const uint32_t word = G.word[lane], code = G.code[lane], mask = G.mask[lane];
     const int nt = (int)blockDim.x;
     const int np = N >> 1; // N is a multiple of 4 (L even)
-    g_u64x2 *src2 = (g_u64x2 *)src;
-    for (int p0 = threadIdx.x; p0 < np; p0 += kP * nt) {
-        pa_u64x2 out[kP], v[kP];
+    g_u32x4 *src2 = (g_u32x4 *)src;
+    for (int w0 = uni((int)threadIdx.x - lane); w0 < np; w0 += kP * nt) {
+        const int p0 = w0 + lane;
+        uint32_t out[kP][4] = {};
+        pa_u32x4 v[kP];
 #pragma unroll
-        for (int k = 0; k < kP; ++k) {
-            out[k] = pa_u64x2{0ull, 0ull};
-            v[k] = out[k];
-        }
+        for (int k = 0; k < kP; ++k)
+            v[k] = pa_u32x4{0u, 0u, 0u, 0u};
         uint32_t last = 0xFFFFFFFFu;
-        for (int i = 0; i < ng; ++i) {
-            const uint32_t sw = uni(G.word[i]);
+        for (int i = 0; i < n; ++i) {
+            const uint32_t sw = (uint32_t)__builtin_amdgcn_readlane((int)word, i);
+            const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)code, i), sh = c >> 8;
+            const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)mask, i);
             if (sw != last) {
 #pragma unroll
                 for (int k = 0; k < kP; ++k)
                     v[k] = src2[(size_t)sw * np + min(p0 + k * nt, np - 1)];
                 last = sw;
             }
-            const int sh = uni(G.shift[i]);
-            const uint64_t mask = uni64(G.mask[i]);
-            if (sh >= 0) {
+            auto put = [&](auto high, auto bits) { // bits(lo, hi): the half's candidate bits
+                constexpr int H = decltype(high)::value;
 #pragma unroll
                 for (int k = 0; k < kP; ++k) {
-                    out[k].x = pa_bop3<PA_T3((PA_A & PA_B) | PA_C)>(v[k].x >> sh, mask, out[k].x);
-                    out[k].y = pa_bop3<PA_T3((PA_A & PA_B) | PA_C)>(v[k].y >> sh, mask, out[k].y);
+                    out[k][H] = pa_bop3<kPut>(bits(v[k].x, v[k].y), m, out[k][H]);
+                    out[k][2 + H] = pa_bop3<kPut>(bits(v[k].z, v[k].w), m, out[k][2 + H]);
                 }
-            } else {
-#pragma unroll
-                for (int k = 0; k < kP; ++k) {
-                    out[k].x = pa_bop3<PA_T3((PA_A & PA_B) | PA_C)>(v[k].x << -sh, mask, out[k].x);
-                    out[k].y = pa_bop3<PA_T3((PA_A & PA_B) | PA_C)>(v[k].y << -sh, mask, out[k].y);
+            };
+            auto half = [&](auto high) {
+                switch (c & 7u) {
+                case kItemBoth:
+                    put(high, [&](uint32_t lo, uint32_t hi) { return __builtin_amdgcn_alignbit(hi, lo, sh); });
+                    break;
+                case kItemHi:
+                    put(high, [&](uint32_t, uint32_t hi) { return hi >> sh; });
+                    break;
+                case kItemLo:
+                    put(high, [&](uint32_t lo, uint32_t) { return __builtin_amdgcn_alignbit(lo, 0u, sh); });
+                    break;
+                case kItemBitLo:
+                    put(high, [&](uint32_t lo, uint32_t) { return (uint32_t)__builtin_amdgcn_sbfe((int)lo, sh, 1u); });
+                    break;
+                default:
+                    put(high, [&](uint32_t, uint32_t hi) { return (uint32_t)__builtin_amdgcn_sbfe((int)hi, sh, 1u); });
+                    break;
                 }
-            }
+            };
+            if (c & kItemHigh)
+                half(std::integral_constant<int, 1>{});
+            else
+                half(std::integral_constant<int, 0>{});
         }
 #pragma unroll
         for (int k = 0; k < kP; ++k) {
             const int p = p0 + k * nt;
             if (p < np)
-                store(p, out[k]);
+                store(p, pa_u64x2{((uint64_t)out[k][1] << 32) | out[k][0], ((uint64_t)out[k][3] << 32) | out[k][2]});
         }
     }
 }
@@ -954,15 +1011,14 @@ __device__ __forceinline__ void sweep_column(const PaRunDesc *__restrict__ runs,
     }
     if (gather && uni(rec->gather) != 0u) {
         // the column of a resampled population, gathered from the other
-        // buffer into LDS (the group lists in wave 0's queue space, unused
+        // buffer into LDS (the item lists in wave 0's queue space, unused
         // until the sweeps)
-        uint64_t *gq = lat + N;
-        uint32_t *gw = reinterpret_cast<uint32_t *>(gq + 64);
-        const GatherGroups G = {gq, gw, reinterpret_cast<int *>(gw + 64), reinterpret_cast<int *>(gw + 128)};
-        gather_groups(rd.dv.anc, w, Rlive, G);
+        uint32_t *gq = reinterpret_cast<uint32_t *>(lat + N);
+        const GatherItems G = {gq, gq + 64, gq + 128, reinterpret_cast<int *>(gq + 192)};
+        gather_items(rd.dv.anc, w, Rlive, G);
         __syncthreads();
         pa_u64x2 *dst = reinterpret_cast<pa_u64x2 *>(lat);
-        gather_sites(rd.dv.spins[cur ^ 1], N, G, [&](int p, pa_u64x2 v) { dst[p] = v; });
+        gather_sites<4>(rd.dv.spins[cur ^ 1], N, G, [&](int p, pa_u64x2 v) { dst[p] = v; });
     } else {
         load_column(lat, g, N);
     }
