@@ -131,6 +131,44 @@ int default_sweep_threads(int N, int d, bool J)
     return best ? best : 768; // none fits: rejected by the LDS check of the batch set-up
 }
 
+// Default size where the batch's columns leave the chip short of workgroups
+// (at most two columns per CU): a column then has a CU's waves nearly to
+// itself, and more lanes per column finish it sooner, until its waves (or the
+// two columns' together) fill the SIMDs.  The size with the least modelled
+// time of a colour: rounds of sites, each the longer of one wave's latency
+// (1800 cycles for a site pass) and its SIMD's waves taking turns (1160 cycles
+// a wave), and the end of the colour (2500 cycles, 600 per wave and SIMD).
+// Measured, theta = 10, R = 2 10^4 (313 columns): 3D L = 16 227 -> 208 us, 3D
+// L = 10 130 -> 88, 2D L = 32 111 -> 74, 2D L = 24 glass 100 -> 71.
+int few_columns_threads(int N, int d, bool J, int64_t columns)
+{
+    constexpr int kCus = 256, kWaves = 16;
+    const int lds_max = g_max_lds ? g_max_lds : kLdsPerCu;
+    const int per_cu = (int)((columns + kCus - 1) / kCus), nh = N / 2;
+    int best = 0;
+    double best_t = 0.0;
+    for (int t = 64; t <= 768; t += 64) {
+        const size_t lds = pa_sweep_lds_bytes(N, d, t, J);
+        const int waves = per_cu * (t / 64);
+        if (!sweep_threads_ok(N, d, t) || lds > (size_t)lds_max || lds * per_cu > (size_t)kLdsPerCu || waves > kWaves)
+            continue;
+        const double ws = (waves + 3) / 4, passes = (nh + t - 1) / t;
+        const double time = passes * std::hypot(1800.0, 1160.0 * ws) + 2500.0 + 600.0 * ws;
+        if (!best || time < best_t - 1e-9) {
+            best_t = time;
+            best = t;
+        }
+    }
+    return best;
+}
+
+// Default sweep workgroup size of a group in a batch of `columns` 64-replica columns.
+int group_sweep_threads(int N, int d, bool J, int64_t columns)
+{
+    const int few = columns <= 2 * 256 ? few_columns_threads(N, d, J, columns) : 0;
+    return few ? few : default_sweep_threads(N, d, J);
+}
+
 uint64_t round256(uint64_t b) { return (b + 255) / 256 * 256; }
 
 // Buffers of one run (base may be null to only measure them).
@@ -347,6 +385,9 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
     Tables tb;
     std::map<std::tuple<int, int, int>, int> group_of_shape;
     std::vector<int> run_group(M);
+    int64_t columns = 0; // of all runs at their target sizes
+    for (const Geometry &g : geo)
+        columns += (g.R + 63) / 64;
     for (int m = 0; m < M; ++m) {
         const Geometry &g = geo[m];
         for (int64_t c = 0; c < (g.cap + PA_CHUNK - 1) / PA_CHUNK; ++c)
@@ -369,7 +410,7 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
             tb.gd.push_back(g.d);
             tb.gN.push_back(g.N);
             tb.gJ.push_back(g.J);
-            tb.gthreads.push_back(default_sweep_threads(g.N, g.d, g.J != 0));
+            tb.gthreads.push_back(group_sweep_threads(g.N, g.d, g.J != 0, columns));
         }
         for (int64_t w = 0; w < g.W; ++w)
             tb.gcol[it->second].push_back({(uint32_t)m, (uint32_t)w});
