@@ -484,6 +484,9 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
             v.gJ[g] = tb.gJ[g];
             v.gthreads[g] = tb.gthreads[g];
         }
+        for (int g = 0; g < v.ngroups; ++g)
+            v.gorder[g] = g;
+        std::stable_sort(v.gorder, v.gorder + v.ngroups, [&](int a, int c) { return v.gN[a] > v.gN[c]; });
         v.steprec = (PaStepRecord *)p_steprec;
         v.npoints = max_points;
         b->dgroup = (int32_t *)p_group;

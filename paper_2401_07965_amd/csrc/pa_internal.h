@@ -188,6 +188,7 @@ struct PaBatchView {
     const PaBlk *gcol[PA_MAX_GROUPS];
     uint32_t gncol[PA_MAX_GROUPS];
     int gd[PA_MAX_GROUPS], gN[PA_MAX_GROUPS], gJ[PA_MAX_GROUPS], gthreads[PA_MAX_GROUPS];
+    int gorder[PA_MAX_GROUPS]; // the groups, largest lattice first (their sweeps start in this order)
     bool weights;          // some run may hold a weighted population (conditional resampling)
     PaStepRecord *steprec; // batched anneal: [nruns][npoints]
     int npoints;

@@ -2616,9 +2616,11 @@ hipError_t pa_b_sweep(const PaBatchView &v, int theta, uint32_t t0, int gather)
         return e;
     }
     // the groups are independent: each on its own stream, so that one group's
-    // last partly filled round of workgroups overlaps the others' work
+    // last partly filled round of workgroups overlaps the others' work, the
+    // longest columns first (a launch that starts last ends last)
     e = hipEventRecord(v.fork, v.stream);
-    for (int g = 0; g < v.ngroups && e == hipSuccess; ++g) {
+    for (int i = 0; i < v.ngroups && e == hipSuccess; ++i) {
+        const int g = v.gorder[i];
         e = hipStreamWaitEvent(v.gstream[g], v.fork, 0);
         if (e == hipSuccess)
             e = sweep_launch(v, g, theta, v.gthreads[g], t0, v.gstream[g], gather);
