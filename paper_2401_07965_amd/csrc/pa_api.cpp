@@ -374,6 +374,7 @@ pa_status hip_fail(Batch *b, hipError_t e, const char *where)
 
 // Whole layout of a batch: tables first, then each run's buffers.
 struct Tables {
+    std::vector<uint32_t> list; // run indices, the large runs first
     std::vector<PaBlk> rep, hrep, crep, fam, col, tile;
     std::vector<std::vector<PaBlk>> gcol;
     std::vector<int> gd, gN, gJ, gthreads;
@@ -388,20 +389,36 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
     int64_t columns = 0; // of all runs at their target sizes
     for (const Geometry &g : geo)
         columns += (g.R + 63) / 64;
-    for (int m = 0; m < M; ++m) {
+    for (int small = 0; small < 2; ++small)
+        for (int m = 0; m < M; ++m)
+            if ((geo[m].cap <= PA_SMALL_CAP) == (small != 0))
+                tb.list.push_back((uint32_t)m);
+    uint32_t nlarge = 0, nhrep_large = 0, nfam_large = 0;
+    int64_t small_cap = 0;
+    for (const uint32_t m : tb.list) {
         const Geometry &g = geo[m];
         for (int64_t c = 0; c < (g.cap + PA_CHUNK - 1) / PA_CHUNK; ++c)
             tb.rep.push_back({(uint32_t)m, (uint32_t)c});
-        for (int64_t c = 0; c < (g.cap + PA_HCHUNK - 1) / PA_HCHUNK; ++c)
+        for (int64_t c = 0; c < (g.cap + pa_counts_tile(g.cap) - 1) / pa_counts_tile(g.cap); ++c) {
             tb.hrep.push_back({(uint32_t)m, (uint32_t)c});
-        for (int64_t c = 0; c < (g.cap + pa_counts_tile(g.cap) - 1) / pa_counts_tile(g.cap); ++c)
             tb.crep.push_back({(uint32_t)m, (uint32_t)c});
+        }
         for (int64_t c = 0; c < (g.R + PA_HCHUNK - 1) / PA_HCHUNK; ++c)
             tb.fam.push_back({(uint32_t)m, (uint32_t)c});
         for (int64_t w = 0; w < g.W; ++w)
             tb.col.push_back({(uint32_t)m, (uint32_t)w});
         for (int64_t k = 0; k < (g.cap + PA_SCAN_TILE - 1) / PA_SCAN_TILE; ++k)
             tb.tile.push_back({(uint32_t)m, (uint32_t)k});
+        if (g.cap > PA_SMALL_CAP) {
+            ++nlarge;
+            nhrep_large = (uint32_t)tb.hrep.size();
+            nfam_large = (uint32_t)tb.fam.size();
+        } else {
+            small_cap = std::max(small_cap, g.cap);
+        }
+    }
+    for (int m = 0; m < M; ++m) { // groups and their columns in run order
+        const Geometry &g = geo[m];
         const auto key = std::make_tuple(g.d, g.L, g.J);
         auto it = group_of_shape.find(key);
         if (it == group_of_shape.end()) {
@@ -422,6 +439,7 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
         return p;
     };
     char *p_desc = take(sizeof(PaRunDesc) * (uint64_t)M);
+    char *p_list = take(sizeof(uint32_t) * tb.list.size());
     char *p_rep = take(sizeof(PaBlk) * tb.rep.size());
     char *p_hrep = take(sizeof(PaBlk) * tb.hrep.size());
     char *p_crep = take(sizeof(PaBlk) * tb.crep.size());
@@ -462,6 +480,11 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
         PaBatchView &v = b->v;
         v.runs = (const PaRunDesc *)p_desc;
         v.nruns = (uint32_t)M;
+        v.list = (const uint32_t *)p_list;
+        v.nlarge = nlarge;
+        v.nhrep_large = nhrep_large;
+        v.nfam_large = nfam_large;
+        v.small_cap = small_cap;
         v.rep = (const PaBlk *)p_rep;
         v.nrep = (uint32_t)tb.rep.size();
         v.hrep = (const PaBlk *)p_hrep;
@@ -608,6 +631,7 @@ pa_status make_batch(const pa_config *cfgs, int32_t nruns, int32_t max_points, v
     };
     e = hipSuccess;
     up(b->ddesc, b->hdesc.data(), sizeof(PaRunDesc) * nruns);
+    up(b->v.list, t.list.data(), sizeof(uint32_t) * t.list.size());
     up(b->v.rep, t.rep.data(), sizeof(PaBlk) * t.rep.size());
     up(b->v.hrep, t.hrep.data(), sizeof(PaBlk) * t.hrep.size());
     up(b->v.crep, t.crep.data(), sizeof(PaBlk) * t.crep.size());

@@ -91,15 +91,17 @@ struct PaScanTile {
 #define PA_SCAN_ITEMS 16
 #define PA_SCAN_TILE (PA_SCAN_THREADS * PA_SCAN_ITEMS)
 #define PA_CHUNK 1024  // replicas (or families) per workgroup of the per-replica kernels
-#define PA_HCHUNK 4096 // replicas per workgroup of the energy histogram (LDS-private counts)
+#define PA_HCHUNK 4096 // families per workgroup of the family statistics
+
+#define PA_SMALL_CAP 4096 // capacity of the runs whose passes over replicas one workgroup takes
 
 // Tile flags of a run's two prefix sums of a resampling (weights, copy
 // numbers): ceil(cap / PA_CHUNK) each, enough for tiles of PA_CHUNK or more
 // slots.
 __host__ __device__ inline int64_t pa_tiles_per_sum(int64_t cap) { return (cap + PA_CHUNK - 1) / PA_CHUNK; }
 
-// Replica slots per tile of the passes that sum the weights or draw and sum
-// nearest-integer or Poisson copy numbers: 4 per thread of 256, or 16 per
+// Replica slots per tile of the observables and of the passes that sum the
+// weights or draw and sum nearest-integer or Poisson copy numbers: 4 per thread of 256, or 16 per
 // thread once the run is large enough that the look-back over the smaller
 // tiles would take longer than the work.  A run's tiles depend on its
 // capacity alone, so a run's results do not depend on the batch it is in.
@@ -168,12 +170,17 @@ struct PaMlpDev {
 };
 
 // What the launchers need to address a batch (device pointers + counts).
+// Every block map lists the blocks of the large runs (capacity above
+// PA_SMALL_CAP) first; the counts *_large are theirs.
 struct PaBatchView {
     const PaRunDesc *runs; // [nruns]
     uint32_t nruns;
+    const uint32_t *list;  // [nruns] run indices, the large runs first
+    uint32_t nlarge, nhrep_large, nfam_large;
+    int64_t small_cap; // largest capacity of the small runs
     const PaBlk *rep;  // chunks of PA_CHUNK replica slots (capacity)
     uint32_t nrep;
-    const PaBlk *hrep; // chunks of PA_HCHUNK replica slots (histogram)
+    const PaBlk *hrep; // chunks of pa_counts_tile replica slots (histogram, observables)
     uint32_t nhrep;
     const PaBlk *crep; // tiles of the copy-number pass (pa_counts_tile slots)
     uint32_t ncrep;

@@ -388,7 +388,7 @@ __global__ __launch_bounds__(kThreads) void k_hist(const PaRunDesc *__restrict__
     const PaRunDesc &rd = runs[b.run];
     PaRecord *rec = rd.dv.rec;
     const int64_t R = (int64_t)rec->Rcur;
-    const int64_t beg = (int64_t)b.idx * PA_HCHUNK;
+    const int64_t tile = pa_counts_tile(rd.cap), beg = (int64_t)b.idx * tile;
     if (beg >= R || frozen(rec))
         return;
     const int H = rd.H, DN = rd.d * rd.N;
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(kThreads) void k_hist(const PaRunDesc *__restrict__
         lh[i] = 0;
     __syncthreads();
     int64_t lo = INT_MAX, hi = INT_MIN;
-    const int64_t end = beg + PA_HCHUNK < R ? beg + PA_HCHUNK : R;
+    const int64_t end = beg + tile < R ? beg + tile : R;
     for (int64_t j = beg + threadIdx.x; j < end; j += blockDim.x) {
         const int32_t e = E[j];
         atomicAdd(&lh[(e + DN) >> 2], 1u);
@@ -1940,16 +1940,19 @@ __global__ __launch_bounds__(kThreads) void k_obs_rep(const PaRunDesc *__restric
     __shared__ double sd[16 * PA_WPARTS];
     __shared__ uint32_t lh[kObsLevels];
     __shared__ int s_lo[kThreads / 64], s_hi[kThreads / 64];
-    // PA_HCHUNK replica slots per workgroup (four chunks): fewer workgroups
-    // merge their level counts and sums into the run's, on the same addresses
+    // pa_counts_tile replica slots per workgroup: four chunks where the run
+    // fills the chip so (fewer workgroups merge their level counts and sums
+    // into the run's, on the same addresses), else one (R = 20011 on five
+    // workgroups took 19.4 us, on twenty 10.9; R = 10^5 19.9 -> 12.4)
     RepCtx c;
     {
         const PaBlk b = map[blockIdx.x];
         c.rd = runs + b.run;
         c.rec = c.rd->dv.rec;
         const int64_t R = (int64_t)c.rec->Rcur;
-        c.beg = (int64_t)b.idx * PA_HCHUNK;
-        c.end = c.beg + PA_HCHUNK < R ? c.beg + PA_HCHUNK : R;
+        const int64_t tile = pa_counts_tile(c.rd->cap);
+        c.beg = (int64_t)b.idx * tile;
+        c.end = c.beg + tile < R ? c.beg + tile : R;
         if (c.beg >= R || frozen(c.rec))
             return;
     }
@@ -1995,7 +1998,7 @@ __global__ __launch_bounds__(kThreads) void k_obs_rep(const PaRunDesc *__restric
     // a weighted population: sums of w, wE, wE^2, wE^3, w|M|, wM^2, w^2 with w = pa_exp(lw)
     const bool wt = c.rec->weighted != 0u;
     double ws[PA_WPARTS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    static_assert(PA_HCHUNK % PA_CHUNK == 0 && PA_CHUNK % kThreads == 0, "whole chunks of whole passes");
+    static_assert(PA_CHUNK % kThreads == 0, "whole chunks of whole passes");
     const int64_t chunks = (c.rd->cap + PA_CHUNK - 1) / PA_CHUNK;
     // kPre passes' loads are issued before the first pass's atomics (which
     // the compiler would not let later loads pass); a slot past the end loads
@@ -2159,17 +2162,80 @@ __device__ __forceinline__ double i128_to_double(unsigned long long lo, unsigned
     return neg ? -m : m;
 }
 
-// Averages of step 4 and the family statistics: rho_t = sum_k c_k^2 / R
-// (Eq. (6) with n_k = c_k / R), S_f = ln R - (1/R) sum_k c_k ln c_k.  A
-// weighted population reports weighted averages sum_j w_j O_j / sum_j w_j and
-// ESS = (sum w)^2 / sum w^2 (the integer sums and family statistics stay
-// those of the members).  In a batched anneal the row of temperature point
-// `point` is written too.
-__global__ __launch_bounds__(kThreads) void k_obs_final(const PaRunDesc *__restrict__ runs, PaStepRecord *steprec,
+// The exact sums of a population and its families.
+struct ObsSums {
+    uint64_t E, E2, absM, M2, E3lo, E3hi, C2, families;
+};
+
+// Averages of step 4 and the family statistics, written to the record: rho_t =
+// sum_k c_k^2 / R (Eq. (6) with n_k = c_k / R), S_f = ln R - (1/R) sum_k c_k ln
+// c_k (clnc).  A weighted population reports weighted averages sum_j w_j O_j /
+// sum_j w_j and ESS = (sum w)^2 / sum w^2 (the integer sums and family
+// statistics stay those of the members).
+__device__ __forceinline__ void publish_averages(PaRecord *rec, int N, const ObsSums &s, double clnc, bool wt,
+                                                 const double (&ws)[PA_WPARTS])
+{
+    rec->sumE = s.E;
+    rec->sumE2 = s.E2;
+    rec->sumAbsM = s.absM;
+    rec->sumM2 = s.M2;
+    rec->sumC2 = s.C2;
+    rec->families = s.families;
+    rec->sumE3[0] = s.E3lo;
+    rec->sumE3[1] = s.E3hi;
+    const double n = (double)N, r = (double)rec->Rcur;
+    rec->e3 = i128_to_double(s.E3lo, s.E3hi) / (n * n * n * r);
+    rec->sumClnC = clnc;
+    rec->e = (double)(long long)s.E / (n * r);
+    rec->e2 = (double)(long long)s.E2 / (n * n * r);
+    rec->abs_m = (double)(long long)s.absM / (n * r);
+    rec->m2 = (double)(long long)s.M2 / (n * n * r);
+    rec->rho_t = (double)s.C2 / r;
+    rec->S_f = log(r) - clnc / r;
+    rec->ess = r;
+    if (wt) {
+        rec->e = ws[1] / ws[0] / n;
+        rec->e2 = ws[2] / ws[0] / (n * n);
+        rec->e3 = ws[3] / ws[0] / (n * n * n);
+        rec->abs_m = ws[4] / ws[0] / n;
+        rec->m2 = ws[5] / ws[0] / (n * n);
+        rec->ess = ws[0] * ws[0] / ws[6];
+    }
+}
+
+// The row of temperature point `point` of a batched anneal.
+__device__ __forceinline__ void write_step_record(const PaRecord *rec, PaStepRecord *o, int point)
+{
+    o->beta = rec->beta;
+    o->lnQ = point > 0 ? rec->lnQ : 0.0;
+    o->lnZ = rec->lnZ;
+    o->sv = rec->sv;
+    o->e = rec->e;
+    o->e2 = rec->e2;
+    o->abs_m = rec->abs_m;
+    o->m2 = rec->m2;
+    o->rho_t = rec->rho_t;
+    o->S_f = rec->S_f;
+    o->R = (long long)rec->Rcur;
+    o->sumE = (long long)rec->sumE;
+    o->sumE2 = (long long)rec->sumE2;
+    o->sumAbsM = (long long)rec->sumAbsM;
+    o->sumM2 = (long long)rec->sumM2;
+    o->sumC2 = (long long)rec->sumC2;
+    o->families = (long long)rec->families;
+    o->status = rec->status;
+    o->pad = 0;
+}
+
+// Publishes the averages of the runs whose passes were k_obs_rep and k_obs_fam
+// (the large ones), from their accumulators and partial sums.
+__global__ __launch_bounds__(kThreads) void k_obs_final(const PaRunDesc *__restrict__ runs,
+                                                        const uint32_t *__restrict__ list, PaStepRecord *steprec,
                                                         int npoints, int point)
 {
-    __shared__ double sd[16];
-    const PaRunDesc &rd = runs[blockIdx.x];
+    __shared__ double sd[16 * PA_WPARTS];
+    const uint32_t run = list[blockIdx.x];
+    const PaRunDesc &rd = runs[run];
     PaRecord *rec = rd.dv.rec;
     const bool fz = frozen(rec);
     const bool wt = !fz && rec->weighted != 0u;
@@ -2179,70 +2245,216 @@ __global__ __launch_bounds__(kThreads) void k_obs_final(const PaRunDesc *__restr
         for (int k = threadIdx.x; k < nparts; k += blockDim.x)
             v = v + rd.dv.partial[k];
     const double t = pa_block_sum_f64(v, sd);
-    double ws[PA_WPARTS];
+    double ws[PA_WPARTS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (wt) {
         const int64_t chunks = (rd.cap + PA_CHUNK - 1) / PA_CHUNK;
         const int nlive = (int)(((int64_t)rec->Rcur + PA_CHUNK - 1) / PA_CHUNK);
-        for (int f = 0; f < PA_WPARTS; ++f) {
-            double a = 0.0;
-            for (int k = threadIdx.x; k < nlive; k += blockDim.x)
-                a = a + rd.dv.wpart[f * chunks + k];
-            ws[f] = pa_block_sum_f64(a, sd);
-        }
+        for (int k = threadIdx.x; k < nlive; k += blockDim.x)
+#pragma unroll
+            for (int f = 0; f < PA_WPARTS; ++f)
+                ws[f] = ws[f] + rd.dv.wpart[f * chunks + k];
+        pa_block_sum_f64x(ws, sd);
     }
     if (threadIdx.x != 0)
         return;
     if (!fz) {
-        rec->sumE = rec->accE;
-        rec->sumE2 = rec->accE2;
-        rec->sumAbsM = rec->accAbsM;
-        rec->sumM2 = rec->accM2;
-        rec->sumC2 = rec->accC2;
-        rec->families = rec->accFam;
+        const ObsSums s = {rec->accE, rec->accE2, rec->accAbsM, rec->accM2,
+                           rec->accE3[0], rec->accE3[1], rec->accC2, rec->accFam};
         rec->accE = rec->accE2 = rec->accAbsM = rec->accM2 = rec->accC2 = rec->accFam = 0;
-        rec->sumE3[0] = rec->accE3[0];
-        rec->sumE3[1] = rec->accE3[1];
         rec->accE3[0] = rec->accE3[1] = 0;
-        const double n = (double)rd.N, r = (double)rec->Rcur;
-        rec->e3 = i128_to_double(rec->sumE3[0], rec->sumE3[1]) / (n * n * n * r);
-        rec->sumClnC = t;
-        rec->e = (double)(long long)rec->sumE / (n * r);
-        rec->e2 = (double)(long long)rec->sumE2 / (n * n * r);
-        rec->abs_m = (double)(long long)rec->sumAbsM / (n * r);
-        rec->m2 = (double)(long long)rec->sumM2 / (n * n * r);
-        rec->rho_t = (double)rec->sumC2 / r;
-        rec->S_f = log(r) - t / r;
-        rec->ess = r;
-        if (wt) {
-            rec->e = ws[1] / ws[0] / n;
-            rec->e2 = ws[2] / ws[0] / (n * n);
-            rec->e3 = ws[3] / ws[0] / (n * n * n);
-            rec->abs_m = ws[4] / ws[0] / n;
-            rec->m2 = ws[5] / ws[0] / (n * n);
-            rec->ess = ws[0] * ws[0] / ws[6];
+        publish_averages(rec, rd.N, s, t, wt, ws);
+    }
+    if (steprec)
+        write_step_record(rec, steprec + (size_t)run * npoints + point, point);
+}
+
+// The whole observables pass of a small run (capacity up to PA_SMALL_CAP) by
+// one workgroup: energy range, level histogram, sums, families (counted in
+// LDS) and averages.  The three passes of a large run cost a small one their
+// launches and their chains of dependent loads: R = 1000 9.1 + 4.0 + 3.0 us ->
+// 7.2, 1024 runs of R = 100 10.3 + 5.4 + 6.2 -> 9.4.  A group of 256 lanes takes
+// each chunk (its replicas are loaded once, before anything waits); with
+// several chunks a group, R = 20011 took 30 us in one workgroup, as long as in
+// three passes.  Every floating-point sum keeps the large runs' order, so a
+// run's numbers depend neither on T (256 where every small run fits one chunk,
+// else 1024) nor on which side of PA_SMALL_CAP it is.
+template <int T>
+__global__ __launch_bounds__(T) void k_obs_small(const PaRunDesc *__restrict__ runs,
+                                                 const uint32_t *__restrict__ list, int build_hist,
+                                                 PaStepRecord *steprec, int npoints, int point)
+{
+    constexpr int kPer = PA_CHUNK / kThreads;
+    static_assert(PA_SMALL_CAP <= PA_HCHUNK && PA_SMALL_CAP <= 4 * PA_CHUNK, "one chunk a group, one chunk of families");
+    __shared__ uint32_t fam[PA_SMALL_CAP];
+    __shared__ uint32_t lh[kObsLevels];
+    __shared__ uint64_t su[7][kThreads], tot[7];
+    __shared__ double sw[T / 64][PA_WPARTS], sf[4], logs[64];
+    __shared__ int s_lo[T / 64], s_hi[T / 64];
+    const uint32_t run = list[blockIdx.x];
+    const PaRunDesc &rd = runs[run];
+    PaRecord *rec = rd.dv.rec;
+    if (frozen(rec)) {
+        if (threadIdx.x == 0 && steprec)
+            write_step_record(rec, steprec + (size_t)run * npoints + point, point);
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int chunk = tid / kThreads, t = tid % kThreads;
+    const int R = (int)rec->Rcur, R0 = (int)rd.R0, cur = rec->cur;
+    const int DN = rd.d * rd.N;
+    const PaDev &dv = rd.dv;
+    const bool wt = rec->weighted != 0u;
+    int32_t pe[kPer], pm[kPer];
+    uint32_t pl[kPer];
+    double plw[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) { // a slot past the end loads the last one again and is not counted
+        const int d = min(chunk * PA_CHUNK + k * kThreads + t, R - 1);
+        pe[k] = dv.E[cur][d];
+        pm[k] = dv.M[cur][d];
+        pl[k] = dv.label[cur][d];
+        plw[k] = wt ? dv.lw[d] : 0.0;
+    }
+    for (int f = tid; f < R0; f += T)
+        fam[f] = 0;
+    for (int k = tid; k < 7 * kThreads; k += T)
+        (&su[0][0])[k] = 0;
+    if (tid < 64) // ln of the small family sizes (most of them)
+        logs[tid] = tid > 1 ? log((double)tid) : 0.0;
+    int hlo = 0, nlh = 0;
+    if (build_hist) {
+        int lo = pe[0], hi = pe[0];
+#pragma unroll
+        for (int k = 1; k < kPer; ++k) {
+            lo = min(lo, pe[k]);
+            hi = max(hi, pe[k]);
+        }
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) {
+            lo = min(lo, __shfl_xor(lo, m, 64));
+            hi = max(hi, __shfl_xor(hi, m, 64));
+        }
+        if (lane == 0) {
+            s_lo[wave] = lo;
+            s_hi[wave] = hi;
+        }
+        __syncthreads();
+        for (int k = 0; k < T / 64; ++k) {
+            lo = min(lo, s_lo[k]);
+            hi = max(hi, s_hi[k]);
+        }
+        hlo = (lo + DN) >> 2;
+        nlh = ((hi + DN) >> 2) - hlo + 1;
+        if (nlh <= kObsLevels)
+            for (int k = tid; k < nlh; k += T)
+                lh[k] = 0;
+        if (tid == 0) {
+            rec->emin = lo;
+            rec->emax = hi;
         }
     }
-    if (steprec) {
-        PaStepRecord *o = steprec + (size_t)blockIdx.x * npoints + point;
-        o->beta = rec->beta;
-        o->lnQ = point > 0 ? rec->lnQ : 0.0;
-        o->lnZ = rec->lnZ;
-        o->sv = rec->sv;
-        o->e = rec->e;
-        o->e2 = rec->e2;
-        o->abs_m = rec->abs_m;
-        o->m2 = rec->m2;
-        o->rho_t = rec->rho_t;
-        o->S_f = rec->S_f;
-        o->R = (long long)rec->Rcur;
-        o->sumE = (long long)rec->sumE;
-        o->sumE2 = (long long)rec->sumE2;
-        o->sumAbsM = (long long)rec->sumAbsM;
-        o->sumM2 = (long long)rec->sumM2;
-        o->sumC2 = (long long)rec->sumC2;
-        o->families = (long long)rec->families;
-        o->status = rec->status;
+    __syncthreads();
+    uint64_t sums[7] = {0, 0, 0, 0, 0, 0, 0}; // E, E^2, |M|, M^2, E^3 (int64 bits), c^2, families
+    double ws[PA_WPARTS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const bool valid = chunk * PA_CHUNK + k * kThreads + t < R;
+        uint32_t lab = 0xFFFFFFFFu;
+        if (valid) {
+            const int64_t e = pe[k], m = pm[k];
+            if (build_hist) {
+                const int h = ((int)e + DN) >> 2;
+                if (nlh <= kObsLevels)
+                    atomicAdd(&lh[h - hlo], 1u);
+                else
+                    atomicAdd(&dv.hist[h], 1u);
+            }
+            sums[0] += (uint64_t)e;
+            sums[1] += (uint64_t)(e * e);
+            sums[2] += (uint64_t)(m < 0 ? -m : m);
+            sums[3] += (uint64_t)(m * m);
+            sums[4] += (uint64_t)(e * e * e);
+            lab = pl[k];
+            if (wt) {
+                const double w = pa_exp(plw[k]), ef = (double)e, mf = (double)(m < 0 ? -m : m);
+                ws[0] = ws[0] + w;
+                ws[1] = ws[1] + w * ef;
+                ws[2] = ws[2] + w * (ef * ef);
+                ws[3] = ws[3] + w * (ef * ef * ef);
+                ws[4] = ws[4] + w * mf;
+                ws[5] = ws[5] + w * (mf * mf);
+                ws[6] = ws[6] + w * w;
+            }
+        }
+        // family counts: one atomic per run of equal labels in the wave
+        const uint32_t prev = (uint32_t)__shfl_up((int)lab, 1, 64);
+        const bool start = valid && (lane == 0 || lab != prev);
+        const uint64_t sm = __ballot(start), vm = __ballot(valid);
+        if (start) {
+            const uint64_t above = lane == 63 ? 0ull : ((sm | ~vm) & ~((2ull << lane) - 1ull));
+            const int stop = above ? __ffsll((long long)above) - 1 : 64;
+            atomicAdd(&fam[lab], (uint32_t)(stop - lane));
+        }
     }
+    if (wt) {
+#pragma unroll
+        for (int f = 0; f < PA_WPARTS; ++f) {
+            const double v = pa_wave_sum_f64(ws[f]);
+            if (lane == 0)
+                sw[wave][f] = v;
+        }
+    }
+    __syncthreads(); // the counts in LDS are complete
+    if (build_hist && nlh <= kObsLevels)
+        for (int k = tid; k < nlh; k += T)
+            if (lh[k])
+                dv.hist[hlo + k] = lh[k]; // the histogram was zero
+    if (wave < 4) { // families: the 256 lanes of a large run's one workgroup
+        double cl = 0.0;
+        for (int f = tid; f < R0; f += kThreads) {
+            const uint64_t c = fam[f];
+            if (c) {
+                sums[5] += c * c;
+                sums[6] += 1;
+                if (c > 1)
+                    cl = cl + (double)c * (c < 64 ? logs[c] : log((double)c));
+            }
+        }
+        cl = pa_wave_sum_f64(cl);
+        if (lane == 0)
+            sf[wave] = cl;
+    }
+    // the block's sums: lane t's of every group meet in LDS, then 32 lanes add each quantity's 256
+#pragma unroll
+    for (int q = 0; q < 7; ++q)
+        atomicAdd((unsigned long long *)&su[q][t], (unsigned long long)sums[q]);
+    __syncthreads();
+    if (tid < 7 * 32) {
+        uint64_t v = 0;
+        for (int k = tid & 31; k < kThreads; k += 32)
+            v += su[tid >> 5][k];
+        for (int m = 16; m >= 1; m >>= 1)
+            v += pa_shfl_xor_u64(v, m);
+        if ((tid & 31) == 0)
+            tot[tid >> 5] = v;
+    }
+    __syncthreads();
+    if (tid != 0)
+        return;
+    const double clnc = ((sf[0] + sf[1]) + sf[2]) + sf[3];
+    // the chunks' sums (their four waves in order) as the large runs add them: a butterfly over up to 4 lanes
+    if (wt)
+        for (int f = 0; f < PA_WPARTS; ++f) {
+            double c[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int q = 0; q < T / kThreads; ++q)
+                if (q * PA_CHUNK < R)
+                    c[q] = ((sw[4 * q][f] + sw[4 * q + 1][f]) + sw[4 * q + 2][f]) + sw[4 * q + 3][f];
+            ws[f] = (c[0] + c[2]) + (c[1] + c[3]);
+        }
+    const ObsSums s = {tot[0], tot[1], tot[2], tot[3], tot[4], (int64_t)tot[4] < 0 ? ~0ull : 0ull, tot[5], tot[6]};
+    publish_averages(rec, rd.N, s, clnc, wt, ws);
+    if (steprec)
+        write_step_record(rec, steprec + (size_t)run * npoints + point, point);
 }
 
 // ------------------------------------------------------------------ overlap
@@ -2746,12 +2958,20 @@ hipError_t pa_b_resample(const PaBatchView &v, int scheme, int freeze, int kq, b
 
 hipError_t pa_b_observables(const PaBatchView &v, int point, int hist_state)
 {
+    const int build = hist_state != PA_HIST_VALID;
+    PaStepRecord *rows = point >= 0 ? v.steprec : nullptr;
     if (hist_state == PA_HIST_STALE)
         k_hist_prep<<<v.nruns, kThreads, 0, v.stream>>>(v.runs);
-    k_obs_rep<<<v.nhrep, kThreads, 0, v.stream>>>(v.runs, v.hrep, hist_state != PA_HIST_VALID);
-    k_obs_fam<<<v.nfam, kThreads, 0, v.stream>>>(v.runs, v.fam);
-    k_obs_final<<<v.nruns, kThreads, 0, v.stream>>>(v.runs, point >= 0 ? v.steprec : nullptr, v.npoints,
-                                                    point);
+    if (v.nlarge) {
+        k_obs_rep<<<v.nhrep_large, kThreads, 0, v.stream>>>(v.runs, v.hrep, build);
+        k_obs_fam<<<v.nfam_large, kThreads, 0, v.stream>>>(v.runs, v.fam);
+        k_obs_final<<<v.nlarge, kThreads, 0, v.stream>>>(v.runs, v.list, rows, v.npoints, point);
+    }
+    const uint32_t small = v.nruns - v.nlarge;
+    if (small && v.small_cap <= PA_CHUNK)
+        k_obs_small<kThreads><<<small, kThreads, 0, v.stream>>>(v.runs, v.list + v.nlarge, build, rows, v.npoints, point);
+    else if (small)
+        k_obs_small<1024><<<small, 1024, 0, v.stream>>>(v.runs, v.list + v.nlarge, build, rows, v.npoints, point);
     return hipGetLastError();
 }
 
