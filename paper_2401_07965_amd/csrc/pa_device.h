@@ -225,41 +225,101 @@ __device__ __forceinline__ double pa_shfl_xor_f64(double v, int m)
     return __longlong_as_double((long long)pa_shfl_xor_u64((uint64_t)__double_as_longlong(v), m));
 }
 
-// Butterfly sum over the 64 lanes of a wavefront: the same pairing in every
-// call, so a double result is the same bits on every run.
+// One level of a butterfly over the 64 lanes, xor distance M, taken from 32
+// down: a and b are this lane's value and its partner's (in either order).
+// Distances 32 and 16 are exchanges of halves and rows, 8 and 4 rotations
+// within a row of 16 (after the level above the values repeat with that
+// period), 2 and 1 quad permutations: no LDS.  (Through LDS permutes a 64-bit
+// sum took twelve of them, one after the other.)
+template <int M>
+__device__ __forceinline__ void pa_level(uint32_t v, uint32_t &a, uint32_t &b)
+{
+    if constexpr (M == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        a = r[0];
+        b = r[1];
+    } else if constexpr (M == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        a = r[0];
+        b = r[1];
+    } else {
+        constexpr int kCtrl = M == 8 ? 0x128 : M == 4 ? 0x124 : M == 2 ? 0x4E : 0xB1; // row_ror 8, 4; quad_perm
+        a = v;
+        b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xF, 0xF, false);
+    }
+}
+
+template <int M, typename F>
+__device__ __forceinline__ uint64_t pa_level64(uint64_t v, F f)
+{
+    uint32_t al, bl, ah, bh;
+    pa_level<M>((uint32_t)v, al, bl);
+    pa_level<M>((uint32_t)(v >> 32), ah, bh);
+    return f(((uint64_t)ah << 32) | al, ((uint64_t)bh << 32) | bl);
+}
+
+// A commutative operation over the wave's 64 lanes (all active), in every
+// lane: the same pairing in every call, so a double result is the same bits
+// on every run.
+template <typename F>
+__device__ __forceinline__ uint64_t pa_wave_reduce(uint64_t v, F f)
+{
+    v = pa_level64<32>(v, f);
+    v = pa_level64<16>(v, f);
+    v = pa_level64<8>(v, f);
+    v = pa_level64<4>(v, f);
+    v = pa_level64<2>(v, f);
+    return pa_level64<1>(v, f);
+}
+
 __device__ __forceinline__ double pa_wave_sum_f64(double v)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1)
-        v = v + pa_shfl_xor_f64(v, m);
-    return v;
+    return __longlong_as_double((long long)pa_wave_reduce((uint64_t)__double_as_longlong(v), [](uint64_t a, uint64_t b) {
+        return (uint64_t)__double_as_longlong(__longlong_as_double((long long)a) + __longlong_as_double((long long)b));
+    }));
 }
 
 __device__ __forceinline__ uint64_t pa_wave_sum_u64(uint64_t v)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1)
-        v += pa_shfl_xor_u64(v, m);
-    return v;
+    return pa_wave_reduce(v, [](uint64_t a, uint64_t b) { return a + b; });
 }
 
 __device__ __forceinline__ int64_t pa_wave_min_i64(int64_t v)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        const int64_t o = (int64_t)pa_shfl_xor_u64((uint64_t)v, m);
-        v = o < v ? o : v;
-    }
-    return v;
+    return (int64_t)pa_wave_reduce((uint64_t)v, [](uint64_t a, uint64_t b) { return (int64_t)b < (int64_t)a ? b : a; });
 }
 
 __device__ __forceinline__ int64_t pa_wave_max_i64(int64_t v)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        const int64_t o = (int64_t)pa_shfl_xor_u64((uint64_t)v, m);
-        v = o > v ? o : v;
-    }
+    return (int64_t)pa_wave_reduce((uint64_t)v, [](uint64_t a, uint64_t b) { return (int64_t)b > (int64_t)a ? b : a; });
+}
+
+// What lane l adds at one level of an inclusive scan over the 64 lanes (0
+// where it adds nothing): the value 1, 2, 4 or 8 lanes below within its row of
+// 16, then the last lane of the row below (rows 1 and 3), then lane 31 (rows
+// 2 and 3).
+template <int LEVEL>
+__device__ __forceinline__ uint32_t pa_scan_from(uint32_t v)
+{
+    constexpr int kCtrl[6] = {0x111, 0x112, 0x114, 0x118, 0x142, 0x143}; // row_shr 1, 2, 4, 8; row_bcast 15, 31
+    constexpr int kRows[6] = {0xF, 0xF, 0xF, 0xF, 0xA, 0xC};
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl[LEVEL], kRows[LEVEL], 0xF, false);
+}
+
+template <int LEVEL = 0>
+__device__ __forceinline__ uint64_t pa_wave_scan_u64(uint64_t v) // inclusive sums (all lanes active)
+{
+    if constexpr (LEVEL < 6)
+        return pa_wave_scan_u64<LEVEL + 1>(v + (((uint64_t)pa_scan_from<LEVEL>((uint32_t)(v >> 32)) << 32) |
+                                                pa_scan_from<LEVEL>((uint32_t)v)));
+    return v;
+}
+
+template <int LEVEL = 0>
+__device__ __forceinline__ uint32_t pa_wave_scanmax_u32(uint32_t v) // inclusive maxima (all lanes active)
+{
+    if constexpr (LEVEL < 6)
+        return pa_wave_scanmax_u32<LEVEL + 1>(max(v, pa_scan_from<LEVEL>(v)));
     return v;
 }
 

@@ -1302,13 +1302,7 @@ __device__ __forceinline__ unsigned long long block_excl_scan(unsigned long long
                                                               unsigned long long *agg)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned long long incl = run;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const unsigned long long o = (unsigned long long)__shfl_up((long long)incl, off, 64);
-        if (lane >= off)
-            incl += o;
-    }
+    const unsigned long long incl = pa_wave_scan_u64(run);
     if (lane == 63)
         s_wave[wave] = incl;
     __syncthreads();
@@ -1373,18 +1367,10 @@ __device__ __forceinline__ void write_ancestors(uint32_t *anc, int64_t cap, uint
             top = v[k] > top ? v[k] : top;
             v[k] = top;
         }
-        uint32_t incl = top; // running maximum over the wave's lanes
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t o = (uint32_t)__shfl_up((int)incl, off, 64);
-            if (lane >= off)
-                incl = o > incl ? o : incl;
-        }
+        const uint32_t incl = pa_wave_scanmax_u32(top); // running maximum over the wave's lanes
         if (lane == 63)
             s_max[wave] = incl;
-        uint32_t before = (uint32_t)__shfl_up((int)incl, 1, 64);
-        if (lane == 0)
-            before = 0;
+        uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x138, 0xF, 0xF, false); // wave_shr 1
         before = carry > before ? carry : before;
         __syncthreads(); // also: the marks have been read
         for (int k = 0; k < THREADS / 64; ++k) {
