@@ -95,40 +95,58 @@ bool sweep_threads_ok(int N, int d, int t)
 
 constexpr int kLdsPerCu = 163840; // gfx950: 160 KiB of LDS per CU
 
-// Default sweep workgroup size, by a score: resident sweep waves per CU
-// (limited by the LDS of the lattice and queues and by whole workgroups of
-// waves) times the fraction of lanes busy over a colour's sites (N/2 sites in
-// rounds of t lanes).  Waves are counted up to 4 per SIMD (what the sweep's
-// registers allow) for workgroups of one or two waves and up to 3 for larger
-// ones: measured, 3D L = 8 and 10 sweep 3-13 % faster with 16 resident waves
-// of 128-lane workgroups than with 12 of 64 lanes, while larger workgroups
-// gain nothing from a fourth wave per SIMD (their waves meet at the end of
-// every colour).  The smaller size wins ties.  Autotuning refines it for
-// batches.
-int default_sweep_threads(int N, int d, bool J)
+// Modelled time (cycles) of one colour's updates over all columns of a batch
+// with t lanes per column: rounds of as many columns as a CU holds, then what
+// is left.  A column's colour takes passes over its sites, each the longer of
+// one wave's latency (1450 cycles) and its SIMD's waves taking turns (1200
+// cycles a wave, 3 % more with coordinates computed at each site), and an end
+// (250 cycles, 750 per wave and SIMD, 120 per wave of the workgroup).  Waves
+// spread evenly over the SIMDs only in workgroups of four or eight; others can
+// meet on one, those of 3, 5, 6 ... waves leave SIMDs idle (3 %), and single
+// ones in 2D, up to seven to a SIMD, gain less than their number (8 %).
+// Fitted to the times of all sizes on 23 shapes (more than 512 columns, theta
+// = 10), 4 % off on average among the better sizes.
+double colour_cycles(int N, int d, int t, bool J, int64_t columns)
 {
-    const int lds_max = g_max_lds ? g_max_lds : kLdsPerCu;
-    const int nh = N / 2;
-    int best = 0;
-    double best_score = -1.0;
+    constexpr int kCus = 256;
+    const int w = t / 64, nh = N / 2, cap = pa_sweep_waves_cap(N, d, t, J);
+    int blocks = (int)((size_t)kLdsPerCu / pa_sweep_lds_bytes(N, d, t, J));
+    blocks = std::min(blocks, cap / w);
+    if (blocks < 1)
+        return HUGE_VAL;
+    const int walk = pa_sweep_walk(N, d, t, J);
+    const double uneven = w > 2 && w % 4 ? 1.03 : w == 1 && d == 2 ? 1.08 : 1.0;
+    const double issue = 1200.0 * (walk == 0 ? 1.03 : 1.0) * uneven;
+    auto together = [&](int b) { // b columns on each CU
+        const double ws = w % 4 == 0 ? b * w / 4.0 : std::min(cap / 4.0, b * w / 4.0 + 0.4);
+        const double passes = std::max(1.0, (double)((nh + 63) / 64 * 64) / t);
+        return passes * std::hypot(1450.0, issue * ws) + 250.0 + 750.0 * ws + 120.0 * w;
+    };
+    const int64_t round = (int64_t)kCus * blocks, left = columns % round;
+    return (double)(columns / round) * together(blocks) + (left ? together((int)((left + kCus - 1) / kCus)) : 0.0);
+}
+
+// Default sweep workgroup size: the least modelled time.  It is the best of
+// all sizes on 22 of those shapes and 2 % behind it on one (2D L = 32);
+// counting resident waves alone, as it was chosen before, lost 15 to 19 % at 3D
+// L = 12 (922 us with 128 lanes, 790 with 256), 3D L = 14 (997 with 192, 829
+// with 256) and 2D L = 48 (707 with 128, 595 with 256).  Autotuning refines it
+// for batches.
+int default_sweep_threads(int N, int d, bool J, int64_t columns)
+{
+    const size_t lds_max = (size_t)(g_max_lds ? g_max_lds : kLdsPerCu);
+    double least = HUGE_VAL;
+    int best = 768; // none fits: rejected by the LDS check of the batch set-up
     for (int t = 64; t <= 768; t += 64) {
-        const size_t lds = pa_sweep_lds_bytes(N, d, t, J);
-        if (!sweep_threads_ok(N, d, t) || lds > (size_t)lds_max)
+        if (!sweep_threads_ok(N, d, t) || pa_sweep_lds_bytes(N, d, t, J) > lds_max)
             continue;
-        const int w = t / 64;
-        const int cap = 4 * (w <= 2 ? 4 : 3); // waves per CU counted
-        int blocks = (int)(kLdsPerCu / lds);
-        if (blocks > cap / w)
-            blocks = cap / w;
-        const int waves = blocks * w;
-        const int rounds = (nh + t - 1) / t;
-        const double score = waves * ((double)nh / ((double)rounds * t));
-        if (score > best_score + 1e-9) {
-            best_score = score;
+        const double c = colour_cycles(N, d, t, J, columns);
+        if (c < least) {
+            least = c;
             best = t;
         }
     }
-    return best ? best : 768; // none fits: rejected by the LDS check of the batch set-up
+    return best;
 }
 
 // Default size where the batch's columns leave the chip short of workgroups
@@ -166,7 +184,7 @@ int few_columns_threads(int N, int d, bool J, int64_t columns)
 int group_sweep_threads(int N, int d, bool J, int64_t columns)
 {
     const int few = columns <= 2 * 256 ? few_columns_threads(N, d, J, columns) : 0;
-    return few ? few : default_sweep_threads(N, d, J);
+    return few ? few : default_sweep_threads(N, d, J, columns);
 }
 
 uint64_t round256(uint64_t b) { return (b + 255) / 256 * 256; }
@@ -595,7 +613,8 @@ pa_status make_batch(const pa_config *cfgs, int32_t nruns, int32_t max_points, v
     if (g_max_lds == 0 && (e = pa_query_lds(&g_max_lds)) != hipSuccess)
         return hip_fail(nullptr, e, "device query");
     for (const Geometry &g : geo)
-        if (pa_sweep_lds_bytes(g.N, g.d, default_sweep_threads(g.N, g.d, g.J != 0), g.J != 0) > (size_t)g_max_lds ||
+        if (pa_sweep_lds_bytes(g.N, g.d, default_sweep_threads(g.N, g.d, g.J != 0, 1 << 20), g.J != 0) >
+                (size_t)g_max_lds ||
             (size_t)g.H * 4 > (size_t)g_max_lds)
             return fail(nullptr, PA_E_INVAL, "lattice too large for the workgroup LDS of this device");
     b->jmask.resize(nruns);

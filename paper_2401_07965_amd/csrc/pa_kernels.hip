@@ -2652,6 +2652,14 @@ int sweep_waves(size_t lds, int threads)
     return (blocks < kWavesPerCu / w ? blocks : kWavesPerCu / w) * w;
 }
 
+// Whether the sweeps claim registers for four waves per SIMD (k_sweep4): more
+// than 16 waves to a CU only for workgroups of one or two waves.
+bool sweep_four(size_t lds, int threads)
+{
+    const int w = threads / 64, blocks = (int)(kLdsPerCu / lds);
+    return w > 2 || blocks * w <= kWavesPerCu;
+}
+
 // The walk a sweep of this shape takes: coordinates that stay from pass to
 // pass where the workgroup size allows it, else the site table unless its LDS
 // costs resident waves (a wave lost costs more than the index arithmetic).
@@ -2690,9 +2698,7 @@ hipError_t sweep_launch(const PaBatchView &v, int g, int theta, int threads, uin
     const int walk = sweep_walk(v.gN[g], v.gd[g], threads, v.gJ[g] != 0);
     if (gather && !sweep_gathers(v, g)) // gathered after the resampling
         gather = 0;
-    // more than 16 waves to a CU only for small workgroups (see k_sweep4)
-    const int w = threads / 64, blocks = (int)(kLdsPerCu / lds);
-    const bool four = w > 2 || blocks * w <= kWavesPerCu;
+    const bool four = sweep_four(lds, threads);
     if (v.gd[g] == 3)
         return pa_sweep3_launch(v.runs, v.gcol[g], v.gncol[g], threads, lds, st, v.gJ[g] != 0, theta, t0, gather, walk,
                                 four);
@@ -2707,6 +2713,13 @@ hipError_t sweep_launch(const PaBatchView &v, int g, int theta, int threads, uin
 size_t pa_sweep_lds_bytes(int N, int d, int threads, bool J)
 {
     return sweep_lds(N, d, threads, J, sweep_walk(N, d, threads, J));
+}
+
+int pa_sweep_walk(int N, int d, int threads, bool J) { return sweep_walk(N, d, threads, J); }
+
+int pa_sweep_waves_cap(int N, int d, int threads, bool J)
+{
+    return sweep_four(pa_sweep_lds_bytes(N, d, threads, J), threads) ? kWavesPerCu : 4 * (d == 3 ? 5 : 7);
 }
 
 // The largest lattice of a cluster update, as the bytes its LDS limit counts: four words per site
