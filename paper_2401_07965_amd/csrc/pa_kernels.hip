@@ -1453,25 +1453,99 @@ __global__ __launch_bounds__(PA_SCAN_THREADS) void k_scan_counts(const PaRunDesc
 }
 
 // The chunk sums of the sampling-variance terms: a wave's slots are one
-// chunk when it holds PA_CHUNK of them (ITEMS = 16), else the tile is one
-// chunk (ITEMS = 4: block sum).  The barriers it contains (or adds) publish
-// what the first wave wrote to LDS before.
+// chunk when it holds PA_CHUNK of them (ITEMS = 16), else four waves' are
+// (ITEMS = 4).  Chunk c goes to out[c]; the barriers publish it to the
+// workgroup where out is LDS, and what the first wave wrote to LDS before.
 template <int ITEMS>
-__device__ __forceinline__ void store_chunk_sv(const PaRunDesc &rd, uint32_t tile, double sv, double *sd)
+__device__ __forceinline__ void store_chunk_sv(double *out, int64_t cap, uint32_t tile, double sv, double *sd)
 {
-    constexpr int kTile = kThreads * ITEMS;
+    static_assert(64 * ITEMS == PA_CHUNK || kThreads * ITEMS == PA_CHUNK, "chunks of one or of four whole waves");
+    const int tid = threadIdx.x, nwaves = (int)(blockDim.x >> 6);
+    const double t = pa_wave_sum_f64(sv);
     if (64 * ITEMS == PA_CHUNK) {
-        const double t = pa_wave_sum_f64(sv);
-        const int64_t chunk = (int64_t)tile * (kTile / PA_CHUNK) + (threadIdx.x >> 6);
-        if ((threadIdx.x & 63) == 0 && chunk * PA_CHUNK < rd.cap)
-            rd.dv.partial[chunk] = t;
-        __syncthreads();
+        const int64_t chunk = (int64_t)tile * nwaves + (tid >> 6);
+        if ((tid & 63) == 0 && chunk * PA_CHUNK < cap)
+            out[chunk] = t;
     } else {
-        static_assert(64 * ITEMS == PA_CHUNK || kTile == PA_CHUNK, "chunks of whole waves or whole tiles");
-        const double t = pa_block_sum_f64(sv, sd);
-        if (threadIdx.x == 0)
-            rd.dv.partial[tile] = t;
+        if ((tid & 63) == 0)
+            sd[tid >> 6] = t;
+        __syncthreads();
+        if (tid < nwaves / 4) {
+            double c = 0.0;
+            for (int k = 0; k < 4; ++k)
+                c = c + sd[4 * tid + k];
+            out[(int64_t)tile * (nwaves / 4) + tid] = c;
+        }
     }
+    __syncthreads();
+}
+
+// The integer weights of the slots [base, base + ITEMS), 0 past the population.
+template <int ITEMS>
+__device__ __forceinline__ void load_weights(const PaRunDesc &rd, const PaRecord *rec, int64_t base, int64_t n,
+                                             uint64_t (&v)[ITEMS])
+{
+    const bool wt = rec->weighted != 0u;
+    const int DN = rd.d * rd.N;
+    const int hmin = (rec->wemin + DN) >> 2;
+    const int32_t *E = rd.dv.E[rec->cur];
+    if (base + ITEMS <= n && !wt) {
+        alignas(16) int32_t e[ITEMS];
+#pragma unroll
+        for (int k = 0; k < ITEMS / 4; ++k)
+            reinterpret_cast<uint4 *>(e)[k] = reinterpret_cast<const uint4 *>(E + base)[k];
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k)
+            v[k] = weight_of(e[k], DN, hmin, rd.dv.wtab);
+    } else {
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k)
+            v[k] = base + k < n ? (wt ? rd.dv.Wj[base + k] : weight_of(E[base + k], DN, hmin, rd.dv.wtab)) : 0ull;
+    }
+}
+
+// The systematic copies of a tile's replicas (weights v, their prefix C before
+// the thread's first one): N(c) = #points (k + U/2^32) S/R below c, k < R, so
+// replica j's copies are [N(C_{j-1}), N(C_j)).  Writes them into the ancestor
+// map, the new size (the tile of the last replica) and the chunk sums of the
+// sampling variance into `part`.  Called after a barrier past the last use of
+// s_wave.
+template <int THREADS, int ITEMS>
+__device__ __forceinline__ void systematic_copies(const PaRunDesc &rd, PaRecord *rec, uint32_t tile, int64_t n,
+                                                  unsigned long long acc, const uint64_t (&v)[ITEMS], double *part,
+                                                  unsigned long long *s_wave, double *sd, uint32_t *s_mark,
+                                                  uint32_t *s_max)
+{
+    constexpr int kTile = THREADS * ITEMS;
+    const int64_t base = (int64_t)tile * kTile + (int64_t)threadIdx.x * ITEMS;
+    const uint64_t S = rec->S, Rt = (uint64_t)rd.R0;
+    const uint32_t U = pa_philox(rd.seed, rd.run_id, 0u, 0u, rec->step + 1, PA_PURPOSE_RS_SYS << 28).x0;
+    uint64_t lo = sys_below(acc, Rt, S, U); // N(C_{base-1}); N(0) = 0
+    const uint64_t first = lo;
+    uint32_t r[ITEMS];
+    double sv = 0.0;
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int64_t j = base + k;
+        r[k] = 0;
+        if (j < n) {
+            acc += v[k];
+            const uint64_t hi = sys_below(acc, Rt, S, U);
+            r[k] = (uint32_t)(hi - lo);
+            if (j == n - 1)
+                rec->Rnew = hi; // N(S) = Rt: the size is kept
+            sv = sv + sv_term(r[k], v[k], (double)S, (double)Rt);
+            lo = hi;
+        }
+    }
+    // the tile's range of copies (the barriers of store_chunk_sv publish it)
+    if (threadIdx.x == 0)
+        s_wave[0] = first;
+    if (threadIdx.x == THREADS - 1)
+        s_wave[1] = lo;
+    store_chunk_sv<ITEMS>(part, rd.cap, tile, sv, sd);
+    const uint64_t o0 = s_wave[0], o1 = s_wave[1];
+    write_ancestors<THREADS, ITEMS>(rd.dv.anc, rd.cap, o0, o1, first - o0, r, (int64_t)tile * kTile, s_mark, s_max);
 }
 
 // Integer weights and their inclusive prefix sums C in one pass: tile t (the
@@ -1495,24 +1569,8 @@ __device__ __forceinline__ void weights_scan_tile(const PaRunDesc &rd, PaRecord 
     PaScanTile *tiles = rd.dv.tiles;
     const int64_t base = (int64_t)tile * kTile + (int64_t)threadIdx.x * ITEMS;
     const bool whole = base + ITEMS <= n; // the thread's slots are all live
-    const bool wt = rec->weighted != 0u;
-    const int DN = rd.d * rd.N;
-    const int hmin = (rec->wemin + DN) >> 2;
-    const int32_t *E = rd.dv.E[rec->cur];
     uint64_t v[ITEMS];
-    if (whole && !wt) {
-        alignas(16) int32_t e[ITEMS];
-#pragma unroll
-        for (int k = 0; k < ITEMS / 4; ++k)
-            reinterpret_cast<uint4 *>(e)[k] = reinterpret_cast<const uint4 *>(E + base)[k];
-#pragma unroll
-        for (int k = 0; k < ITEMS; ++k)
-            v[k] = weight_of(e[k], DN, hmin, rd.dv.wtab);
-    } else {
-#pragma unroll
-        for (int k = 0; k < ITEMS; ++k)
-            v[k] = base + k < n ? (wt ? rd.dv.Wj[base + k] : weight_of(E[base + k], DN, hmin, rd.dv.wtab)) : 0ull;
-    }
+    load_weights<ITEMS>(rd, rec, base, n, v);
     if (MODE == PA_SCAN_MULTINOMIAL) {
         if (whole) {
 #pragma unroll
@@ -1558,37 +1616,9 @@ __device__ __forceinline__ void weights_scan_tile(const PaRunDesc &rd, PaRecord 
         }
         return;
     }
-    // systematic: N(c) = #points (k + U/2^32) S/R below c, k < R
-    __syncthreads();
-    const uint64_t S = rec->S, Rt = (uint64_t)rd.R0;
-    const uint32_t U = pa_philox(rd.seed, rd.run_id, 0u, 0u, rec->step + 1, PA_PURPOSE_RS_SYS << 28).x0;
-    unsigned long long acc = *s_excl + thread_excl;
-    uint64_t lo = sys_below(acc, Rt, S, U); // N(C_{base-1}); N(0) = 0
-    const uint64_t first = lo;
-    uint32_t r[ITEMS];
-    double sv = 0.0;
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) {
-        const int64_t j = base + k;
-        r[k] = 0;
-        if (j < n) {
-            acc += v[k];
-            const uint64_t hi = sys_below(acc, Rt, S, U);
-            r[k] = (uint32_t)(hi - lo);
-            if (j == n - 1)
-                rec->Rnew = hi; // N(S) = Rt: the size is kept
-            sv = sv + sv_term(r[k], v[k], (double)S, (double)Rt);
-            lo = hi;
-        }
-    }
-    // the tile's range of copies (the barriers of store_chunk_sv publish it)
-    if (threadIdx.x == 0)
-        s_wave[0] = first;
-    if (threadIdx.x == kThreads - 1)
-        s_wave[1] = lo;
-    store_chunk_sv<ITEMS>(rd, tile, sv, sd);
-    const uint64_t o0 = s_wave[0], o1 = s_wave[1];
-    write_ancestors<kThreads, ITEMS>(rd.dv.anc, rd.cap, o0, o1, first - o0, r, (int64_t)tile * kTile, s_mark, s_max);
+    __syncthreads(); // s_excl
+    systematic_copies<kThreads, ITEMS>(rd, rec, tile, n, *s_excl + thread_excl, v, rd.dv.partial, s_wave, sd, s_mark,
+                                       s_max);
 }
 
 template <int MODE>
@@ -1616,25 +1646,14 @@ __global__ __launch_bounds__(kThreads) void k_weights_scan(const PaRunDesc *__re
         weights_scan_tile<MODE, 4>(rd, rec, s_tile, s_wave, &s_excl, sd, s_mark, s_max);
 }
 
-// Nearest-integer (SCHEME 2: floor(tauhat) + [u S < (R W mod S) 2^32], u =
-// x0 of Philox(j, 0, i, RS_NI<<28)) or Poisson (SCHEME 1) copy numbers drawn
-// and summed in one pass: tile t (the run's ticket order) holds replica slots
-// [T t, T (t + 1)), T = kThreads ITEMS = pa_counts_tile(cap), ITEMS
-// consecutive ones per thread.  Each thread draws its replicas' copy
-// numbers, the workgroup sums them, the look-back gives the tile's offset,
-// and the ancestor map is written from it.  The sampling-variance terms of
-// chunk c (PA_CHUNK slots) go to partial[c].
+// The copy numbers of the slots [base, base + ITEMS) and their sum: nearest
+// integer (SCHEME 2: floor(tauhat) + [u S < (R W mod S) 2^32], u = x0 of
+// Philox(j, 0, i, RS_NI<<28)) or Poisson (SCHEME 1); *sv: their
+// sampling-variance terms' sum.
 template <int SCHEME, int ITEMS>
-__device__ __forceinline__ void counts_scan_tile(const PaRunDesc &rd, PaRecord *rec, uint32_t *s_tile,
-                                                 unsigned long long *s_wave, unsigned long long *s_excl,
-                                                 double *sd, uint32_t *s_mark, uint32_t *s_max)
+__device__ __forceinline__ unsigned long long draw_copies(const PaRunDesc &rd, const PaRecord *rec, int64_t base,
+                                                          int64_t n, uint32_t (&r)[ITEMS], double *sv)
 {
-    constexpr int kTile = kThreads * ITEMS;
-    const uint32_t tile = *s_tile;
-    const int64_t n = (int64_t)rec->Rcur;
-    const int64_t ntiles = (rd.cap + kTile - 1) / kTile;
-    PaScanTile *tiles = rd.dv.tiles + pa_tiles_per_sum(rd.cap);
-    const int64_t base = (int64_t)tile * kTile + (int64_t)threadIdx.x * ITEMS;
     const bool wt = rec->weighted != 0u;
     const int DN = rd.d * rd.N;
     const int hmin = (rec->wemin + DN) >> 2;
@@ -1651,8 +1670,7 @@ __device__ __forceinline__ void counts_scan_tile(const PaRunDesc &rd, PaRecord *
         for (int k = 0; k < ITEMS; ++k)
             e[k] = (!wt && base + k < n) ? E[base + k] : 0;
     }
-    uint32_t r[ITEMS];
-    double sv = 0.0;
+    *sv = 0.0;
     unsigned long long run = 0;
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
@@ -1671,9 +1689,33 @@ __device__ __forceinline__ void counts_scan_tile(const PaRunDesc &rd, PaRecord *
         } else {
             r[k] = poisson_copies(rd, W, S, Rt, j, step);
         }
-        sv = sv + sv_term(r[k], W, (double)S, (double)Rt);
+        *sv = *sv + sv_term(r[k], W, (double)S, (double)Rt);
         run += r[k];
     }
+    return run;
+}
+
+// Nearest-integer (SCHEME 2) or Poisson (SCHEME 1) copy numbers drawn and
+// summed in one pass: tile t (the run's ticket order) holds replica slots
+// [T t, T (t + 1)), T = kThreads ITEMS = pa_counts_tile(cap), ITEMS
+// consecutive ones per thread.  Each thread draws its replicas' copy
+// numbers, the workgroup sums them, the look-back gives the tile's offset,
+// and the ancestor map is written from it.  The sampling-variance terms of
+// chunk c (PA_CHUNK slots) go to partial[c].
+template <int SCHEME, int ITEMS>
+__device__ __forceinline__ void counts_scan_tile(const PaRunDesc &rd, PaRecord *rec, uint32_t *s_tile,
+                                                 unsigned long long *s_wave, unsigned long long *s_excl,
+                                                 double *sd, uint32_t *s_mark, uint32_t *s_max)
+{
+    constexpr int kTile = kThreads * ITEMS;
+    const uint32_t tile = *s_tile;
+    const int64_t n = (int64_t)rec->Rcur;
+    const int64_t ntiles = (rd.cap + kTile - 1) / kTile;
+    PaScanTile *tiles = rd.dv.tiles + pa_tiles_per_sum(rd.cap);
+    const int64_t base = (int64_t)tile * kTile + (int64_t)threadIdx.x * ITEMS;
+    uint32_t r[ITEMS];
+    double sv;
+    const unsigned long long run = draw_copies<SCHEME, ITEMS>(rd, rec, base, n, r, &sv);
     unsigned long long agg;
     const unsigned long long thread_excl = block_excl_scan<kThreads>(run, s_wave, &agg);
     if ((threadIdx.x >> 6) == 0) {
@@ -1684,7 +1726,7 @@ __device__ __forceinline__ void counts_scan_tile(const PaRunDesc &rd, PaRecord *
                 rec->Rnew = excl + agg;
         }
     }
-    store_chunk_sv<ITEMS>(rd, tile, sv, sd);
+    store_chunk_sv<ITEMS>(rd.dv.partial, rd.cap, tile, sv, sd);
     write_ancestors<kThreads, ITEMS>(rd.dv.anc, rd.cap, *s_excl, *s_excl + agg, thread_excl, r,
                                      (int64_t)tile * kTile, s_mark, s_max);
 }
@@ -1844,6 +1886,28 @@ __global__ __launch_bounds__(kThreads) void k_keep(const PaRunDesc *__restrict__
         dv.lw[j] = wx(dv, c.rec, cur, wt, j) + m;
 }
 
+// The record after an applied resampling (one thread).
+__device__ __forceinline__ void commit_resampled(PaRecord *rec, double sv, uint64_t Rnew, bool gather)
+{
+    rec->sv = sv;
+    rec->lnZ = rec->lnZ + rec->lnQ;
+    rec->lnq_hist[0] = rec->lnq_hist[1];
+    rec->lnq_hist[1] = rec->lnq_hist[2];
+    rec->lnq_hist[2] = rec->lnQ;
+    rec->T[0] = rec->Tn[0];
+    rec->T[1] = rec->Tn[1];
+    rec->T[2] = rec->Tn[2];
+    rec->Rprev = rec->Rcur;
+    rec->Rcur = Rnew;
+    rec->cur ^= 1;
+    rec->gather = gather ? 1 : 0; // the spins wait in the other buffer
+    rec->beta = rec->beta_next;
+    rec->step += 1;
+    rec->sweeps = 0;
+    rec->weighted = 0;
+    rec->resamplings += 1;
+}
+
 // Completes an applied resampling: SV (Eq. (5)) from the partials in fixed
 // order, ln Z_hat += ln Q (Eq. (7)), the new beta and its thresholds, the
 // buffer swap and the step count.  A kept population advances the same way
@@ -1892,24 +1956,99 @@ __global__ __launch_bounds__(kThreads) void k_commit(const PaRunDesc *__restrict
     for (int k = threadIdx.x; k < nlive; k += blockDim.x)
         v = v + rd.dv.partial[k];
     const double t = pa_block_sum_f64(v, sd);
-    if (threadIdx.x == 0) {
-        rec->sv = t / (double)Rprev;
-        rec->lnZ = rec->lnZ + rec->lnQ;
-        rec->lnq_hist[0] = rec->lnq_hist[1];
-        rec->lnq_hist[1] = rec->lnq_hist[2];
-        rec->lnq_hist[2] = rec->lnQ;
-        rec->T[0] = rec->Tn[0];
-        rec->T[1] = rec->Tn[1];
-        rec->T[2] = rec->Tn[2];
-        rec->Rprev = (uint64_t)Rprev;
-        rec->Rcur = rec->Rnew;
-        rec->cur ^= 1;
-        rec->gather = spins_moved ? 0 : 1; // else the spins wait in the other buffer
-        rec->beta = rec->beta_next;
-        rec->step += 1;
-        rec->sweeps = 0;
-        rec->weighted = 0;
-        rec->resamplings += 1;
+    if (threadIdx.x == 0)
+        commit_resampled(rec, t / (double)Rprev, rec->Rnew, spins_moved == 0);
+}
+
+// The whole resampling of a small run (capacity up to PA_SMALL_CAP) by one
+// workgroup: copy numbers (SCHEME as above, 3: systematic), ancestor map,
+// energies, magnetisations and labels, and the commit.  Its spins follow as a
+// large run's that the sweeps gather (PaRecord::gather).  Bound by its chain of
+// dependent loads; three launches (copy numbers, gather, commit) with a chain
+// each become one: R = 1000 6.2 + 3.8 + 2.6 us -> 9.5 and two launches less,
+// 1024 runs of R = 100 8.1 + 4.7 + 4.8 -> 9.6.  Every sum keeps the large
+// runs' order and every number their definition, so a run's results depend
+// neither on T (256 where every run fits one chunk, else 1024) nor on the
+// launches of its batch.
+template <int T, int SCHEME>
+__global__ __launch_bounds__(T) void k_resample_small(const PaRunDesc *__restrict__ runs, int freeze)
+{
+    constexpr int kItems = 4, kPer = PA_SMALL_CAP / 1024;
+    static_assert(kPer * 256 >= PA_CHUNK && kThreads * kItems == PA_CHUNK, "every slot has a lane's item");
+    __shared__ unsigned long long s_wave[T / 64];
+    __shared__ double sd[16], part[T / kThreads];
+    __shared__ alignas(16) uint32_t s_mark[T * kItems];
+    __shared__ uint32_t s_max[T / 64];
+    const PaRunDesc &rd = runs[blockIdx.x];
+    PaRecord *rec = rd.dv.rec;
+    if (frozen(rec))
+        return;
+    const int tid = threadIdx.x, cur = rec->cur;
+    const int64_t n = (int64_t)rec->Rcur, base = (int64_t)tid * kItems;
+    unsigned long long agg;
+    if (SCHEME == 3) {
+        uint64_t v[kItems];
+        load_weights<kItems>(rd, rec, base, n, v);
+        unsigned long long run = 0;
+#pragma unroll
+        for (int k = 0; k < kItems; ++k)
+            run += v[k];
+        const unsigned long long before = block_excl_scan<T>(run, s_wave, &agg);
+        __syncthreads(); // the waves' totals have been read
+        systematic_copies<T, kItems>(rd, rec, 0u, n, before, v, part, s_wave, sd, s_mark, s_max);
+        agg = s_wave[1]; // the copies end at N(S)
+    } else {
+        uint32_t r[kItems];
+        double sv;
+        const unsigned long long run = draw_copies<SCHEME, kItems>(rd, rec, base, n, r, &sv);
+        const unsigned long long before = block_excl_scan<T>(run, s_wave, &agg);
+        store_chunk_sv<kItems>(part, rd.cap, 0u, sv, sd);
+        write_ancestors<T, kItems>(rd.dv.anc, rd.cap, 0u, agg, before, r, 0, s_mark, s_max);
+        if (tid == 0)
+            rec->Rnew = agg;
+    }
+    __syncthreads(); // the ancestor map and the new size
+    const uint32_t st = resample_status(rec, rd.cap);
+    const int64_t Rnew = (int64_t)agg;
+    if (st == 0u) {
+        uint32_t a[kPer];
+        int32_t e[kPer], m[kPer];
+        uint32_t l[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) { // a slot past the end loads the last one's
+            const int64_t d = tid + k * T;
+            a[k] = rd.dv.anc[d < Rnew ? d : Rnew - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            e[k] = rd.dv.E[cur][a[k]];
+            m[k] = rd.dv.M[cur][a[k]];
+            l[k] = rd.dv.label[cur][a[k]];
+        }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int64_t d = tid + k * T;
+            if (d < Rnew) {
+                rd.dv.E[cur ^ 1][d] = e[k];
+                rd.dv.M[cur ^ 1][d] = m[k];
+                rd.dv.label[cur ^ 1][d] = l[k];
+            }
+        }
+    }
+    __syncthreads(); // every thread has read the record before thread 0 writes it
+    if (st != 0u) {
+        if (tid == 0) {
+            rec->skip = 1;
+            rec->status = freeze ? (st | PA_ST_FROZEN) : st;
+            rec->gather = 0;
+        }
+        return;
+    }
+    if (tid < 64) {
+        const int nlive = (int)((n + PA_CHUNK - 1) / PA_CHUNK);
+        const double t = pa_wave_sum_f64(tid < nlive ? part[tid] : 0.0);
+        if (tid == 0)
+            commit_resampled(rec, t / (double)n, (uint64_t)Rnew, true);
     }
 }
 
@@ -2898,7 +3037,30 @@ hipError_t pa_b_check_candidate(const PaBatchView &v, double alpha_star, double 
     return hipGetLastError();
 }
 
-// Launches per scheme (after the reweighting): nearest integer and Poisson
+// The spins of the groups whose sweeps do not gather them, after the commit.
+static hipError_t gather_rest(const PaBatchView &v)
+{
+    for (int g = 0; g < v.ngroups; ++g)
+        if (v.gncol[g] && !sweep_gathers(v, g))
+            k_gather_spins<false><<<v.gncol[g], kGatherThreads, 0, v.stream>>>(v.runs, v.gcol[g]);
+    return hipGetLastError();
+}
+
+template <int T>
+static void resample_small_launch(const PaBatchView &v, int scheme, int freeze)
+{
+    if (scheme == 1)
+        k_resample_small<T, 1><<<v.nruns, T, 0, v.stream>>>(v.runs, freeze);
+    else if (scheme == 2)
+        k_resample_small<T, 2><<<v.nruns, T, 0, v.stream>>>(v.runs, freeze);
+    else
+        k_resample_small<T, 3><<<v.nruns, T, 0, v.stream>>>(v.runs, freeze);
+}
+
+// Launches per scheme (after the reweighting): where every run is small and
+// resampled, one workgroup per run for all of it (k_resample_small; a large
+// run needs the whole chip, and conditional or multinomial steps have passes
+// of their own).  Otherwise: nearest integer and Poisson
 // draw the copy numbers and sum them into the ancestor map in one pass;
 // systematic sums the weights and writes the ancestor map from each
 // replica's closed-form copy range in the same pass; multinomial sums the
@@ -2911,6 +3073,13 @@ hipError_t pa_b_resample(const PaBatchView &v, int scheme, int freeze, int kq, b
     hipError_t e;
     if (!prepped)
         k_resample_prep<<<v.nruns, kThreads, 0, v.stream>>>(v.runs);
+    if (v.nlarge == 0 && kq < 0 && scheme >= 1 && scheme <= 3) { // small runs only
+        if (v.small_cap <= PA_CHUNK)
+            resample_small_launch<256>(v, scheme, freeze);
+        else
+            resample_small_launch<1024>(v, scheme, freeze);
+        return gather_rest(v);
+    }
     if (kq >= 0)
         k_cond_decide<<<v.nruns, 64, 0, v.stream>>>(v.runs, (uint32_t)kq);
     switch (scheme) {
@@ -2949,10 +3118,7 @@ hipError_t pa_b_resample(const PaBatchView &v, int scheme, int freeze, int kq, b
     if (kq >= 0)
         k_keep<<<v.nrep, kThreads, 0, v.stream>>>(v.runs, v.rep);
     k_commit<<<v.nruns, kThreads, 0, v.stream>>>(v.runs, freeze, any ? 0 : 1);
-    for (int g = 0; any && g < v.ngroups; ++g)
-        if (v.gncol[g] && !sweep_gathers(v, g))
-            k_gather_spins<false><<<v.gncol[g], kGatherThreads, 0, v.stream>>>(v.runs, v.gcol[g]);
-    return hipGetLastError();
+    return any ? gather_rest(v) : hipGetLastError();
 }
 
 hipError_t pa_b_observables(const PaBatchView &v, int point, int hist_state)
