@@ -1110,12 +1110,8 @@ __global__ __launch_bounds__(kThreads) void k_rw_final(const PaRunDesc *__restri
 // step's weights, ESS = S^2 / sum_j W_j^2, is below kappa R_cur.  Decided
 // exactly as 2^16 S^2 < kq R_cur sum_j W_j^2 (kq = kappa 2^16) on 192-bit
 // integers: S^2 < 2^128, sum W^2 < 2^104, kq R_cur < 2^41.
-__global__ void k_cond_decide(const PaRunDesc *__restrict__ runs, uint32_t kq)
+__device__ __forceinline__ bool ess_below(const PaRecord *rec, uint32_t kq)
 {
-    const PaRunDesc &rd = runs[blockIdx.x];
-    PaRecord *rec = rd.dv.rec;
-    if (threadIdx.x != 0 || frozen(rec))
-        return;
     const uint64_t S = rec->S;
     const pa_u128 S2 = (pa_u128)S * S;
     const uint64_t a0 = (uint64_t)(S2 << 16), a1 = (uint64_t)((S2 << 16) >> 64), a2 = (uint64_t)(S2 >> 112);
@@ -1123,12 +1119,24 @@ __global__ void k_cond_decide(const PaRunDesc *__restrict__ runs, uint32_t kq)
     const pa_u128 p0 = (pa_u128)rec->Q2[0] * f, p1 = (pa_u128)rec->Q2[1] * f;
     const pa_u128 mid = (p0 >> 64) + (pa_u128)(uint64_t)p1;
     const uint64_t r0 = (uint64_t)p0, r1 = (uint64_t)mid, r2 = (uint64_t)(p1 >> 64) + (uint64_t)(mid >> 64);
-    const bool resample = a2 != r2 ? a2 < r2 : (a1 != r1 ? a1 < r1 : a0 < r0);
-    rec->keep = resample ? 0u : 1u;
-    if (!resample)
-        rec->Rnew = rec->Rcur; // the capacity and extinction checks see the kept size
+    return a2 != r2 ? a2 < r2 : (a1 != r1 ? a1 < r1 : a0 < r0);
 }
 
+// Whether a run's population is kept (kq < 0: never).  Every workgroup of the
+// resampling's first pass decides it from the same sums, which that pass does
+// not change; the run's first one records it, and the kept size for the
+// capacity and extinction checks, for the passes after it.  (As a launch of its
+// own the decision took 4.6 us of a step.)
+__device__ __forceinline__ bool decide_kept(PaRecord *rec, int kq, uint32_t block)
+{
+    if (kq < 0 || ess_below(rec, (uint32_t)kq))
+        return false;
+    if (block == 0 && threadIdx.x == 0) {
+        rec->keep = 1u;
+        rec->Rnew = rec->Rcur;
+    }
+    return true;
+}
 
 // Sampling variance, Eq. (5): each chunk sums (r_j - tauhat_j)^2 over its
 // replicas in a fixed order (per thread, then the block's fixed tree) into
@@ -1632,7 +1640,7 @@ __device__ __forceinline__ void weights_scan_tile(const PaRunDesc &rd, PaRecord 
 
 template <int MODE>
 __global__ __launch_bounds__(kThreads) void k_weights_scan(const PaRunDesc *__restrict__ runs,
-                                                           const PaBlk *__restrict__ map)
+                                                           const PaBlk *__restrict__ map, int kq)
 {
     __shared__ uint32_t s_tile;
     __shared__ unsigned long long s_wave[kThreads / 64];
@@ -1643,7 +1651,7 @@ __global__ __launch_bounds__(kThreads) void k_weights_scan(const PaRunDesc *__re
     const PaBlk b = map[blockIdx.x];
     const PaRunDesc &rd = runs[b.run];
     PaRecord *rec = rd.dv.rec;
-    if (frozen(rec) || rec->keep)
+    if (frozen(rec) || decide_kept(rec, kq, b.idx))
         return; // every tile of a frozen (or kept) run returns: none waits
     if (threadIdx.x == 0)
         s_tile = atomicAdd(&rec->ticket[0], 1u);
@@ -1742,7 +1750,7 @@ __device__ __forceinline__ void counts_scan_tile(const PaRunDesc &rd, PaRecord *
 
 template <int SCHEME>
 __global__ __launch_bounds__(kThreads) void k_counts_scan(const PaRunDesc *__restrict__ runs,
-                                                          const PaBlk *__restrict__ map)
+                                                          const PaBlk *__restrict__ map, int kq)
 {
     __shared__ uint32_t s_tile;
     __shared__ unsigned long long s_wave[kThreads / 64];
@@ -1753,7 +1761,7 @@ __global__ __launch_bounds__(kThreads) void k_counts_scan(const PaRunDesc *__res
     const PaBlk b = map[blockIdx.x];
     const PaRunDesc &rd = runs[b.run];
     PaRecord *rec = rd.dv.rec;
-    if (frozen(rec) || rec->keep)
+    if (frozen(rec) || decide_kept(rec, kq, b.idx))
         return; // every tile of a frozen (or kept) run returns: none waits
     if (threadIdx.x == 0)
         s_tile = atomicAdd(&rec->ticket[1], 1u);
@@ -1806,20 +1814,33 @@ __device__ __forceinline__ uint32_t resample_status(const PaRecord *rec, int64_t
 
 // ------------------------------------------------------------------ apply
 
+// The replicas [beg, end) of a kept population take their new log-weights
+// x_j + m (m = 0 if it was uniform).
+__device__ __forceinline__ void keep_weights(const PaRunDesc &rd, const PaRecord *rec, int64_t beg, int64_t end)
+{
+    const bool wt = rec->weighted != 0u;
+    const double m = wt ? xmag_value(rec) : 0.0;
+    for (int64_t j = beg + threadIdx.x; j < end; j += blockDim.x)
+        rd.dv.lw[j] = wx(rd.dv, rec, rec->cur, wt, j) + m;
+}
+
 // A resampled population's energies, magnetisations and labels, from their
 // ancestors into the other buffer (before the commit swaps the buffers).  Its
 // spins follow later (PaRecord::gather): in the next sweep's column load, or
-// in k_gather_spins when something else reads them first.
+// in k_gather_spins when something else reads them first.  A kept population
+// gets its new log-weights here.
 __global__ __launch_bounds__(kThreads) void k_gather_meta(const PaRunDesc *__restrict__ runs,
                                                           const PaBlk *__restrict__ map)
 {
     const PaBlk blk = map[blockIdx.x];
     const PaRunDesc &rd = runs[blk.run];
     PaRecord *rec = rd.dv.rec;
-    if (frozen(rec) || rec->keep || resample_status(rec, rd.cap) != 0u)
+    if (frozen(rec) || resample_status(rec, rd.cap) != 0u)
         return;
-    const int64_t Rnew = (int64_t)rec->Rnew;
+    const int64_t Rnew = (int64_t)rec->Rnew; // kept: the population's size
     const int64_t beg = (int64_t)blk.idx * PA_CHUNK, end = beg + PA_CHUNK < Rnew ? beg + PA_CHUNK : Rnew;
+    if (rec->keep)
+        return keep_weights(rd, rec, beg, end);
     const int cur = rec->cur;
     for (int64_t d = beg + threadIdx.x; d < end; d += blockDim.x) {
         const uint32_t a = rd.dv.anc[d];
@@ -1854,8 +1875,10 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather_spins(const PaRunDesc
     const uint32_t w = blk.idx;
     if (frozen(rec) || (int64_t)w * 64 >= R)
         return;
-    if (PRE ? (rec->keep || resample_status(rec, rd.cap) != 0u) : rec->gather == 0u)
+    if (PRE ? resample_status(rec, rd.cap) != 0u : rec->gather == 0u)
         return;
+    if (PRE && rec->keep) // kept: its new log-weights
+        return keep_weights(rd, rec, 64 * (int64_t)w, min(64 * (int64_t)w + 64, R));
     const int N = rd.N;
     const int cur = rec->cur;
     const int from = PRE ? cur : cur ^ 1;
@@ -1878,21 +1901,6 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather_spins(const PaRunDesc
         gather_sites<8>(rd.dv.spins[from], N, G, put);
     else
         gather_sites<4>(rd.dv.spins[from], N, G, put);
-}
-
-// A kept population takes its new log-weights x_j + m (m = 0 if it was uniform).
-__global__ __launch_bounds__(kThreads) void k_keep(const PaRunDesc *__restrict__ runs,
-                                                   const PaBlk *__restrict__ map)
-{
-    RepCtx c;
-    if (!rep_ctx(runs, map, &c) || !c.rec->keep || resample_status(c.rec, c.rd->cap) != 0u)
-        return;
-    const PaDev &dv = c.rd->dv;
-    const int cur = c.rec->cur;
-    const bool wt = c.rec->weighted != 0u;
-    const double m = wt ? xmag_value(c.rec) : 0.0;
-    for (int64_t j = c.beg + threadIdx.x; j < c.end; j += blockDim.x)
-        dv.lw[j] = wx(dv, c.rec, cur, wt, j) + m;
 }
 
 // The record after an applied resampling (one thread).
@@ -3072,13 +3080,13 @@ static void resample_small_launch(const PaBatchView &v, int scheme, int freeze)
 // Launches per scheme (after the reweighting): where every run is small and
 // resampled, one workgroup per run for all of it (k_resample_small; a large
 // run needs the whole chip, and conditional or multinomial steps have passes
-// of their own).  Otherwise: nearest integer and Poisson
-// draw the copy numbers and sum them into the ancestor map in one pass;
-// systematic sums the weights and writes the ancestor map from each
-// replica's closed-form copy range in the same pass; multinomial sums the
-// weights, draws, adds the sampling variance and sums the copy numbers.
-// Then the energies, magnetisations and labels move to the ancestors' order
-// and the commit swaps the buffers; the spins follow at once for groups whose
+// of their own).  Otherwise: nearest integer and Poisson draw the copy numbers
+// and sum them into the ancestor map in one pass; systematic sums the weights
+// and writes the ancestor map from each replica's closed-form copy range in
+// the same pass; multinomial sums the weights, draws, adds the sampling
+// variance and sums the copy numbers.  Then the energies, magnetisations and
+// labels move to the ancestors' order (a kept population takes its new
+// log-weights in the same launch) and the commit swaps the buffers; the spins follow at once for groups whose
 // sweeps do not gather them, else in the next sweep or pa_b_gather.
 hipError_t pa_b_resample(const PaBatchView &v, int scheme, int freeze, int kq, bool prepped)
 {
@@ -3092,21 +3100,19 @@ hipError_t pa_b_resample(const PaBatchView &v, int scheme, int freeze, int kq, b
             resample_small_launch<1024>(v, scheme, freeze);
         return gather_rest(v);
     }
-    if (kq >= 0)
-        k_cond_decide<<<v.nruns, 64, 0, v.stream>>>(v.runs, (uint32_t)kq);
     switch (scheme) {
     case 2:
-        k_counts_scan<2><<<v.ncrep, kThreads, 0, v.stream>>>(v.runs, v.crep);
+        k_counts_scan<2><<<v.ncrep, kThreads, 0, v.stream>>>(v.runs, v.crep, kq);
         break;
     case 1:
-        k_counts_scan<1><<<v.ncrep, kThreads, 0, v.stream>>>(v.runs, v.crep);
+        k_counts_scan<1><<<v.ncrep, kThreads, 0, v.stream>>>(v.runs, v.crep, kq);
         break;
     case 3:
     case 0:
         if (scheme == 3) {
-            k_weights_scan<PA_SCAN_SYSTEMATIC><<<v.ncrep, kThreads, 0, v.stream>>>(v.runs, v.crep);
+            k_weights_scan<PA_SCAN_SYSTEMATIC><<<v.ncrep, kThreads, 0, v.stream>>>(v.runs, v.crep, kq);
         } else {
-            k_weights_scan<PA_SCAN_MULTINOMIAL><<<v.ncrep, kThreads, 0, v.stream>>>(v.runs, v.crep);
+            k_weights_scan<PA_SCAN_MULTINOMIAL><<<v.ncrep, kThreads, 0, v.stream>>>(v.runs, v.crep, kq);
             k_counts_multinomial<<<v.nrep, kThreads, 0, v.stream>>>(v.runs, v.rep);
             k_sv_partial<<<v.nrep, kThreads, 0, v.stream>>>(v.runs, v.rep);
             k_scan_counts<<<v.ntile, PA_SCAN_THREADS, 0, v.stream>>>(v.runs, v.tile);
@@ -3127,8 +3133,6 @@ hipError_t pa_b_resample(const PaBatchView &v, int scheme, int freeze, int kq, b
         k_gather_meta<<<v.nrep, kThreads, 0, v.stream>>>(v.runs, v.rep);
     else
         k_gather_spins<true><<<v.ncol, kGatherThreads, 0, v.stream>>>(v.runs, v.col);
-    if (kq >= 0)
-        k_keep<<<v.nrep, kThreads, 0, v.stream>>>(v.runs, v.rep);
     k_commit<<<v.nruns, kThreads, 0, v.stream>>>(v.runs, freeze, any ? 0 : 1);
     return any ? gather_rest(v) : hipGetLastError();
 }
