@@ -218,6 +218,7 @@ uint64_t carve_run(const Geometry &g, char *base, PaDev *dv)
     d.qhist = (unsigned long long *)take((uint64_t)(g.N + 1) * 8);
     // tile flags of the two prefix sums of a resampling (weights, copy numbers)
     d.tiles = (PaScanTile *)take((uint64_t)(2 * pa_tiles_per_sum(g.cap)) * sizeof(PaScanTile));
+    d.calls = (unsigned long long *)take((uint64_t)g.W * 8);
     d.partial = (double *)take(chunks * 8);
     d.fam = (uint32_t *)take((uint64_t)g.R * 4);
     d.lw = (double *)take(slots * 8);
@@ -1225,6 +1226,9 @@ pa_status pa_get_counters(pa_ctx *c, pa_counters *out)
     Batch *b = &c->b;
     if (!out)
         return fail(b, PA_E_INVAL, "out is NULL");
+    const hipError_t e = pa_b_counters(b->v);
+    if (e != hipSuccess)
+        return hip_fail(b, e, "pa_get_counters");
     pa_status s = ctx_records(b, "pa_get_counters");
     if (s != PA_OK)
         return s;

@@ -56,7 +56,7 @@ struct PaRecord {
     float feat[8];                 // inputs of the learned step model
     double cand_dbeta;             // the model's proposal
     uint32_t fallback, pad1;       // 1: the proposal failed the overlap check
-    unsigned long long philox_calls; // Philox4x32-10 evaluations of all sweeps so far
+    unsigned long long philox_calls; // Philox4x32-10 evaluations of all sweeps so far (summed by pa_b_counters)
     unsigned long long site_updates; // word-site updates (64 attempts each) so far
     unsigned long long attempts;     // spin-flip attempts so far: theta N R per sweep call
     uint32_t ticket[2];              // tile tickets of the two prefix sums of a resampling
@@ -121,6 +121,7 @@ struct PaDev {
     uint64_t *C;
     unsigned long long *qhist; // [N+1] overlap histogram
     PaScanTile *tiles;
+    unsigned long long *calls; // [W] Philox evaluations of each column's sweeps so far
     double *partial; // fixed-order partial sums, one per chunk
     uint32_t *fam;   // [R0] replicas per family
     double *lw;      // [slots] log-weights of a weighted population
@@ -212,6 +213,7 @@ hipError_t pa_b_init(const PaBatchView &v);
 // t0: sweeps already done at this beta; gather: the populations' spins may
 // still be in the other buffer (PaRecord::gather), taken in by the sweep
 hipError_t pa_b_sweep(const PaBatchView &v, int theta, uint32_t t0, int gather);
+hipError_t pa_b_counters(const PaBatchView &v); // sums the columns' Philox evaluations into the records
 hipError_t pa_b_gather(const PaBatchView &v); // gathers the spins a resampling left for the sweeps to gather
 hipError_t pa_b_sweep_group(const PaBatchView &v, int g, int theta, int threads);
 // hist_clean: the level histogram is zero (observables or init ran since it was last built)

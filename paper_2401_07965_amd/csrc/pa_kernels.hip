@@ -82,6 +82,21 @@ __global__ __launch_bounds__(kThreads) void k_sites(const PaRunDesc *__restrict_
     }
 }
 
+// A run's Philox evaluations: its columns' counts (each written by its column's
+// workgroup alone).
+__global__ __launch_bounds__(kThreads) void k_sum_calls(const PaRunDesc *__restrict__ runs)
+{
+    __shared__ uint64_t su[16];
+    const PaRunDesc &rd = runs[blockIdx.x];
+    const int64_t W = (rd.cap + 63) / 64;
+    uint64_t n = 0;
+    for (int64_t w = threadIdx.x; w < W; w += blockDim.x)
+        n += rd.dv.calls[w];
+    n = pa_block_sum_u64(n, su);
+    if (threadIdx.x == 0)
+        rd.dv.rec->philox_calls = n;
+}
+
 // Replica 64w+b, site s: bit b of x0 | x1<<32 of Philox(s, w, 0, INIT<<28).
 __global__ __launch_bounds__(kThreads) void k_init_spins(const PaRunDesc *__restrict__ runs,
                                                          const PaBlk *__restrict__ map)
@@ -89,6 +104,8 @@ __global__ __launch_bounds__(kThreads) void k_init_spins(const PaRunDesc *__rest
     const PaBlk b = map[blockIdx.x];
     const PaRunDesc &rd = runs[b.run];
     const uint32_t w = b.idx;
+    if (threadIdx.x == 0)
+        rd.dv.calls[w] = 0;
     if ((int64_t)w * 64 >= rd.R0)
         return;
     uint64_t *g = rd.dv.spins[0] + (size_t)w * rd.N;
@@ -361,7 +378,8 @@ __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(cons
     }
     if (tid == 0 && w == 0) // once per run; no block reads it during the launch
         rec->sweeps = t0 + (uint32_t)nsteps;
-    recount_column<D, J>(lat, [&](int t, int, int, int) -> uint32_t { return jl[t]; }, g, xb, rd, cur, w, Rlive, L, N, LL, mL);
+    recount_column<D, J>(lat, [&](int t, int, int, int) -> uint32_t { return jl[t]; }, g, xb, rd, cur, w, Rlive, L, N,
+                         LL, mL, 0ull);
 }
 
 // The sweep counter advances after the sweeps (a separate launch, so that no
@@ -2964,6 +2982,12 @@ hipError_t pa_b_init(const PaBatchView &v)
 hipError_t pa_b_sweep_group(const PaBatchView &v, int g, int theta, int threads)
 {
     return sweep_launch(v, g, theta, threads, 0u, v.stream, 0);
+}
+
+hipError_t pa_b_counters(const PaBatchView &v)
+{
+    k_sum_calls<<<v.nruns, kThreads, 0, v.stream>>>(v.runs);
+    return hipGetLastError();
 }
 
 hipError_t pa_b_gather(const PaBatchView &v)

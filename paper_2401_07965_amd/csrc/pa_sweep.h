@@ -416,10 +416,15 @@ __device__ __forceinline__ void wave_count2(const uint64_t (&a)[8], const uint64
 // writes the lattice back to g.  Per-lane counts stay below 2^8: at most
 // ceil(N / blockDim) sites per lane, d bonds each (the launch checks).
 // jbits(t, x, y, z): site t's bond bits (bit mu: to s + e_mu).
+// calls: the wave's Philox evaluations, added to the column's count here: an
+// atomic per wave on the run's record (and one per workgroup for the updates)
+// took 12 to 14 ns each, one after the other, and held the launch's end back:
+// two sweeps of 6200 columns of 2D L = 24 257 -> 106 us (128 lanes), of 4000 of
+// 3D L = 8 121 -> 55 (64 lanes), of 1536 of 3D L = 16 155 -> 135 (256).
 template <int D, bool J, typename JBits>
 __device__ __forceinline__ void recount_column(const uint64_t *lat, JBits jbits, uint64_t *g, uint64_t *red,
                                                const PaRunDesc &rd, int cur, uint32_t w, int64_t Rlive, int L,
-                                               int N, int LL, uint32_t mL)
+                                               int N, int LL, uint32_t mL, uint64_t calls)
 {
     const int tid = threadIdx.x, bs = blockDim.x;
     uint64_t ve[8] = {0, 0, 0, 0, 0, 0, 0, 0}, vm[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -472,9 +477,17 @@ __device__ __forceinline__ void recount_column(const uint64_t *lat, JBits jbits,
 #pragma unroll
         for (int k = 0; k < 14; ++k)
             red32[wave * 64 + (lane & 1) * 32 + (lane >> 1) * 16 + k] = c[k];
+    if (lane == 0) // the places the 14 planes leave
+        red[wave * 32 + 7] = calls;
     __syncthreads();
     if (wave == 0) {
         uint32_t U = 0, nd = 0;
+        if (lane == 0) {
+            for (int v = 1; v < nw; ++v)
+                calls += red[v * 32 + 7];
+            if (calls)
+                rd.dv.calls[w] += calls;
+        }
         const uint32_t *p = red32 + (lane >> 5) * 16; // this replica's half
         const uint32_t bit = (uint32_t)lane & 31u;
         for (int v = 0; v < nw; ++v, p += 64)
@@ -1076,16 +1089,11 @@ __device__ __forceinline__ void sweep_column(const PaRunDesc *__restrict__ runs,
         with_walk(std::false_type{});
 
     // after the sweeps the queue region is free: per-wave partial counts of the measurement
-    if (theta > 0) {
-        const uint64_t tot = pa_wave_sum_u64(calls);
-        if ((tid & 63) == 0)
-            atomicAdd(&rec->philox_calls, (unsigned long long)tot);
-        if (tid == 0)
-            atomicAdd(&rec->site_updates, (unsigned long long)theta * (unsigned long long)N);
-        if (tid == 0 && w == 0) { // once per run; no block reads these during the launch
-            rec->sweeps = t0 + (uint32_t)theta;
-            rec->attempts += (unsigned long long)theta * (unsigned long long)N * (unsigned long long)Rlive;
-        }
+    if (theta > 0 && tid == 0 && w == 0) { // once per run; no block reads these during the launch
+        const unsigned long long updates = (unsigned long long)theta * (unsigned long long)N;
+        rec->sweeps = t0 + (uint32_t)theta;
+        rec->site_updates += updates * (unsigned long long)((Rlive + 63) / 64);
+        rec->attempts += updates * (unsigned long long)Rlive;
     }
     auto jbits = [&](int t, int x, int y, int z) -> uint32_t {
         if (!table)
@@ -1093,7 +1101,8 @@ __device__ __forceinline__ void sweep_column(const PaRunDesc *__restrict__ runs,
         const int c = (x + y + z) & 1, k = (y + L * z) * half + (x >> 1); // the site's place in the walk
         return (tab[c * nh + k] >> kSiteJ) & 63u;
     };
-    recount_column<D, J>(lat, jbits, g, lat + N, rd, cur, w, Rlive, L, N, LL, mL);
+    recount_column<D, J>(lat, jbits, g, lat + N, rd, cur, w, Rlive, L, N, LL, mL,
+                         theta > 0 ? pa_wave_sum_u64(calls) : 0ull);
 }
 
 // The kernel in two register allocations.  Its registers would allow 5 (3D) to
