@@ -98,40 +98,37 @@ constexpr int kLdsPerCu = 163840; // gfx950: 160 KiB of LDS per CU
 // Modelled time (cycles) of one colour's updates over all columns of a batch
 // with t lanes per column: rounds of as many columns as a CU holds, then what
 // is left.  A column's colour takes passes over its sites, each the longer of
-// one wave's latency (1450 cycles) and its SIMD's waves taking turns (1200
-// cycles a wave, 3 % more with coordinates computed at each site), and an end
-// (250 cycles, 750 per wave and SIMD, 120 per wave of the workgroup).  Waves
+// one wave's latency (1500 cycles) and its SIMD's waves taking turns (1200
+// cycles a wave, 2 % more with coordinates computed at each site), and an end
+// (60 cycles, 900 per wave and SIMD, 70 per wave of the workgroup).  Waves
 // spread evenly over the SIMDs only in workgroups of four or eight; others can
-// meet on one, those of 3, 5, 6 ... waves leave SIMDs idle (3 %), and single
-// ones in 2D, up to seven to a SIMD, gain less than their number (8 %).
-// Fitted to the times of all sizes on 23 shapes (more than 512 columns, theta
-// = 10), 4 % off on average among the better sizes.
+// meet on one, and those of 3, 5, 6 ... waves leave SIMDs idle (40 %).
+// Fitted to the times of all sizes on 945 shapes, numbers of columns above 512,
+// sweeps a launch (2 and 10) and temperatures.
 double colour_cycles(int N, int d, int t, bool J, int64_t columns)
 {
     constexpr int kCus = 256;
-    const int w = t / 64, nh = N / 2, cap = pa_sweep_waves_cap(N, d, t, J);
+    const int w = t / 64, cap = pa_sweep_waves_cap(N, d, t, J);
     int blocks = (int)((size_t)kLdsPerCu / pa_sweep_lds_bytes(N, d, t, J));
     blocks = std::min(blocks, cap / w);
     if (blocks < 1)
         return HUGE_VAL;
-    const int walk = pa_sweep_walk(N, d, t, J);
-    const double uneven = w > 2 && w % 4 ? 1.03 : w == 1 && d == 2 ? 1.08 : 1.0;
-    const double issue = 1200.0 * (walk == 0 ? 1.03 : 1.0) * uneven;
+    const double issue = 1200.0 * (pa_sweep_walk(N, d, t, J) == 0 ? 1.02 : 1.0) * (w > 2 && w % 4 ? 1.4 : 1.0);
+    const double passes = std::max(1.0, (double)((N / 2 + 63) / 64 * 64) / t);
     auto together = [&](int b) { // b columns on each CU
-        const double ws = w % 4 == 0 ? b * w / 4.0 : std::min(cap / 4.0, b * w / 4.0 + 0.4);
-        const double passes = std::max(1.0, (double)((nh + 63) / 64 * 64) / t);
-        return passes * std::hypot(1450.0, issue * ws) + 250.0 + 750.0 * ws + 120.0 * w;
+        const double ws = w % 4 == 0 ? b * w / 4.0 : std::min(cap / 4.0, b * w / 4.0 + 0.7);
+        return passes * std::hypot(1500.0, issue * ws) + 60.0 + 900.0 * ws + 70.0 * w;
     };
     const int64_t round = (int64_t)kCus * blocks, left = columns % round;
     return (double)(columns / round) * together(blocks) + (left ? together((int)((left + kCus - 1) / kCus)) : 0.0);
 }
 
-// Default sweep workgroup size: the least modelled time.  It is the best of
-// all sizes on 22 of those shapes and 2 % behind it on one (2D L = 32);
-// counting resident waves alone, as it was chosen before, lost 15 to 19 % at 3D
-// L = 12 (922 us with 128 lanes, 790 with 256), 3D L = 14 (997 with 192, 829
-// with 256) and 2D L = 48 (707 with 128, 595 with 256).  Autotuning refines it
-// for batches.
+// Default sweep workgroup size: the least modelled time.  On the shapes it was
+// fitted to it loses 0.6 % on average against the best of all sizes, 17 % at
+// most; by the waves a CU holds, as it was chosen before, 6.9 % and 52 %: ten
+// sweeps at 3D L = 12 took 922 us with 128 lanes, 790 with 256 (4688 columns),
+// 3D L = 14 997 with 192, 829 with 256 (3125), 2D L = 48 707 with 128, 595 with
+// 256 (3125).  Autotuning refines it for batches.
 int default_sweep_threads(int N, int d, bool J, int64_t columns)
 {
     const size_t lds_max = (size_t)(g_max_lds ? g_max_lds : kLdsPerCu);
