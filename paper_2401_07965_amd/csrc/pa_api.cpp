@@ -102,7 +102,8 @@ constexpr int kLdsPerCu = 163840; // gfx950: 160 KiB of LDS per CU
 // cycles a wave, 2 % more with coordinates computed at each site), and an end
 // (60 cycles, 900 per wave and SIMD, 70 per wave of the workgroup).  Waves
 // spread evenly over the SIMDs only in workgroups of four or eight; others can
-// meet on one, and those of 3, 5, 6 ... waves leave SIMDs idle (40 %).
+// meet on one, those of 3, 5, 6 ... waves leave SIMDs idle (40 %), and those of
+// two, where five share a SIMD, gain less than their number (3 %).
 // Fitted to the times of all sizes on 945 shapes, numbers of columns above 512,
 // sweeps a launch (2 and 10) and temperatures.
 double colour_cycles(int N, int d, int t, bool J, int64_t columns)
@@ -113,7 +114,8 @@ double colour_cycles(int N, int d, int t, bool J, int64_t columns)
     blocks = std::min(blocks, cap / w);
     if (blocks < 1)
         return HUGE_VAL;
-    const double issue = 1200.0 * (pa_sweep_walk(N, d, t, J) == 0 ? 1.02 : 1.0) * (w > 2 && w % 4 ? 1.4 : 1.0);
+    const double uneven = w > 2 && w % 4 ? 1.4 : w == 2 && cap > 16 ? 1.03 : 1.0;
+    const double issue = 1200.0 * (pa_sweep_walk(N, d, t, J) == 0 ? 1.02 : 1.0) * uneven;
     const double passes = std::max(1.0, (double)((N / 2 + 63) / 64 * 64) / t);
     auto together = [&](int b) { // b columns on each CU
         const double ws = w % 4 == 0 ? b * w / 4.0 : std::min(cap / 4.0, b * w / 4.0 + 0.7);
@@ -123,27 +125,25 @@ double colour_cycles(int N, int d, int t, bool J, int64_t columns)
     return (double)(columns / round) * together(blocks) + (left ? together((int)((left + kCus - 1) / kCus)) : 0.0);
 }
 
-// Default sweep workgroup size: the least modelled time.  On the shapes it was
-// fitted to it loses 0.6 % on average against the best of all sizes, 17 % at
-// most; by the waves a CU holds, as it was chosen before, 6.9 % and 52 %: ten
-// sweeps at 3D L = 12 took 922 us with 128 lanes, 790 with 256 (4688 columns),
-// 3D L = 14 997 with 192, 829 with 256 (3125), 2D L = 48 707 with 128, 595 with
-// 256 (3125).  Autotuning refines it for batches.
+// Default sweep workgroup size: the smallest within 2 % of the least modelled
+// time.  On the shapes it was fitted to it loses 0.6 % on average against the
+// best of all sizes, 15 % at most; by the waves a CU holds, as it was chosen
+// before, 6.9 % and 52 %: ten sweeps at 3D L = 12 took 922 us with 128 lanes,
+// 790 with 256 (4688 columns), 3D L = 14 997 with 192, 829 with 256 (3125), 2D
+// L = 48 707 with 128, 595 with 256 (3125).  Autotuning refines it for batches.
 int default_sweep_threads(int N, int d, bool J, int64_t columns)
 {
     const size_t lds_max = (size_t)(g_max_lds ? g_max_lds : kLdsPerCu);
-    double least = HUGE_VAL;
-    int best = 768; // none fits: rejected by the LDS check of the batch set-up
+    double cycles[13], least = HUGE_VAL;
     for (int t = 64; t <= 768; t += 64) {
-        if (!sweep_threads_ok(N, d, t) || pa_sweep_lds_bytes(N, d, t, J) > lds_max)
-            continue;
-        const double c = colour_cycles(N, d, t, J, columns);
-        if (c < least) {
-            least = c;
-            best = t;
-        }
+        const bool ok = sweep_threads_ok(N, d, t) && pa_sweep_lds_bytes(N, d, t, J) <= lds_max;
+        cycles[t / 64] = ok ? colour_cycles(N, d, t, J, columns) : HUGE_VAL;
+        least = std::min(least, cycles[t / 64]);
     }
-    return best;
+    for (int t = 64; t <= 768 && least < HUGE_VAL; t += 64)
+        if (cycles[t / 64] <= 1.02 * least)
+            return t;
+    return 768; // none fits: rejected by the LDS check of the batch set-up
 }
 
 // Default size where the batch's columns leave the chip short of workgroups
