@@ -1024,7 +1024,7 @@ def main():
         "sweep_attempts_per_ns": r["attempts"] / (sum(r["sweep_ms"]) * 1e-3) / 1e9,
         "resample_GB_per_s": r["res_bytes"] / (sum(r["res_ms"]) * 1e-3) / 1e9,
         "sweep_share_of_step": sum(r["sweep_ms"]) * 1e-3 / r["elapsed"],
-        "roofline": sweep_roofline("k_sweep<3,true>", L ** D, r["attempts"], r["calls"], r["updates"], r["words"],
+        "roofline": sweep_roofline("k_sweep4<3,true>", L ** D, r["attempts"], r["calls"], r["updates"], r["words"],
                                    r["sweep_ms"], rate, "3d_pmj", prof),
     }
     rows = [] if a.no_rows else [x for x in a.rows.split(",") if x]
