@@ -313,6 +313,22 @@ hipError_t launch_resample(Batch *b, int scheme, int freeze, int kq)
     return e;
 }
 
+// A reweighting and the resampling after it.
+hipError_t launch_advance(Batch *b, double beta_next, int scheme, int freeze)
+{
+    if (!pa_advances_at_once(b->v, scheme)) {
+        const hipError_t e = launch_reweight(b, beta_next);
+        return e == hipSuccess ? launch_resample(b, scheme, freeze, -1) : e;
+    }
+    hipError_t e = settle_spins(b); // the ancestors below are of the populations as they are now
+    if (e == hipSuccess)
+        e = pa_b_advance(b->v, beta_next, b->hist_state, scheme, freeze);
+    b->gather_pending = true;
+    b->rs_prepped = false;
+    b->hist_state = PA_HIST_ZERO;
+    return e;
+}
+
 // The observables pass also builds the level histogram unless it is valid.
 hipError_t launch_observables(Batch *b, int point)
 {
@@ -1424,9 +1440,7 @@ pa_status pa_batch_anneal(pa_batch *p, const double *betas, int32_t npoints, int
     if (e == hipSuccess)
         e = launch_observables(b, 0);
     for (int i = 1; i < npoints && e == hipSuccess; ++i) {
-        e = launch_reweight(b, betas[i]);
-        if (e == hipSuccess)
-            e = launch_resample(b, (int)scheme, 1, -1);
+        e = launch_advance(b, betas[i], (int)scheme, 1);
         if (e == hipSuccess && theta > 0)
             e = launch_updates(b, theta, 0u, 0); // every run was just resampled
         if (e == hipSuccess)

@@ -226,6 +226,9 @@ hipError_t pa_b_reweight(const PaBatchView &v, double beta_next, int hist_state)
 // kq >= 0: conditional, resample only when ESS < kq 2^-16 R_cur (else keep the population)
 // prepped: a pa_b_reweight came right before (it clears the resampling's flags and status)
 hipError_t pa_b_resample(const PaBatchView &v, int scheme, int freeze, int kq, bool prepped);
+// Both at once, where pa_advances_at_once says so (small runs, none weighted).
+bool pa_advances_at_once(const PaBatchView &v, int scheme);
+hipError_t pa_b_advance(const PaBatchView &v, double beta_next, int hist_state, int scheme, int freeze);
 hipError_t pa_b_observables(const PaBatchView &v, int point, int hist_state); // builds the histogram if not valid
 hipError_t pa_b_rule(const PaBatchView &v, double alpha_star, double dbeta_max, int iterations, int bisect,
                      int hist_state);

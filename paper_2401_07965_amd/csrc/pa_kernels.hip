@@ -466,13 +466,9 @@ __device__ __forceinline__ pa_u128 block_sum_u128(pa_u128 v, uint64_t *su)
 // but started: 1024 runs of 2D L = 16 15.5 -> 5.9 us.  The sums are of the same 16 waves' chunks
 // either way.
 template <int T>
-__global__ __launch_bounds__(T) void k_reweight(const PaRunDesc *__restrict__ runs, double beta_next)
+__device__ __forceinline__ void reweight_run(const PaRunDesc &rd, PaRecord *rec, double beta_next)
 {
     __shared__ uint64_t su[16 * 6];
-    const PaRunDesc &rd = runs[blockIdx.x];
-    PaRecord *rec = rd.dv.rec;
-    if (frozen(rec))
-        return;
     const int DN = rd.d * rd.N;
     const double dbeta = beta_next - rec->beta;
     const int32_t emin = rec->emin, emax = rec->emax;
@@ -572,6 +568,14 @@ __global__ __launch_bounds__(T) void k_reweight(const PaRunDesc *__restrict__ ru
     } else if (threadIdx.x < 4) {
         rec->Tn[threadIdx.x - 1] = pa_threshold(beta_next, 4 * (int)threadIdx.x);
     }
+}
+
+template <int T>
+__global__ __launch_bounds__(T) void k_reweight(const PaRunDesc *__restrict__ runs, double beta_next)
+{
+    const PaRunDesc &rd = runs[blockIdx.x];
+    if (!frozen(rd.dv.rec))
+        reweight_run<T>(rd, rd.dv.rec, beta_next);
 }
 
 // ------------------------------------------------------------------ adaptive step
@@ -2006,7 +2010,7 @@ __global__ __launch_bounds__(kThreads) void k_commit(const PaRunDesc *__restrict
 // neither on T (256 where every run fits one chunk, else 1024) nor on the
 // launches of its batch.
 template <int T, int SCHEME>
-__global__ __launch_bounds__(T) void k_resample_small(const PaRunDesc *__restrict__ runs, int freeze)
+__device__ __forceinline__ void resample_small_run(const PaRunDesc &rd, PaRecord *rec, int freeze)
 {
     constexpr int kItems = 4, kPer = PA_SMALL_CAP / 1024;
     static_assert(kPer * 256 >= PA_CHUNK && kThreads * kItems == PA_CHUNK, "every slot has a lane's item");
@@ -2014,10 +2018,6 @@ __global__ __launch_bounds__(T) void k_resample_small(const PaRunDesc *__restric
     __shared__ double sd[16], part[T / kThreads];
     __shared__ alignas(16) uint32_t s_mark[T * kItems];
     __shared__ uint32_t s_max[T / 64];
-    const PaRunDesc &rd = runs[blockIdx.x];
-    PaRecord *rec = rd.dv.rec;
-    if (frozen(rec))
-        return;
     const int tid = threadIdx.x, cur = rec->cur;
     const int64_t n = (int64_t)rec->Rcur, base = (int64_t)tid * kItems;
     unsigned long long agg;
@@ -2085,6 +2085,28 @@ __global__ __launch_bounds__(T) void k_resample_small(const PaRunDesc *__restric
         if (tid == 0)
             commit_resampled(rec, t / (double)n, (uint64_t)Rnew, true);
     }
+}
+
+template <int T, int SCHEME>
+__global__ __launch_bounds__(T) void k_resample_small(const PaRunDesc *__restrict__ runs, int freeze)
+{
+    const PaRunDesc &rd = runs[blockIdx.x];
+    if (!frozen(rd.dv.rec))
+        resample_small_run<T, SCHEME>(rd, rd.dv.rec, freeze);
+}
+
+// The reweighting (of a uniform population) and the resampling of a small run
+// in one launch, for steps that nobody looks into in between: 1024 runs of 2D
+// L = 16, R = 100 5.9 + 9.8 us -> 13.3.
+template <int T, int SCHEME>
+__global__ __launch_bounds__(T) void k_advance_small(const PaRunDesc *__restrict__ runs, double beta_next, int freeze)
+{
+    const PaRunDesc &rd = runs[blockIdx.x];
+    if (frozen(rd.dv.rec))
+        return;
+    reweight_run<T>(rd, rd.dv.rec, beta_next);
+    __syncthreads(); // the record, the level weights and the cleared histogram
+    resample_small_run<T, SCHEME>(rd, rd.dv.rec, freeze);
 }
 
 // ------------------------------------------------------------------ step 4: observables
@@ -3090,6 +3112,37 @@ static hipError_t gather_rest(const PaBatchView &v)
     return hipGetLastError();
 }
 
+// Whether a step's resampling takes one workgroup per run.
+static bool resamples_small(const PaBatchView &v, int scheme, int kq)
+{
+    return v.nlarge == 0 && kq < 0 && scheme >= 1 && scheme <= 3;
+}
+
+template <int T>
+static void advance_small_launch(const PaBatchView &v, double beta_next, int scheme, int freeze)
+{
+    if (scheme == 1)
+        k_advance_small<T, 1><<<v.nruns, T, 0, v.stream>>>(v.runs, beta_next, freeze);
+    else if (scheme == 2)
+        k_advance_small<T, 2><<<v.nruns, T, 0, v.stream>>>(v.runs, beta_next, freeze);
+    else
+        k_advance_small<T, 3><<<v.nruns, T, 0, v.stream>>>(v.runs, beta_next, freeze);
+}
+
+bool pa_advances_at_once(const PaBatchView &v, int scheme) { return resamples_small(v, scheme, -1) && !v.weights; }
+
+hipError_t pa_b_advance(const PaBatchView &v, double beta_next, int hist_state, int scheme, int freeze)
+{
+    hipError_t e = hist_launch(v, hist_state);
+    if (e != hipSuccess)
+        return e;
+    if (v.small_cap <= PA_CHUNK)
+        advance_small_launch<256>(v, beta_next, scheme, freeze);
+    else
+        advance_small_launch<1024>(v, beta_next, scheme, freeze);
+    return gather_rest(v);
+}
+
 template <int T>
 static void resample_small_launch(const PaBatchView &v, int scheme, int freeze)
 {
@@ -3117,7 +3170,7 @@ hipError_t pa_b_resample(const PaBatchView &v, int scheme, int freeze, int kq, b
     hipError_t e;
     if (!prepped)
         k_resample_prep<<<v.nruns, kThreads, 0, v.stream>>>(v.runs);
-    if (v.nlarge == 0 && kq < 0 && scheme >= 1 && scheme <= 3) { // small runs only
+    if (resamples_small(v, scheme, kq)) {
         if (v.small_cap <= PA_CHUNK)
             resample_small_launch<256>(v, scheme, freeze);
         else

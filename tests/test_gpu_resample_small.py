@@ -63,3 +63,35 @@ def test_refused_and_repeated(R, capacity):
             return
         g.close()
     pytest.fail("no seed overflowed the capacity")
+
+
+@pytest.mark.parametrize("scheme", [O.MULTINOMIAL, O.POISSON, O.NEAREST_INT, O.SYSTEMATIC])
+@pytest.mark.parametrize("sizes", [(1, 63, 900), (1000, 40, 2049, 3000)])
+def test_anneal_against_steps(scheme, sizes):
+    """A batch of small runs reweights and resamples in one launch; its runs are
+    those of the step-by-step calls, also through a run that dies out."""
+    from paper_2401_07965_amd import pa
+    betas = [0.0, 0.15, 0.3, 0.32, 0.9]
+    cfgs = [dict(dim=2, L=8, R=r, seed=5, run_id=k) for k, r in enumerate(sizes)]
+    for graph in (False, True):
+        print(f"[resample] batch {sizes} scheme {scheme} graph={graph}", flush=True)
+        B = pa.PABatch(cfgs, max_points=len(betas))
+        for _ in range(2):
+            B.anneal(betas, 2, scheme, use_graph=graph)
+        rec = B.records()
+        for k, c in enumerate(cfgs):
+            g = pa.PARun(**c)
+            for i, b in enumerate(betas[1:], 1):
+                q = g.reweight(b)
+                try:
+                    g.resample(scheme)
+                except pa.ExtinctError:
+                    break
+                g.sweep(2)
+                o = g.observables()
+                assert (rec[k]["lnQ"][i], rec[k]["R"][i], rec[k]["sum_E"][i]) == (q, g.export(arrays=False)["R"], o["sum_E"])
+            else:
+                a, b = B.export_run(k), g.export()
+                assert all(np.array_equal(a[f], b[f]) for f in ("spins", "energy", "magnetization", "label"))
+            g.close()
+        B.close()
