@@ -2849,11 +2849,17 @@ int sweep_waves(size_t lds, int threads)
 }
 
 // Whether the sweeps claim registers for four waves per SIMD (k_sweep4): more
-// than 16 waves to a CU only for workgroups of one or two waves.
+// than 16 waves to a CU only for workgroups of one or two waves, and only
+// where LDS holds at least six waves per SIMD.  With 17 to 23 the SIMDs hold
+// four, five or six of them, and a column on the fullest is late: ten sweeps
+// of 4000 columns of 2D L = 32 (128 lanes, 20 waves) 395 us against 341 with
+// 16, of 8000 of 2D L = 24 (64 lanes, 18 waves) 498 against 419, of 5000 of 3D
+// L = 8 (64 lanes, 18 waves) 287 against 254.  From 24 on k_sweep is the
+// faster: 2D L = 16 (64 lanes, 27) 0 to 3 %, 2D L = 8 (128 lanes, 40) 8 %.
 bool sweep_four(size_t lds, int threads)
 {
     const int w = threads / 64, blocks = (int)(kLdsPerCu / lds);
-    return w > 2 || blocks * w <= kWavesPerCu;
+    return w > 2 || blocks * w < 24;
 }
 
 // The walk a sweep of this shape takes: coordinates that stay from pass to

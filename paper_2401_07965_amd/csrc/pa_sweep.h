@@ -1109,9 +1109,8 @@ __device__ __forceinline__ void sweep_column(const PaRunDesc *__restrict__ runs,
 // 7 (2D) waves per SIMD.  Where LDS holds fewer workgroups than that, they
 // spread unevenly over the SIMDs (3D L = 10: 8 workgroups of two waves per CU
 // ran 6 % slower than with at most four waves to a SIMD), so k_sweep4 claims
-// registers for four; k_sweep runs where LDS lets more than 16 waves of one or
-// two-wave workgroups share a CU (3D L = 8 5 % faster than with four to a
-// SIMD, 2D L = 16 5 %).
+// registers for four; k_sweep runs where LDS lets 24 or more waves of one or
+// two-wave workgroups share a CU (sweep_four).
 template <int D, bool J>
 __global__ __launch_bounds__(kSweepMaxThreads) void k_sweep(const PaRunDesc *__restrict__ runs,
                                                             const PaBlk *__restrict__ map, int theta, uint32_t t0,
