@@ -93,96 +93,90 @@ bool sweep_threads_ok(int N, int d, int t)
     return t >= 64 && t <= kSweepMaxLanes && t % 64 == 0 && (int64_t)((N + t - 1) / t) * d <= 255;
 }
 
-constexpr int kLdsPerCu = 163840; // gfx950: 160 KiB of LDS per CU
+constexpr int kLdsPerCu = 163840, kCus = 256; // gfx950: 160 KiB of LDS per CU, 256 CUs
 
 // Modelled time (cycles) of one colour's updates over all columns of a batch
 // with t lanes per column: rounds of as many columns as a CU holds, then what
 // is left.  A column's colour takes passes over its sites, each the longer of
-// one wave's latency (1500 cycles) and its SIMD's waves taking turns (1200
-// cycles a wave, 2 % more with coordinates computed at each site), and an end
-// (60 cycles, 900 per wave and SIMD, 70 per wave of the workgroup).  Waves
-// spread evenly over the SIMDs only in workgroups of four or eight; others can
-// meet on one, those of 3, 5, 6 ... waves leave SIMDs idle (40 %), and those of
-// two, where five share a SIMD, gain less than their number (3 %).
-// Fitted to the times of all sizes on 945 shapes, numbers of columns above 512,
-// sweeps a launch (2 and 10) and temperatures.
+// one wave's latency (1200 cycles) and its SIMD's waves taking turns (1200
+// cycles a wave), and an end (250 cycles, 850 per wave and SIMD, 70 per wave
+// of the workgroup).  Waves spread evenly over the SIMDs only in workgroups of
+// four or eight; others can meet on one, those of 3, 5, 6 ... waves leave SIMDs
+// idle (40 %), and those of two, where more than four share a SIMD, gain less
+// than their number (7 %).
 double colour_cycles(int N, int d, int t, bool J, int64_t columns)
 {
-    constexpr int kCus = 256;
     const int w = t / 64, cap = pa_sweep_waves_cap(N, d, t, J);
     int blocks = (int)((size_t)kLdsPerCu / pa_sweep_lds_bytes(N, d, t, J));
     blocks = std::min(blocks, cap / w);
     if (blocks < 1)
         return HUGE_VAL;
-    const double uneven = w > 2 && w % 4 ? 1.4 : w == 2 && cap > 16 ? 1.03 : 1.0;
-    const double issue = 1200.0 * (pa_sweep_walk(N, d, t, J) == 0 ? 1.02 : 1.0) * uneven;
+    const double uneven = w > 2 && w % 4 ? 1.4 : w == 2 && cap > 16 ? 1.07 : 1.0;
     const double passes = std::max(1.0, (double)((N / 2 + 63) / 64 * 64) / t);
     auto together = [&](int b) { // b columns on each CU
-        const double ws = w % 4 == 0 ? b * w / 4.0 : std::min(cap / 4.0, b * w / 4.0 + 0.7);
-        return passes * std::hypot(1500.0, issue * ws) + 60.0 + 900.0 * ws + 70.0 * w;
+        const double ws = w % 4 == 0 ? b * w / 4.0 : std::min(cap / 4.0, b * w / 4.0 + 0.72);
+        return passes * std::hypot(1200.0, 1200.0 * uneven * ws) + 250.0 + 850.0 * ws + 70.0 * w;
     };
     const int64_t round = (int64_t)kCus * blocks, left = columns % round;
     return (double)(columns / round) * together(blocks) + (left ? together((int)((left + kCus - 1) / kCus)) : 0.0);
 }
 
-// Default sweep workgroup size: the smallest within 2 % of the least modelled
-// time.  On the shapes it was fitted to it loses 0.6 % on average against the
-// best of all sizes, 15 % at most; by the waves a CU holds, as it was chosen
-// before, 6.9 % and 52 %: ten sweeps at 3D L = 12 took 922 us with 128 lanes,
-// 790 with 256 (4688 columns), 3D L = 14 997 with 192, 829 with 256 (3125), 2D
-// L = 48 707 with 128, 595 with 256 (3125).  Autotuning refines it for batches.
-int default_sweep_threads(int N, int d, bool J, int64_t columns)
+// The same where a CU has at most two columns: they run in step, so that a
+// colour takes whole passes (the longer of 2100 cycles of latency and 1160 a
+// wave) and every SIMD waits for the one with the most waves (an end of 2500
+// cycles and 600 per wave; two workgroups of waves that do not fill the SIMDs
+// evenly put one more on it); two columns that the CU cannot hold together
+// run one after the other.
+double few_columns_cycles(int N, int d, int t, bool J, int64_t columns)
 {
-    const size_t lds_max = (size_t)(g_max_lds ? g_max_lds : kLdsPerCu);
-    double cycles[13], least = HUGE_VAL;
-    for (int t = 64; t <= 768; t += 64) {
-        const bool ok = sweep_threads_ok(N, d, t) && pa_sweep_lds_bytes(N, d, t, J) <= lds_max;
-        cycles[t / 64] = ok ? colour_cycles(N, d, t, J, columns) : HUGE_VAL;
-        least = std::min(least, cycles[t / 64]);
+    constexpr int kWaves = 16;
+    const int w = t / 64, per_cu = (int)((columns + kCus - 1) / kCus), passes = (N / 2 + t - 1) / t;
+    const int fit = std::min((int)((size_t)kLdsPerCu / pa_sweep_lds_bytes(N, d, t, J)), kWaves / w);
+    if (fit < 1)
+        return HUGE_VAL;
+    double cycles = 0.0;
+    for (int left = per_cu; left > 0; left -= fit) {
+        const int b = std::min(left, fit);
+        const double ws = std::min((b * w + 3) / 4 + (w % 4 ? b - 1 : 0), kWaves / 4);
+        cycles += passes * std::hypot(2100.0, 1160.0 * ws) + 2500.0 + 600.0 * ws;
     }
-    for (int t = 64; t <= 768 && least < HUGE_VAL; t += 64)
-        if (cycles[t / 64] <= 1.02 * least)
-            return t;
-    return 768; // none fits: rejected by the LDS check of the batch set-up
+    return cycles;
 }
 
-// Default size where the batch's columns leave the chip short of workgroups
-// (at most two columns per CU): a column then has a CU's waves nearly to
-// itself, and more lanes per column finish it sooner, until its waves (or the
-// two columns' together) fill the SIMDs.  The size with the least modelled
-// time of a colour: rounds of sites, each the longer of one wave's latency
-// (1800 cycles for a site pass) and its SIMD's waves taking turns (1160 cycles
-// a wave), and the end of the colour (2500 cycles, 600 per wave and SIMD).
-// Measured, theta = 10, R = 2 10^4 (313 columns): 3D L = 16 227 -> 208 us, 3D
-// L = 10 130 -> 88, 2D L = 32 111 -> 74, 2D L = 24 glass 100 -> 71.
-int few_columns_threads(int N, int d, bool J, int64_t columns)
+} // namespace
+
+// Default sweep workgroup size in a batch of `columns` 64-replica columns: the
+// least modelled time; of equal ones the smallest that takes a colour's sites
+// in one pass, else the largest (its last pass is the emptier).  The two models
+// were fitted to the times of all sizes on 4798 shapes (lattices of 16 to 16384
+// sites, 1 to 20000 columns; 1, 2 and 10 sweeps a launch).  There the rule loses 0.9 % on average
+// against the best size, and 18 % at most (launches of one or two sweeps, whose
+// fixed costs the models do not count: one sweep of 900 columns of 3D L = 8
+// 19.4 us at the 256 lanes it takes, 16.5 at 128).  The size with the most busy
+// lanes among the waves a CU holds loses 18 % on average and 162 % at most; the
+// first model alone up to 23 % (below two columns per CU).
+// Ten sweeps of 313 columns of 2D L = 32 71 us at 256 lanes against 106 at 128,
+// of 2D L = 96 395 at 768 against 799 at 128; of 4200 columns of 3D L = 12 699
+// at 256 against 830 at 128.  Autotuning refines it for batches.
+int pa_default_sweep_threads(int N, int d, bool J, int64_t columns)
 {
-    constexpr int kCus = 256, kWaves = 16;
-    const int lds_max = g_max_lds ? g_max_lds : kLdsPerCu;
-    const int per_cu = (int)((columns + kCus - 1) / kCus), nh = N / 2;
-    int best = 0;
-    double best_t = 0.0;
+    const size_t lds_max = (size_t)(g_max_lds ? g_max_lds : kLdsPerCu);
+    double least = HUGE_VAL;
+    int best = 768; // none fits: rejected by the LDS check of the batch set-up
     for (int t = 64; t <= 768; t += 64) {
-        const size_t lds = pa_sweep_lds_bytes(N, d, t, J);
-        const int waves = per_cu * (t / 64);
-        if (!sweep_threads_ok(N, d, t) || lds > (size_t)lds_max || lds * per_cu > (size_t)kLdsPerCu || waves > kWaves)
+        if (!sweep_threads_ok(N, d, t) || pa_sweep_lds_bytes(N, d, t, J) > lds_max)
             continue;
-        const double ws = (waves + 3) / 4, passes = (nh + t - 1) / t;
-        const double time = passes * std::hypot(1800.0, 1160.0 * ws) + 2500.0 + 600.0 * ws;
-        if (!best || time < best_t - 1e-9) {
-            best_t = time;
+        const double cycles =
+            columns <= 2 * kCus ? few_columns_cycles(N, d, t, J, columns) : colour_cycles(N, d, t, J, columns);
+        if (cycles < least || (cycles == least && N / 2 > best)) {
+            least = cycles;
             best = t;
         }
     }
     return best;
 }
 
-// Default sweep workgroup size of a group in a batch of `columns` 64-replica columns.
-int group_sweep_threads(int N, int d, bool J, int64_t columns)
-{
-    const int few = columns <= 2 * 256 ? few_columns_threads(N, d, J, columns) : 0;
-    return few ? few : default_sweep_threads(N, d, J, columns);
-}
+namespace {
 
 uint64_t round256(uint64_t b) { return (b + 255) / 256 * 256; }
 
@@ -459,7 +453,7 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
             tb.gd.push_back(g.d);
             tb.gN.push_back(g.N);
             tb.gJ.push_back(g.J);
-            tb.gthreads.push_back(group_sweep_threads(g.N, g.d, g.J != 0, columns));
+            tb.gthreads.push_back(pa_default_sweep_threads(g.N, g.d, g.J != 0, columns));
         }
         for (int64_t w = 0; w < g.W; ++w)
             tb.gcol[it->second].push_back({(uint32_t)m, (uint32_t)w});
@@ -627,7 +621,7 @@ pa_status make_batch(const pa_config *cfgs, int32_t nruns, int32_t max_points, v
     if (g_max_lds == 0 && (e = pa_query_lds(&g_max_lds)) != hipSuccess)
         return hip_fail(nullptr, e, "device query");
     for (const Geometry &g : geo)
-        if (pa_sweep_lds_bytes(g.N, g.d, default_sweep_threads(g.N, g.d, g.J != 0, 1 << 20), g.J != 0) >
+        if (pa_sweep_lds_bytes(g.N, g.d, pa_default_sweep_threads(g.N, g.d, g.J != 0, 1 << 20), g.J != 0) >
                 (size_t)g_max_lds ||
             (size_t)g.H * 4 > (size_t)g_max_lds)
             return fail(nullptr, PA_E_INVAL, "lattice too large for the workgroup LDS of this device");

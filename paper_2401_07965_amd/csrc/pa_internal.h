@@ -255,5 +255,6 @@ hipError_t pa_query_lds(int *max_lds);
 size_t pa_sweep_lds_bytes(int N, int d, int threads, bool J); // dynamic LDS of a sweep workgroup (J: bond masks)
 int pa_sweep_walk(int N, int d, int threads, bool J);      // 0 coordinates at each site, 1 site table, 2 or 3 fixed axis
 int pa_sweep_waves_cap(int N, int d, int threads, bool J); // most sweep waves on a CU (registers)
+int pa_default_sweep_threads(int N, int d, bool J, int64_t columns); // default sweep workgroup size (pa_api.cpp)
 size_t pa_cluster_lds_bytes(int N, bool J);                   // dynamic LDS of a cluster-update workgroup
 hipError_t pa_b_cluster(const PaBatchView &v, int nsteps, uint32_t t0); // Wolff updates of every run
