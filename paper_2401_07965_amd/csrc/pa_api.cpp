@@ -178,7 +178,8 @@ int pa_default_sweep_threads(int N, int d, bool J, int64_t columns)
 
 namespace {
 
-uint64_t round256(uint64_t b) { return (b + 255) / 256 * 256; }
+constexpr uint64_t round256(uint64_t b) { return (b + 255) / 256 * 256; }
+constexpr uint64_t kRecordBytes = round256(sizeof(PaRecord));
 
 // Buffers of one run (base may be null to only measure them).
 uint64_t carve_run(const Geometry &g, char *base, PaDev *dv)
@@ -209,13 +210,14 @@ uint64_t carve_run(const Geometry &g, char *base, PaDev *dv)
     d.qhist = (unsigned long long *)take((uint64_t)(g.N + 1) * 8);
     // tile flags of the two prefix sums of a resampling (weights, copy numbers)
     d.tiles = (PaScanTile *)take((uint64_t)(2 * pa_tiles_per_sum(g.cap)) * sizeof(PaScanTile));
-    d.calls = (unsigned long long *)take((uint64_t)g.W * 8);
     d.partial = (double *)take(chunks * 8);
     d.fam = (uint32_t *)take((uint64_t)g.R * 4);
     d.lw = (double *)take(slots * 8);
     d.Wj = (uint64_t *)take(slots * 8);
     d.wpart = (double *)take(chunks * PA_WPARTS * 8);
-    d.rec = (PaRecord *)take(sizeof(PaRecord));
+    char *rec = take(kRecordBytes + PA_CALL_SLOTS * 8); // the counters behind the record: one copy reads both
+    d.rec = (PaRecord *)rec;
+    d.calls = rec ? (unsigned long long *)(rec + kRecordBytes) : nullptr;
     if (dv)
         *dv = d;
     return off;
@@ -636,8 +638,8 @@ pa_status make_batch(const pa_config *cfgs, int32_t nruns, int32_t max_points, v
         b->hdesc[m].run_id = cfgs[m].run_id;
     }
     b->v.stream = (hipStream_t)stream;
-    if ((e = hipHostMalloc((void **)&b->hrec, sizeof(PaRecord) * (size_t)nruns, hipHostMallocDefault)) !=
-        hipSuccess)
+    const size_t hbytes = std::max(sizeof(PaRecord) * (size_t)nruns, (size_t)(kRecordBytes + PA_CALL_SLOTS * 8));
+    if ((e = hipHostMalloc((void **)&b->hrec, hbytes, hipHostMallocDefault)) != hipSuccess)
         return hip_fail(nullptr, e, "pinned records");
     if (b->v.ngroups > 1) { // side streams (default priority) and events for the groups' sweeps
         e = hipEventCreateWithFlags(&b->v.fork, hipEventDisableTiming);
@@ -683,13 +685,12 @@ pa_status make_batch(const pa_config *cfgs, int32_t nruns, int32_t max_points, v
     return PA_OK;
 }
 
-// Run m's record once the batch's stream has drained (one copy: reading one
+// Run m's record (its first `bytes`) once the batch's stream has drained (one copy: reading one
 // run of a batch fetched every run's record, 1024 copies of 1.8 us each and
 // their launches for a batch of 1024).
-pa_status fetch_record(Batch *b, int m, const char *where)
+pa_status fetch_record(Batch *b, int m, const char *where, size_t bytes = sizeof(PaRecord))
 {
-    hipError_t e =
-        hipMemcpyAsync(b->hrec + m, b->hdesc[m].dv.rec, sizeof(PaRecord), hipMemcpyDeviceToHost, b->v.stream);
+    hipError_t e = hipMemcpyAsync(b->hrec + m, b->hdesc[m].dv.rec, bytes, hipMemcpyDeviceToHost, b->v.stream);
     if (e == hipSuccess)
         e = hipStreamSynchronize(b->v.stream);
     if (e != hipSuccess)
@@ -712,9 +713,9 @@ pa_status status_error(Batch *b, uint32_t st)
 
 // Records of a single run once its stream has drained.  A run frozen by a
 // deferred pa_resample reports the failure that froze it.
-pa_status ctx_records(Batch *b, const char *where)
+pa_status ctx_records(Batch *b, const char *where, size_t bytes = sizeof(PaRecord))
 {
-    pa_status s = fetch_record(b, 0, where);
+    pa_status s = fetch_record(b, 0, where, bytes);
     if (s != PA_OK)
         return s;
     if (b->hrec[0].status & PA_ST_FROZEN)
@@ -1233,13 +1234,13 @@ pa_status pa_get_counters(pa_ctx *c, pa_counters *out)
     Batch *b = &c->b;
     if (!out)
         return fail(b, PA_E_INVAL, "out is NULL");
-    const hipError_t e = pa_b_counters(b->v);
-    if (e != hipSuccess)
-        return hip_fail(b, e, "pa_get_counters");
-    pa_status s = ctx_records(b, "pa_get_counters");
+    pa_status s = ctx_records(b, "pa_get_counters", kRecordBytes + PA_CALL_SLOTS * 8);
     if (s != PA_OK)
         return s;
-    out->philox_calls = b->hrec[0].philox_calls;
+    const unsigned long long *calls = (const unsigned long long *)((const char *)b->hrec + kRecordBytes);
+    out->philox_calls = 0;
+    for (int k = 0; k < PA_CALL_SLOTS; ++k)
+        out->philox_calls += calls[k];
     out->site_updates = b->hrec[0].site_updates;
     out->sweeps = b->sweeps_total;
     out->spin_attempts = b->hrec[0].attempts;

@@ -56,7 +56,6 @@ struct PaRecord {
     float feat[8];                 // inputs of the learned step model
     double cand_dbeta;             // the model's proposal
     uint32_t fallback, pad1;       // 1: the proposal failed the overlap check
-    unsigned long long philox_calls; // Philox4x32-10 evaluations of all sweeps so far (summed by pa_b_counters)
     unsigned long long site_updates; // word-site updates (64 attempts each) so far
     unsigned long long attempts;     // spin-flip attempts so far: theta N R per sweep call
     uint32_t ticket[2];              // tile tickets of the two prefix sums of a resampling
@@ -95,6 +94,13 @@ struct PaScanTile {
 
 #define PA_SMALL_CAP 4096 // capacity of the runs whose passes over replicas one workgroup takes
 
+// Counters that a run's Philox evaluations are spread over; pa_get_counters adds
+// them up.  Columns that end together meet on one address in PA_CALL_SLOTS, and
+// neighbouring ones on different cache lines (atomics on one counter took 12 to
+// 14 ns each, one after the other).
+#define PA_CALL_SLOTS 256
+__host__ __device__ inline uint32_t pa_call_slot(uint32_t column) { return ((column & 15u) << 4) | ((column >> 4) & 15u); }
+
 // Tile flags of a run's two prefix sums of a resampling (weights, copy
 // numbers): ceil(cap / PA_CHUNK) each, enough for tiles of PA_CHUNK or more
 // slots.
@@ -121,7 +127,7 @@ struct PaDev {
     uint64_t *C;
     unsigned long long *qhist; // [N+1] overlap histogram
     PaScanTile *tiles;
-    unsigned long long *calls; // [W] Philox evaluations of each column's sweeps so far
+    unsigned long long *calls; // [PA_CALL_SLOTS] right behind the record: Philox4x32-10 evaluations of all sweeps so far
     double *partial; // fixed-order partial sums, one per chunk
     uint32_t *fam;   // [R0] replicas per family
     double *lw;      // [slots] log-weights of a weighted population
@@ -213,7 +219,6 @@ hipError_t pa_b_init(const PaBatchView &v);
 // t0: sweeps already done at this beta; gather: the populations' spins may
 // still be in the other buffer (PaRecord::gather), taken in by the sweep
 hipError_t pa_b_sweep(const PaBatchView &v, int theta, uint32_t t0, int gather);
-hipError_t pa_b_counters(const PaBatchView &v); // sums the columns' Philox evaluations into the records
 hipError_t pa_b_gather(const PaBatchView &v); // gathers the spins a resampling left for the sweeps to gather
 hipError_t pa_b_sweep_group(const PaBatchView &v, int g, int theta, int threads);
 // hist_clean: the level histogram is zero (observables or init ran since it was last built)

@@ -38,6 +38,8 @@ int grid_for(int64_t n, int threads = kThreads, int cap = 4096)
 __global__ void k_init_rec(const PaRunDesc *__restrict__ runs)
 {
     const PaRunDesc &rd = runs[blockIdx.x];
+    for (int k = threadIdx.x; k < PA_CALL_SLOTS; k += blockDim.x)
+        rd.dv.calls[k] = 0;
     if (threadIdx.x != 0)
         return;
     PaRecord *rec = rd.dv.rec;
@@ -54,7 +56,6 @@ __global__ void k_init_rec(const PaRunDesc *__restrict__ runs)
     rec->sv = 0.0;
     for (int k = 0; k < 3; ++k)
         rec->T[k] = rec->Tn[k] = 1ull << 32;
-    rec->philox_calls = 0;
     rec->site_updates = 0;
     rec->attempts = 0;
     rec->accE = rec->accE2 = rec->accAbsM = rec->accM2 = rec->accC2 = rec->accFam = 0;
@@ -82,21 +83,6 @@ __global__ __launch_bounds__(kThreads) void k_sites(const PaRunDesc *__restrict_
     }
 }
 
-// A run's Philox evaluations: its columns' counts (each written by its column's
-// workgroup alone).
-__global__ __launch_bounds__(kThreads) void k_sum_calls(const PaRunDesc *__restrict__ runs)
-{
-    __shared__ uint64_t su[16];
-    const PaRunDesc &rd = runs[blockIdx.x];
-    const int64_t W = (rd.cap + 63) / 64;
-    uint64_t n = 0;
-    for (int64_t w = threadIdx.x; w < W; w += blockDim.x)
-        n += rd.dv.calls[w];
-    n = pa_block_sum_u64(n, su);
-    if (threadIdx.x == 0)
-        rd.dv.rec->philox_calls = n;
-}
-
 // Replica 64w+b, site s: bit b of x0 | x1<<32 of Philox(s, w, 0, INIT<<28).
 __global__ __launch_bounds__(kThreads) void k_init_spins(const PaRunDesc *__restrict__ runs,
                                                          const PaBlk *__restrict__ map)
@@ -104,8 +90,6 @@ __global__ __launch_bounds__(kThreads) void k_init_spins(const PaRunDesc *__rest
     const PaBlk b = map[blockIdx.x];
     const PaRunDesc &rd = runs[b.run];
     const uint32_t w = b.idx;
-    if (threadIdx.x == 0)
-        rd.dv.calls[w] = 0;
     if ((int64_t)w * 64 >= rd.R0)
         return;
     uint64_t *g = rd.dv.spins[0] + (size_t)w * rd.N;
@@ -3010,12 +2994,6 @@ hipError_t pa_b_init(const PaBatchView &v)
 hipError_t pa_b_sweep_group(const PaBatchView &v, int g, int theta, int threads)
 {
     return sweep_launch(v, g, theta, threads, 0u, v.stream, 0);
-}
-
-hipError_t pa_b_counters(const PaBatchView &v)
-{
-    k_sum_calls<<<v.nruns, kThreads, 0, v.stream>>>(v.runs);
-    return hipGetLastError();
 }
 
 hipError_t pa_b_gather(const PaBatchView &v)

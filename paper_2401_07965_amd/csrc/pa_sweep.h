@@ -416,9 +416,10 @@ __device__ __forceinline__ void wave_count2(const uint64_t (&a)[8], const uint64
 // writes the lattice back to g.  Per-lane counts stay below 2^8: at most
 // ceil(N / blockDim) sites per lane, d bonds each (the launch checks).
 // jbits(t, x, y, z): site t's bond bits (bit mu: to s + e_mu).
-// calls: the wave's Philox evaluations, added to the column's count here: an
-// atomic per wave on the run's record (and one per workgroup for the updates)
-// took 12 to 14 ns each, one after the other, and held the launch's end back:
+// calls: the wave's Philox evaluations; the workgroup's are added to one of the
+// run's counters here (PA_CALL_SLOTS).  An atomic per wave on the run's record
+// (and one per workgroup for the updates) took 12 to 14 ns each, one after the
+// other, and held the launch's end back:
 // two sweeps of 6200 columns of 2D L = 24 257 -> 106 us (128 lanes), of 4000 of
 // 3D L = 8 121 -> 55 (64 lanes), of 1536 of 3D L = 16 155 -> 135 (256).
 template <int D, bool J, typename JBits>
@@ -486,7 +487,7 @@ __device__ __forceinline__ void recount_column(const uint64_t *lat, JBits jbits,
             for (int v = 1; v < nw; ++v)
                 calls += red[v * 32 + 7];
             if (calls)
-                rd.dv.calls[w] += calls;
+                atomicAdd(&rd.dv.calls[pa_call_slot(w)], (unsigned long long)calls);
         }
         const uint32_t *p = red32 + (lane >> 5) * 16; // this replica's half
         const uint32_t bit = (uint32_t)lane & 31u;
