@@ -403,7 +403,7 @@ pa_status hip_fail(Batch *b, hipError_t e, const char *where)
 // Whole layout of a batch: tables first, then each run's buffers.
 struct Tables {
     std::vector<uint32_t> list; // run indices, the large runs first
-    std::vector<PaBlk> rep, hrep, crep, fam, col, tile;
+    std::vector<PaBlk> rep, crep, fam, col, tile;
     std::vector<std::vector<PaBlk>> gcol;
     std::vector<int> gd, gN, gJ, gthreads;
 };
@@ -421,16 +421,14 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
         for (int m = 0; m < M; ++m)
             if ((geo[m].cap <= PA_SMALL_CAP) == (small != 0))
                 tb.list.push_back((uint32_t)m);
-    uint32_t nlarge = 0, nhrep_large = 0, nfam_large = 0;
+    uint32_t nlarge = 0, ncrep_large = 0, nfam_large = 0;
     int64_t small_cap = 0;
     for (const uint32_t m : tb.list) {
         const Geometry &g = geo[m];
         for (int64_t c = 0; c < (g.cap + PA_CHUNK - 1) / PA_CHUNK; ++c)
             tb.rep.push_back({(uint32_t)m, (uint32_t)c});
-        for (int64_t c = 0; c < (g.cap + pa_counts_tile(g.cap) - 1) / pa_counts_tile(g.cap); ++c) {
-            tb.hrep.push_back({(uint32_t)m, (uint32_t)c});
+        for (int64_t c = 0; c < (g.cap + pa_counts_tile(g.cap) - 1) / pa_counts_tile(g.cap); ++c)
             tb.crep.push_back({(uint32_t)m, (uint32_t)c});
-        }
         for (int64_t c = 0; c < (g.R + PA_HCHUNK - 1) / PA_HCHUNK; ++c)
             tb.fam.push_back({(uint32_t)m, (uint32_t)c});
         for (int64_t w = 0; w < g.W; ++w)
@@ -439,7 +437,7 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
             tb.tile.push_back({(uint32_t)m, (uint32_t)k});
         if (g.cap > PA_SMALL_CAP) {
             ++nlarge;
-            nhrep_large = (uint32_t)tb.hrep.size();
+            ncrep_large = (uint32_t)tb.crep.size();
             nfam_large = (uint32_t)tb.fam.size();
         } else {
             small_cap = std::max(small_cap, g.cap);
@@ -469,7 +467,6 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
     char *p_desc = take(sizeof(PaRunDesc) * (uint64_t)M);
     char *p_list = take(sizeof(uint32_t) * tb.list.size());
     char *p_rep = take(sizeof(PaBlk) * tb.rep.size());
-    char *p_hrep = take(sizeof(PaBlk) * tb.hrep.size());
     char *p_crep = take(sizeof(PaBlk) * tb.crep.size());
     char *p_fam = take(sizeof(PaBlk) * tb.fam.size());
     char *p_col = take(sizeof(PaBlk) * tb.col.size());
@@ -510,13 +507,11 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
         v.nruns = (uint32_t)M;
         v.list = (const uint32_t *)p_list;
         v.nlarge = nlarge;
-        v.nhrep_large = nhrep_large;
+        v.ncrep_large = ncrep_large;
         v.nfam_large = nfam_large;
         v.small_cap = small_cap;
         v.rep = (const PaBlk *)p_rep;
         v.nrep = (uint32_t)tb.rep.size();
-        v.hrep = (const PaBlk *)p_hrep;
-        v.nhrep = (uint32_t)tb.hrep.size();
         v.crep = (const PaBlk *)p_crep;
         v.ncrep = (uint32_t)tb.crep.size();
         v.fam = (const PaBlk *)p_fam;
@@ -662,7 +657,6 @@ pa_status make_batch(const pa_config *cfgs, int32_t nruns, int32_t max_points, v
     up(b->ddesc, b->hdesc.data(), sizeof(PaRunDesc) * nruns);
     up(b->v.list, t.list.data(), sizeof(uint32_t) * t.list.size());
     up(b->v.rep, t.rep.data(), sizeof(PaBlk) * t.rep.size());
-    up(b->v.hrep, t.hrep.data(), sizeof(PaBlk) * t.hrep.size());
     up(b->v.crep, t.crep.data(), sizeof(PaBlk) * t.crep.size());
     up(b->v.fam, t.fam.data(), sizeof(PaBlk) * t.fam.size());
     up(b->v.col, t.col.data(), sizeof(PaBlk) * t.col.size());

@@ -183,13 +183,11 @@ struct PaBatchView {
     const PaRunDesc *runs; // [nruns]
     uint32_t nruns;
     const uint32_t *list;  // [nruns] run indices, the large runs first
-    uint32_t nlarge, nhrep_large, nfam_large;
+    uint32_t nlarge, ncrep_large, nfam_large;
     int64_t small_cap; // largest capacity of the small runs
     const PaBlk *rep;  // chunks of PA_CHUNK replica slots (capacity)
     uint32_t nrep;
-    const PaBlk *hrep; // chunks of pa_counts_tile replica slots (histogram, observables)
-    uint32_t nhrep;
-    const PaBlk *crep; // tiles of the copy-number pass (pa_counts_tile slots)
+    const PaBlk *crep; // tiles of pa_counts_tile replica slots (histogram, observables, copy numbers)
     uint32_t ncrep;
     const PaBlk *fam;  // chunks of PA_HCHUNK families
     uint32_t nfam;
