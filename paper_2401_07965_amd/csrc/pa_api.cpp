@@ -402,7 +402,7 @@ pa_status hip_fail(Batch *b, hipError_t e, const char *where)
 
 // Whole layout of a batch: tables first, then each run's buffers.
 struct Tables {
-    std::vector<uint32_t> list; // run indices, the large runs first
+    std::vector<uint32_t> list; // run indices: large, middle, tiny runs
     std::vector<PaBlk> rep, crep, fam, col, tile;
     std::vector<std::vector<PaBlk>> gcol;
     std::vector<int> gd, gN, gJ, gthreads;
@@ -417,12 +417,11 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
     int64_t columns = 0; // of all runs at their target sizes
     for (const Geometry &g : geo)
         columns += (g.R + 63) / 64;
-    for (int small = 0; small < 2; ++small)
+    for (int cls = 0; cls < 3; ++cls)
         for (int m = 0; m < M; ++m)
-            if ((geo[m].cap <= PA_SMALL_CAP) == (small != 0))
+            if ((geo[m].cap > PA_SMALL_CAP ? 0 : geo[m].cap > PA_CHUNK ? 1 : 2) == cls)
                 tb.list.push_back((uint32_t)m);
-    uint32_t nlarge = 0, ncrep_large = 0, nfam_large = 0;
-    int64_t small_cap = 0;
+    uint32_t nlarge = 0, nmid = 0, ncrep_large = 0, nfam_large = 0;
     for (const uint32_t m : tb.list) {
         const Geometry &g = geo[m];
         for (int64_t c = 0; c < (g.cap + PA_CHUNK - 1) / PA_CHUNK; ++c)
@@ -439,8 +438,8 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
             ++nlarge;
             ncrep_large = (uint32_t)tb.crep.size();
             nfam_large = (uint32_t)tb.fam.size();
-        } else {
-            small_cap = std::max(small_cap, g.cap);
+        } else if (g.cap > PA_CHUNK) {
+            ++nmid;
         }
     }
     for (int m = 0; m < M; ++m) { // groups and their columns in run order
@@ -509,7 +508,7 @@ uint64_t layout(const std::vector<Geometry> &geo, int max_points, char *base, Ba
         v.nlarge = nlarge;
         v.ncrep_large = ncrep_large;
         v.nfam_large = nfam_large;
-        v.small_cap = small_cap;
+        v.nmid = nmid;
         v.rep = (const PaBlk *)p_rep;
         v.nrep = (uint32_t)tb.rep.size();
         v.crep = (const PaBlk *)p_crep;

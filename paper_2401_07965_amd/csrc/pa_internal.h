@@ -178,13 +178,13 @@ struct PaMlpDev {
 
 // What the launchers need to address a batch (device pointers + counts).
 // Every block map lists the blocks of the large runs (capacity above
-// PA_SMALL_CAP) first; the counts *_large are theirs.
+// PA_SMALL_CAP) first; the counts *_large are theirs.  Of the others those above
+// PA_CHUNK come first (nmid of them), then the tiny ones.
 struct PaBatchView {
     const PaRunDesc *runs; // [nruns]
     uint32_t nruns;
-    const uint32_t *list;  // [nruns] run indices, the large runs first
-    uint32_t nlarge, ncrep_large, nfam_large;
-    int64_t small_cap; // largest capacity of the small runs
+    const uint32_t *list;  // [nruns] run indices: large, middle, tiny
+    uint32_t nlarge, nmid, ncrep_large, nfam_large;
     const PaBlk *rep;  // chunks of PA_CHUNK replica slots (capacity)
     uint32_t nrep;
     const PaBlk *crep; // tiles of pa_counts_tile replica slots (histogram, observables, copy numbers)

@@ -2106,9 +2106,10 @@ __device__ __forceinline__ void resample_small_run(const PaRunDesc &rd, PaRecord
 }
 
 template <int T, int SCHEME>
-__global__ __launch_bounds__(T) void k_resample_small(const PaRunDesc *__restrict__ runs, int freeze)
+__global__ __launch_bounds__(T) void k_resample_small(const PaRunDesc *__restrict__ runs,
+                                                      const uint32_t *__restrict__ list, int freeze)
 {
-    const PaRunDesc &rd = runs[blockIdx.x];
+    const PaRunDesc &rd = runs[list[blockIdx.x]];
     if (!frozen(rd.dv.rec))
         resample_small_run<T, SCHEME>(rd, rd.dv.rec, freeze);
 }
@@ -2117,9 +2118,10 @@ __global__ __launch_bounds__(T) void k_resample_small(const PaRunDesc *__restric
 // in one launch, for steps that nobody looks into in between: 1024 runs of 2D
 // L = 16, R = 100 5.9 + 9.8 us -> 13.3.
 template <int T, int SCHEME>
-__global__ __launch_bounds__(T) void k_advance_small(const PaRunDesc *__restrict__ runs, double beta_next, int freeze)
+__global__ __launch_bounds__(T) void k_advance_small(const PaRunDesc *__restrict__ runs,
+                                                     const uint32_t *__restrict__ list, double beta_next, int freeze)
 {
-    const PaRunDesc &rd = runs[blockIdx.x];
+    const PaRunDesc &rd = runs[list[blockIdx.x]];
     if (frozen(rd.dv.rec))
         return;
     reweight_run<T>(rd, rd.dv.rec, beta_next);
@@ -3125,15 +3127,27 @@ static bool resamples_small(const PaBatchView &v, int scheme, int kq)
     return v.nlarge == 0 && kq < 0 && scheme >= 1 && scheme <= 3;
 }
 
-template <int T>
-static void advance_small_launch(const PaBatchView &v, double beta_next, int scheme, int freeze)
+// Calls f(lanes, runs, n) for the small runs: workgroups of 1024 lanes, or of
+// 256 where every run is tiny.  Where tiny runs outnumber the CUs and all
+// small runs are more than two to a CU (what 1024-lane workgroups fill), the
+// middle and the tiny ones start apart: 1024 lanes for a tiny run leave most
+// idle but take their place.  2D L = 8, R = 100 with one run of R = 2000, a step:
+// 4001 runs 327 us in one launch each, 153 in two, 1001 runs 94 and 68, 501
+// runs 59 and 59, 301 runs 55 and 59.
+constexpr uint32_t kSplitTiny = 256, kSplitAll = 512;
+template <typename F>
+static void small_launches(const PaBatchView &v, F f)
 {
-    if (scheme == 1)
-        k_advance_small<T, 1><<<v.nruns, T, 0, v.stream>>>(v.runs, beta_next, freeze);
-    else if (scheme == 2)
-        k_advance_small<T, 2><<<v.nruns, T, 0, v.stream>>>(v.runs, beta_next, freeze);
-    else
-        k_advance_small<T, 3><<<v.nruns, T, 0, v.stream>>>(v.runs, beta_next, freeze);
+    const uint32_t *list = v.list + v.nlarge;
+    const uint32_t n = v.nruns - v.nlarge, tiny = n - v.nmid;
+    if (v.nmid && tiny > kSplitTiny && n > kSplitAll) {
+        f(std::integral_constant<int, 1024>{}, list, v.nmid);
+        f(std::integral_constant<int, 256>{}, list + v.nmid, tiny);
+    } else if (v.nmid) {
+        f(std::integral_constant<int, 1024>{}, list, n);
+    } else if (n) {
+        f(std::integral_constant<int, 256>{}, list, n);
+    }
 }
 
 bool pa_advances_at_once(const PaBatchView &v, int scheme) { return resamples_small(v, scheme, -1) && !v.weights; }
@@ -3143,22 +3157,16 @@ hipError_t pa_b_advance(const PaBatchView &v, double beta_next, int hist_state, 
     hipError_t e = hist_launch(v, hist_state);
     if (e != hipSuccess)
         return e;
-    if (v.small_cap <= PA_CHUNK)
-        advance_small_launch<256>(v, beta_next, scheme, freeze);
-    else
-        advance_small_launch<1024>(v, beta_next, scheme, freeze);
+    small_launches(v, [&](auto lanes, const uint32_t *list, uint32_t n) {
+        constexpr int T = decltype(lanes)::value;
+        if (scheme == 1)
+            k_advance_small<T, 1><<<n, T, 0, v.stream>>>(v.runs, list, beta_next, freeze);
+        else if (scheme == 2)
+            k_advance_small<T, 2><<<n, T, 0, v.stream>>>(v.runs, list, beta_next, freeze);
+        else
+            k_advance_small<T, 3><<<n, T, 0, v.stream>>>(v.runs, list, beta_next, freeze);
+    });
     return gather_rest(v);
-}
-
-template <int T>
-static void resample_small_launch(const PaBatchView &v, int scheme, int freeze)
-{
-    if (scheme == 1)
-        k_resample_small<T, 1><<<v.nruns, T, 0, v.stream>>>(v.runs, freeze);
-    else if (scheme == 2)
-        k_resample_small<T, 2><<<v.nruns, T, 0, v.stream>>>(v.runs, freeze);
-    else
-        k_resample_small<T, 3><<<v.nruns, T, 0, v.stream>>>(v.runs, freeze);
 }
 
 // Launches per scheme (after the reweighting): where every run is small and
@@ -3178,10 +3186,15 @@ hipError_t pa_b_resample(const PaBatchView &v, int scheme, int freeze, int kq, b
     if (!prepped)
         k_resample_prep<<<v.nruns, kThreads, 0, v.stream>>>(v.runs);
     if (resamples_small(v, scheme, kq)) {
-        if (v.small_cap <= PA_CHUNK)
-            resample_small_launch<256>(v, scheme, freeze);
-        else
-            resample_small_launch<1024>(v, scheme, freeze);
+        small_launches(v, [&](auto lanes, const uint32_t *list, uint32_t n) {
+            constexpr int T = decltype(lanes)::value;
+            if (scheme == 1)
+                k_resample_small<T, 1><<<n, T, 0, v.stream>>>(v.runs, list, freeze);
+            else if (scheme == 2)
+                k_resample_small<T, 2><<<n, T, 0, v.stream>>>(v.runs, list, freeze);
+            else
+                k_resample_small<T, 3><<<n, T, 0, v.stream>>>(v.runs, list, freeze);
+        });
         return gather_rest(v);
     }
     switch (scheme) {
@@ -3232,11 +3245,10 @@ hipError_t pa_b_observables(const PaBatchView &v, int point, int hist_state)
         k_obs_fam<<<v.nfam_large, kThreads, 0, v.stream>>>(v.runs, v.fam);
         k_obs_final<<<v.nlarge, kThreads, 0, v.stream>>>(v.runs, v.list, rows, v.npoints, point);
     }
-    const uint32_t small = v.nruns - v.nlarge;
-    if (small && v.small_cap <= PA_CHUNK)
-        k_obs_small<kThreads><<<small, kThreads, 0, v.stream>>>(v.runs, v.list + v.nlarge, build, rows, v.npoints, point);
-    else if (small)
-        k_obs_small<1024><<<small, 1024, 0, v.stream>>>(v.runs, v.list + v.nlarge, build, rows, v.npoints, point);
+    small_launches(v, [&](auto lanes, const uint32_t *list, uint32_t n) {
+        constexpr int T = decltype(lanes)::value;
+        k_obs_small<T><<<n, T, 0, v.stream>>>(v.runs, list, build, rows, v.npoints, point);
+    });
     return hipGetLastError();
 }
 
