@@ -341,7 +341,7 @@ hipError_t launch_updates(Batch *b, int n, uint32_t t0, int cluster)
     if (cluster) {
         e = settle_spins(b);
         if (e == hipSuccess)
-            e = pa_b_cluster(b->v, n, t0);
+            e = pa_b_cluster(b->v, n, t0, b->beta);
     } else {
         e = pa_b_sweep(b->v, n, t0, b->gather_pending ? 1 : 0);
         b->gather_pending = false;

@@ -260,4 +260,5 @@ int pa_sweep_walk(int N, int d, int threads, bool J);      // 0 coordinates at e
 int pa_sweep_waves_cap(int N, int d, int threads, bool J); // most sweep waves on a CU (registers)
 int pa_default_sweep_threads(int N, int d, bool J, int64_t columns); // default sweep workgroup size (pa_api.cpp)
 size_t pa_cluster_lds_bytes(int N, bool J);                   // dynamic LDS of a cluster-update workgroup
-hipError_t pa_b_cluster(const PaBatchView &v, int nsteps, uint32_t t0); // Wolff updates of every run
+// Wolff updates of every run; beta: the runs' (it chooses the kernel, not the result)
+hipError_t pa_b_cluster(const PaBatchView &v, int nsteps, uint32_t t0, double beta);

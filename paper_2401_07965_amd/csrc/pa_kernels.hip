@@ -11,7 +11,9 @@
 // each run's capacity; workgroups past the live population return at once.
 #include "pa_sweep.h"
 
+#include <algorithm>
 #include <climits>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -146,8 +148,28 @@ __global__ __launch_bounds__(kThreads) void k_init_labels(const PaRunDesc *__res
 // four, 0.45 ms now.  Two or eight passes to a barrier ran 3 % and 1 % slower.
 constexpr int kGrowPasses = 4;
 
-// Most lanes of a workgroup: N <= 4096 sites in patches of 16, of 4 (2D) or of 8 (3D).
-constexpr int cluster_lanes(int d, int patch) { return patch == 16 ? 256 : (d == 2 ? 1024 : 512); }
+// Most lanes of a workgroup: N <= 4096 sites in patches of 16, of 4 (2D) or of 8 (3D); twice as many
+// as there can be patches of 16 for the decisions of few columns (cluster_launch).
+constexpr int cluster_lanes(int d, int patch) { return patch == 16 ? 512 : (d == 2 ? 1024 : 512); }
+
+// T_p at the run's beta.
+__device__ __forceinline__ uint64_t wolff_threshold(const PaRecord *rec)
+{
+    const double p = 1.0 - pa_exp(-(2.0 * rec->beta));
+    const double tf = floor(ldexp(p, 32));
+    uint64_t T = (uint64_t)tf;
+    if (T > (1ull << 32))
+        T = 1ull << 32;
+    return uni64(T);
+}
+
+// The seed site of replica b.
+__device__ __forceinline__ uint32_t wolff_seed(const PlaneCtx &pc, uint32_t b, int N)
+{
+    const pa_philox_out o =
+        pa_philox(pc.seed, pc.run_id, b, pc.w, pc.step, (PA_PURPOSE_WSEED << 28) | (pc.t << 8));
+    return (uint32_t)(((uint64_t)o.x0 * (uint64_t)N) >> 32);
+}
 
 // Activity of bond (owner, mu) for the replicas in cnd.
 __device__ __forceinline__ uint64_t wolff_bond(const PlaneCtx &pc, uint32_t owner, uint32_t mu, uint64_t cnd,
@@ -174,11 +196,35 @@ __device__ __forceinline__ uint64_t wolff_bond(const PlaneCtx &pc, uint32_t owne
     return acc;
 }
 
-// PX, PY (and in 3D PZ) divide L; a workgroup has a lane for each of the N / (PX PY PZ) patches.
+// The same for replica b alone.
+__device__ __forceinline__ bool wolff_bond_of(const PlaneCtx &pc, uint32_t owner, uint32_t mu, uint32_t b, uint64_t T)
+{
+    if (T >= (1ull << 32))
+        return true;
+    constexpr int kFirst = 3;
+    const uint32_t x3 = (PA_PURPOSE_WBOND << 28) | (pc.t << 8) | (mu << 4);
+    const pa_philox_shared sh = pa_philox_share(pc.seed, pc.run_id, owner, pc.w, pc.step);
+    uint32_t u = 0; // the uniform's leading bits
+    auto bits = [&](const pa_philox_out &o) {
+        u = (u << 2) | ((((b < 32u ? o.x0 : o.x1) >> (b & 31u)) & 1u) << 1) | (((b < 32u ? o.x2 : o.x3) >> (b & 31u)) & 1u);
+    };
+    pa_philox_out o[kFirst];
+    pa_philox_k<kFirst>(pc.seed, pc.run_id, sh, pc.w, pc.step, x3, o);
+#pragma unroll
+    for (int q = 0; q < kFirst; ++q)
+        bits(o[q]);
+    int left = 32 - 2 * kFirst; // bits to come
+    for (uint32_t q = kFirst; left > 0 && u == (uint32_t)T >> left; ++q, left -= 2)
+        bits(pa_philox_with(pc.seed, pc.run_id, sh, pc.w, pc.step, x3 | q));
+    return u < (uint32_t)T >> left;
+}
+
+// PX, PY (and in 3D PZ) divide L; a workgroup has a lane for each of the N / (PX PY PZ) patches, and
+// more that only decide bonds, recount and copy.
 template <int D, bool J, int PX, int PY, int PZ>
 __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(const PaRunDesc *__restrict__ runs,
                                                                           const PaBlk *__restrict__ map, int nsteps,
-                                                                          uint32_t t0)
+                                                                          uint32_t t0, int listed)
 {
     static_assert(D == 3 || PZ == 1, "flat patches in 2D");
     // dynamic LDS: lattice, then cluster, [N] | one axis's bonds [N] (at least 32 per wave, reused by
@@ -191,6 +237,9 @@ __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(cons
     const int64_t Rlive = (int64_t)rec->Rcur;
     if ((int64_t)w * 64 >= Rlive || frozen(rec))
         return;
+    const int first = listed ? uni((int)rd.dv.r[w]) : 0; // the updates k_cluster_list left
+    if (first >= nsteps)
+        return;
     const int L = uni(rd.L), N = uni(rd.N), LL = L * L;
     const int cur = uni(rec->cur);
     const int tid = threadIdx.x, bs = blockDim.x, nw = bs >> 6;
@@ -201,12 +250,7 @@ __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(cons
     if (J)
         load_jmask(jl, rd.dv.jmask, N);
     const uint32_t mL = uni((uint32_t)(((1ull << 32) + (uint64_t)L - 1) / (uint64_t)L));
-    const double p = 1.0 - pa_exp(-(2.0 * rec->beta));
-    const double tf = floor(ldexp(p, 32));
-    uint64_t T = (uint64_t)tf;
-    if (T > (1ull << 32))
-        T = 1ull << 32;
-    T = uni64(T);
+    const uint64_t T = wolff_threshold(rec);
     PlaneCtx pc;
     pc.seed = uni(rd.seed);
     pc.run_id = uni(rd.run_id);
@@ -222,7 +266,7 @@ __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(cons
     const int oym = qy == 0 ? L * (L - 1) : -L, oyp = qy == py - 1 ? -L * (L - 1) : L;
     const int ozm = qz == 0 ? LL * (L - 1) : -LL, ozp = (qz + 1) * PZ == L ? -LL * (L - 1) : LL;
     __syncthreads();
-    for (int step = 0; step < nsteps; ++step) {
+    for (int step = first; step < nsteps; ++step) {
         pc.t = t0 + (uint32_t)step;
         // the patch's own bonds (towards +e_mu), and those its neighbours own into its low faces
         uint64_t bx[PZ][PY][PX], by[PZ][PY][PX], bz[PZ][PY][PX], fx[PZ][PY], fy[PZ][PX], fz[PY][PX];
@@ -266,10 +310,7 @@ __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(cons
             lat[s] = 0;
         __syncthreads();
         if (tid < 64) { // the seed of replica tid
-            const pa_philox_out o = pa_philox(pc.seed, pc.run_id, (uint32_t)tid, w, pc.step,
-                                              (PA_PURPOSE_WSEED << 28) | (pc.t << 8));
-            const uint32_t sd = (uint32_t)(((uint64_t)o.x0 * (uint64_t)N) >> 32);
-            atomicOr((unsigned long long *)&lat[sd], 1ull << tid);
+            atomicOr((unsigned long long *)&lat[wolff_seed(pc, (uint32_t)tid, N)], 1ull << tid);
         }
         __syncthreads();
         uint64_t c[PZ][PY][PX];
@@ -363,6 +404,101 @@ __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(cons
     if (tid == 0 && w == 0) // once per run; no block reads it during the launch
         rec->sweeps = t0 + (uint32_t)nsteps;
     recount_column<D, J>(lat, [&](int t, int, int, int) -> uint32_t { return jl[t]; }, g, xb, rd, cur, w, Rlive, L, N,
+                         LL, mL, 0ull);
+}
+
+// The same updates where few bonds are active, one workgroup per column: the
+// clusters grow pair by pair (site, replica), level by level, from a list in
+// LDS; a lane decides one bond of a listed pair.  Deciding every bond of the
+// lattice would be most of such an update.  An update whose list overflows is
+// left, with those after it, to k_cluster: r[w] holds the first one left (the
+// copy numbers are scratch between resamplings).  Bound by the column's load
+// and recount and the latency of a few levels.  3D L = 12, R = 10^5, (2 d - 1) p =
+// 0.2: 180 us with the bonds decided as passes over the lattice reached them,
+// 165 with all decided first, 41 now.
+constexpr int kListed = 1024;
+template <int D, bool J>
+__global__ __launch_bounds__(1024) void k_cluster_list(const PaRunDesc *__restrict__ runs,
+                                                       const PaBlk *__restrict__ map, int nsteps, uint32_t t0)
+{
+    // dynamic LDS: lattice [N] | cluster [N] (at least 32 per wave, reused by the recount) | jmask [N] bytes
+    extern __shared__ uint64_t lat[];
+    __shared__ uint32_t item[kListed], listed; // site << 6 | replica; how many
+    const PaBlk blk = map[blockIdx.x];
+    const PaRunDesc &rd = runs[blk.run];
+    PaRecord *rec = rd.dv.rec;
+    const uint32_t w = blk.idx;
+    const int64_t Rlive = (int64_t)rec->Rcur;
+    if ((int64_t)w * 64 >= Rlive || frozen(rec))
+        return;
+    const int L = uni(rd.L), N = uni(rd.N), LL = L * L;
+    const int cur = uni(rec->cur);
+    const int tid = threadIdx.x, bs = blockDim.x, nw = bs >> 6;
+    uint64_t *cl = lat + N;
+    uint8_t *jl = reinterpret_cast<uint8_t *>(cl + max(N, 32 * nw));
+    uint64_t *g = rd.dv.spins[cur] + (size_t)w * N;
+    load_column(lat, g, N);
+    if (J)
+        load_jmask(jl, rd.dv.jmask, N);
+    const uint32_t mL = uni((uint32_t)(((1ull << 32) + (uint64_t)L - 1) / (uint64_t)L));
+    const uint64_t T = wolff_threshold(rec);
+    PlaneCtx pc;
+    pc.seed = uni(rd.seed);
+    pc.run_id = uni(rd.run_id);
+    pc.w = w;
+    pc.step = uni(rec->step);
+    int step = 0;
+    for (; step < nsteps; ++step) {
+        pc.t = t0 + (uint32_t)step;
+        for (int s = tid; s < N; s += bs)
+            cl[s] = 0;
+        if (tid == 0)
+            listed = 64;
+        __syncthreads();
+        if (tid < 64) {
+            const uint32_t sd = wolff_seed(pc, (uint32_t)tid, N);
+            atomicOr((unsigned long long *)&cl[sd], 1ull << tid);
+            item[tid] = (sd << 6) | (uint32_t)tid;
+        }
+        __syncthreads();
+        int lo = 0, hi = T == 0 ? 0 : 64;
+        while (lo < hi && hi <= kListed) { // every level adds pairs or is the last
+            for (int t = tid; t < (hi - lo) * 2 * D; t += bs) {
+                const int k = t / (2 * D), dir = t - k * 2 * D, mu = dir % D;
+                const uint32_t it = item[lo + k], b = it & 63u;
+                const int s = (int)(it >> 6), row = (int)__umulhi((uint32_t)s, mL);
+                const int x = s - row * L;
+                const int z = (D == 2) ? 0 : (int)__umulhi((uint32_t)row, mL);
+                const int y = row - z * L;
+                const int c = mu == 0 ? x : (mu == 1 ? y : z), st = mu == 0 ? 1 : (mu == 1 ? L : LL);
+                const int n = dir < D ? (c == L - 1 ? s - st * (L - 1) : s + st) : (c == 0 ? s + st * (L - 1) : s - st);
+                const int owner = dir < D ? s : n;
+                const uint64_t out = bond<J>(lat[s], lat[n], J ? (uint32_t)jl[owner] : 0u, mu) | cl[n];
+                if (((out >> b) & 1ull) == 0 && wolff_bond_of(pc, (uint32_t)owner, (uint32_t)mu, b, T) &&
+                    ((atomicOr((unsigned long long *)&cl[n], 1ull << b) >> b) & 1ull) == 0) {
+                    const uint32_t slot = atomicAdd(&listed, 1u);
+                    if (slot < (uint32_t)kListed)
+                        item[slot] = ((uint32_t)n << 6) | b;
+                }
+            }
+            __syncthreads();
+            lo = hi;
+            hi = uni((int)listed);
+            __syncthreads(); // every lane has the number before it grows
+        }
+        if (lo < hi)
+            break; // the list is full
+        for (int s = tid; s < N; s += bs)
+            lat[s] ^= cl[s];
+        __syncthreads();
+    }
+    if (tid == 0) {
+        rd.dv.r[w] = (uint32_t)step;
+        if (w == 0) // once per run; no block reads it during the launch
+            rec->sweeps = t0 + (uint32_t)nsteps;
+    }
+    __syncthreads();
+    recount_column<D, J>(lat, [&](int t, int, int, int) -> uint32_t { return jl[t]; }, g, cl, rd, cur, w, Rlive, L, N,
                          LL, mL, 0ull);
 }
 
@@ -2942,45 +3078,75 @@ size_t pa_cluster_lds_bytes(int N, bool J)
 
 namespace {
 
-template <int D, bool J, int PX, int PY, int PZ>
-hipError_t cluster_launch(const PaBatchView &v, int g, int nsteps, uint32_t t0)
+// Where (2 d - 1) p, p = 1 - exp(-2 beta), the most active bonds a site of the
+// cluster can have towards new ones on average, is below kListBelow, clusters
+// are small enough for k_cluster_list: an update at 0.2, 0.6, 1.2, 1.4 and 1.6 takes
+// 23, 26, 36, 47, 202 us against 100, 102, 113, 122, 147 at 3D L = 16, R = 2
+// 10^4, and 13, 15, 27, 40, 66 against 22, 22, 26, 29, 38 at 2D L = 32, R = 5000.
+// Deciding every bond is no more work where the lattice has few sites (2D L =
+// 16, R = 5000 14 us by the list, 12 by the flood at 0.2).
+constexpr double kListBelow = 1.2;
+constexpr int kListSites = 512;
+constexpr int kFewColumns = 256; // no more columns than CUs: each has a CU to itself
+
+size_t cluster_lds(int N, int threads, bool J)
 {
+    return ((size_t)N + (size_t)std::max(N, threads / 2)) * 8 + (J ? (((size_t)N + 7) & ~(size_t)7) : 0);
+}
+
+template <int D, bool J, int PX, int PY, int PZ>
+hipError_t cluster_launch(const PaBatchView &v, int g, int nsteps, uint32_t t0, int listed)
+{
+    constexpr int kMost = cluster_lanes(D, PX * PY * PZ);
     const int N = v.gN[g];
-    const int threads = (N / (PX * PY * PZ) + 63) / 64 * 64, nw = threads / 64;
-    if (threads > cluster_lanes(D, PX * PY * PZ))
+    int threads = (N / (PX * PY * PZ) + 63) / 64 * 64;
+    if (threads > kMost)
         return hipErrorInvalidValue;
-    const size_t lds = ((size_t)N + (size_t)(N > 32 * nw ? N : 32 * nw)) * 8 + (J ? (((size_t)N + 7) & ~(size_t)7) : 0);
-    k_cluster<D, J, PX, PY, PZ><<<v.gncol[g], threads, lds, v.stream>>>(v.runs, v.gcol[g], nsteps, t0);
+    // more lanes decide a column's bonds sooner where it has a CU to itself: 2D L = 32, R = 5000 at the
+    // critical point 69 -> 49 us, 3D L = 16 180 -> 169
+    if (v.gncol[g] <= kFewColumns)
+        threads = std::max(threads, std::min(kMost, (N + 63) / 64 * 64));
+    k_cluster<D, J, PX, PY, PZ>
+        <<<v.gncol[g], threads, cluster_lds(N, threads, J), v.stream>>>(v.runs, v.gcol[g], nsteps, t0, listed);
     return hipGetLastError();
 }
 
 // Patches of 16 sites (4 x 4 or 4 x 2 x 2) where L allows it and they fill at least a wave, else of
 // two sites each way: with fewer than 64 patches the lanes without one idle through the growth.
 template <int D, bool J>
-hipError_t cluster_launch(const PaBatchView &v, int g, int nsteps, uint32_t t0, int L)
+hipError_t cluster_launch(const PaBatchView &v, int g, int nsteps, uint32_t t0, double beta)
 {
-    const bool wide = L % 4 == 0 && v.gN[g] >= 16 * 64;
+    const int N = v.gN[g];
+    int L = 2;
+    while ((D == 2 ? L * L : L * L * L) < N)
+        ++L;
+    const int listed = N > kListSites && (2 * D - 1) * -std::expm1(-2.0 * beta) < kListBelow;
+    if (listed) {
+        const int threads = std::min(v.gncol[g] <= kFewColumns ? 1024 : 512, (N / 4 + 63) / 64 * 64);
+        k_cluster_list<D, J>
+            <<<v.gncol[g], threads, cluster_lds(N, threads, J), v.stream>>>(v.runs, v.gcol[g], nsteps, t0);
+    }
+    const bool wide = L % 4 == 0 && N >= 16 * 64;
     if constexpr (D == 2)
-        return wide ? cluster_launch<2, J, 4, 4, 1>(v, g, nsteps, t0) : cluster_launch<2, J, 2, 2, 1>(v, g, nsteps, t0);
+        return wide ? cluster_launch<2, J, 4, 4, 1>(v, g, nsteps, t0, listed)
+                    : cluster_launch<2, J, 2, 2, 1>(v, g, nsteps, t0, listed);
     else
-        return wide ? cluster_launch<3, J, 4, 2, 2>(v, g, nsteps, t0) : cluster_launch<3, J, 2, 2, 2>(v, g, nsteps, t0);
+        return wide ? cluster_launch<3, J, 4, 2, 2>(v, g, nsteps, t0, listed)
+                    : cluster_launch<3, J, 2, 2, 2>(v, g, nsteps, t0, listed);
 }
 
 } // namespace
 
-hipError_t pa_b_cluster(const PaBatchView &v, int nsteps, uint32_t t0)
+hipError_t pa_b_cluster(const PaBatchView &v, int nsteps, uint32_t t0, double beta)
 {
     for (int g = 0; g < v.ngroups; ++g) {
         if (v.gncol[g] == 0)
             continue;
-        int L = 2;
-        while ((v.gd[g] == 2 ? L * L : L * L * L) < v.gN[g])
-            ++L;
         hipError_t e;
         if (v.gd[g] == 2)
-            e = v.gJ[g] ? cluster_launch<2, true>(v, g, nsteps, t0, L) : cluster_launch<2, false>(v, g, nsteps, t0, L);
+            e = v.gJ[g] ? cluster_launch<2, true>(v, g, nsteps, t0, beta) : cluster_launch<2, false>(v, g, nsteps, t0, beta);
         else
-            e = v.gJ[g] ? cluster_launch<3, true>(v, g, nsteps, t0, L) : cluster_launch<3, false>(v, g, nsteps, t0, L);
+            e = v.gJ[g] ? cluster_launch<3, true>(v, g, nsteps, t0, beta) : cluster_launch<3, false>(v, g, nsteps, t0, beta);
         if (e != hipSuccess)
             return e;
     }
