@@ -179,9 +179,9 @@ pa_status pa_sweep(pa_ctx *ctx, int32_t theta);
  * cluster flips.  t counts sweeps and cluster updates together within step i
  * (at most 2^20).  Energies and magnetisations are recounted afterwards.
  * PA_E_INVAL if nsteps < 0, if the step's updates would pass 2^20, or if the
- * lattice is too large: 32 N bytes and 24 KiB, plus N bytes with couplings,
- * must not pass the device's LDS per workgroup (N <= 4352, or 4220 with
- * couplings, on 160 KiB).  Enqueued on the run's stream. */
+ * lattice has more than 4096 sites (L <= 64 in 2D, 16 in 3D): a workgroup holds
+ * a column in its LDS and has a lane for each patch of 4 to 16 of its sites.
+ * Enqueued on the run's stream. */
 pa_status pa_cluster(pa_ctx *ctx, int32_t nsteps);
 
 /* Step 2 of Sec. 2: for beta_next >= beta, ln Q of Eq. (1) over the current

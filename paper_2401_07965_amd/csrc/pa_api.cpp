@@ -855,8 +855,8 @@ pa_status pa_cluster(pa_ctx *c, int32_t nsteps)
     if ((uint64_t)b->sweeps + (uint64_t)nsteps > (1u << 20))
         return fail(b, PA_E_INVAL, "more than 2^20 sweeps and cluster updates at one temperature");
     for (int g = 0; g < b->v.ngroups; ++g)
-        if (pa_cluster_lds_bytes(b->v.gN[g], b->v.gJ[g] != 0) > (size_t)g_max_lds)
-            return fail(b, PA_E_INVAL, "lattice too large for cluster updates (LDS of one workgroup)");
+        if (b->v.gN[g] > PA_CLUSTER_SITES || pa_cluster_lds_bytes(b->v.gN[g], b->v.gJ[g] != 0) > (size_t)g_max_lds)
+            return fail(b, PA_E_INVAL, "lattice too large for cluster updates (more than 4096 sites)");
     if (nsteps == 0)
         return PA_OK;
     hipError_t e = launch_updates(b, nsteps, b->sweeps, 1);

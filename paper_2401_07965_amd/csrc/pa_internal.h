@@ -92,6 +92,7 @@ struct PaScanTile {
 #define PA_CHUNK 1024  // replicas (or families) per workgroup of the per-replica kernels
 #define PA_HCHUNK 4096 // families per workgroup of the family statistics
 
+#define PA_CLUSTER_SITES 4096 // sites of the largest lattice of cluster updates (a lane for each patch)
 #define PA_SMALL_CAP 4096 // capacity of the runs whose passes over replicas one workgroup takes
 
 // Counters that a run's Philox evaluations are spread over; pa_get_counters adds
@@ -259,6 +260,6 @@ size_t pa_sweep_lds_bytes(int N, int d, int threads, bool J); // dynamic LDS of 
 int pa_sweep_walk(int N, int d, int threads, bool J);      // 0 coordinates at each site, 1 site table, 2 or 3 fixed axis
 int pa_sweep_waves_cap(int N, int d, int threads, bool J); // most sweep waves on a CU (registers)
 int pa_default_sweep_threads(int N, int d, bool J, int64_t columns); // default sweep workgroup size (pa_api.cpp)
-size_t pa_cluster_lds_bytes(int N, bool J);                   // dynamic LDS of a cluster-update workgroup
+size_t pa_cluster_lds_bytes(int N, bool J);                   // LDS of a cluster-update workgroup, at most
 // Wolff updates of every run; beta: the runs' (it chooses the kernel, not the result)
 hipError_t pa_b_cluster(const PaBatchView &v, int nsteps, uint32_t t0, double beta);

@@ -3069,13 +3069,6 @@ int pa_sweep_waves_cap(int N, int d, int threads, bool J)
     return sweep_four(pa_sweep_lds_bytes(N, d, threads, J), threads) ? kWavesPerCu : 4 * (d == 3 ? 5 : 7);
 }
 
-// The largest lattice of a cluster update, as the bytes its LDS limit counts: four words per site
-// and 24 KiB (N <= 4352 on 160 KiB), one byte more per site with couplings.
-size_t pa_cluster_lds_bytes(int N, bool J)
-{
-    return (size_t)N * 32 + 24576 + (J ? (((size_t)N + 7) & ~(size_t)7) : 0);
-}
-
 namespace {
 
 // Where (2 d - 1) p, p = 1 - exp(-2 beta), the most active bonds a site of the
@@ -3093,6 +3086,10 @@ size_t cluster_lds(int N, int threads, bool J)
 {
     return ((size_t)N + (size_t)std::max(N, threads / 2)) * 8 + (J ? (((size_t)N + 7) & ~(size_t)7) : 0);
 }
+
+static_assert(PA_CLUSTER_SITES / 16 <= cluster_lanes(2, 16) && PA_CLUSTER_SITES / 4 <= cluster_lanes(2, 4) &&
+                  PA_CLUSTER_SITES / 8 <= cluster_lanes(3, 8),
+              "a lane for each patch");
 
 template <int D, bool J, int PX, int PY, int PZ>
 hipError_t cluster_launch(const PaBatchView &v, int g, int nsteps, uint32_t t0, int listed)
@@ -3152,6 +3149,8 @@ hipError_t pa_b_cluster(const PaBatchView &v, int nsteps, uint32_t t0, double be
     }
     return hipSuccess;
 }
+
+size_t pa_cluster_lds_bytes(int N, bool J) { return cluster_lds(N, 1024, J) + (kListed + 1) * sizeof(uint32_t); }
 
 hipError_t pa_query_lds(int *max_lds)
 {

@@ -78,3 +78,18 @@ def test_more_columns_than_cus():
         o.cluster(2)
         compare_state(g, o, f"beta {b}")
     g.close()
+
+
+@pytest.mark.parametrize("d,L,glass,taken", [(2, 64, True, True), (2, 66, False, False), (2, 68, False, False),
+                                             (3, 16, True, True), (3, 18, False, False), (3, 20, False, False)])
+def test_largest_lattices(d, L, glass, taken):
+    """4096 sites are taken, more refused, with the bound in the message."""
+    from paper_2401_07965_amd import pa
+    g = pa.PARun(d, L, 10, seed=1, couplings=ea_couplings(d, L, 1) if glass else None)
+    if taken:
+        g.cluster(1)
+        g.export()
+    else:
+        with pytest.raises(pa.PAError, match="4096"):
+            g.cluster(1)
+    g.close()
