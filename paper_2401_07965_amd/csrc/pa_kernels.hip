@@ -749,14 +749,16 @@ struct Overlap {
     pa_u128 num, den;
 };
 
+// The whole workgroup's overlap at dbeta: every thread takes every
+// blockDim-th level (with a contiguous range each, the lanes' reads of counts
+// and weights lay apart: 60 halvings over 16000 levels 1370 -> 1196 us, over
+// 4000 399 -> 353).
 __device__ Overlap rule_overlap(const uint32_t *__restrict__ hist, int hmin, int nlev, uint64_t R, double dbeta,
                                 uint64_t *wcache, uint64_t *su)
 {
-    const int chunk = (nlev + (int)blockDim.x - 1) / (int)blockDim.x;
-    const int lo = (int)threadIdx.x * chunk;
-    const int hi = lo + chunk < nlev ? lo + chunk : nlev;
+    const int bs = (int)blockDim.x;
     uint64_t s = 0;
-    for (int k = lo; k < hi; ++k) {
+    for (int k = threadIdx.x; k < nlev; k += bs) {
         const uint64_t W = pa_weight(dbeta, 4 * k);
         if (k < kRuleCache)
             wcache[k] = W;
@@ -764,7 +766,7 @@ __device__ Overlap rule_overlap(const uint32_t *__restrict__ hist, int hmin, int
     }
     const uint64_t S = pa_block_sum_u64(s, su);
     pa_u128 a = 0;
-    for (int k = lo; k < hi; ++k) {
+    for (int k = threadIdx.x; k < nlev; k += bs) {
         const uint64_t W = k < kRuleCache ? wcache[k] : pa_weight(dbeta, 4 * k);
         const uint64_t RW = R * W;
         a += (pa_u128)hist[hmin + k] * (RW < S ? RW : S);
@@ -839,7 +841,9 @@ struct RuleSearch {
     bool waves; // a wave per point
 
     // Starts a search over the run's populated levels (all threads).
-    __device__ __forceinline__ RuleSearch(RuleLds *lds, const PaRunDesc &rd, const PaRecord *rec, double alpha_star)
+    // most: levels up to which a wave takes a point of its own
+    __device__ __forceinline__ RuleSearch(RuleLds *lds, const PaRunDesc &rd, const PaRecord *rec, double alpha_star,
+                                          int most = kRuleLevels)
         : l(lds), hist(rd.dv.hist), buf(0)
     {
         const int DN = rd.d * rd.N;
@@ -847,7 +851,7 @@ struct RuleSearch {
         nlev = uni(((rec->emax + DN) >> 2) - hmin + 1);
         R = uni64(rec->Rcur);
         A = uni64((uint64_t)rint(ldexp(alpha_star, 32)));
-        waves = nlev <= kRuleLevels;
+        waves = nlev <= most;
         if (waves)
             for (int k = threadIdx.x; k < nlev; k += blockDim.x)
                 l->count[k] = hist[hmin + k];
@@ -1008,7 +1012,9 @@ __global__ __launch_bounds__(kRuleWaves * 64) void k_rule(const PaRunDesc *__res
     PaRecord *rec = rd.dv.rec;
     if (frozen(rec))
         return;
-    RuleSearch rs(&lds, rd, rec, alpha_star);
+    // a single point of many levels: the workgroup's lanes outweigh its barriers (2000 levels 23.8 -> 17.8 us
+    // with the call's copy and wait)
+    RuleSearch rs(&lds, rd, rec, alpha_star, bisect ? kRuleLevels : 64 * kRuleHeld);
     const double xs[1] = {dbeta_max};
     rs.points(xs);
     const Overlap top = rs.at(0, dbeta_max);
