@@ -70,14 +70,16 @@ __global__ void k_init_rec(const PaRunDesc *__restrict__ runs)
     rec->ess = (double)rd.R0;
 }
 
-// The site words of the sweeps' table walk, one workgroup per run: word c N/2
-// + k is site k of colour c (row = y + L z = k div (L/2), x = 2 (k mod L/2) +
-// (y + z + c) mod 2).
+// The site words of the sweeps' table walk: word c N/2 + k is site k of colour
+// c (row = y + L z = k div (L/2), x = 2 (k mod L/2) + (y + z + c) mod 2).
+// Workgroups (run, kThreads sites): one for a run's whole table kept the
+// creation of a 2D L = 128 run waiting, with couplings 252 -> 227 us.
 __global__ __launch_bounds__(kThreads) void k_sites(const PaRunDesc *__restrict__ runs)
 {
     const PaRunDesc &rd = runs[blockIdx.x];
     const int L = rd.L, half = L >> 1, nh = rd.N >> 1;
-    for (int i = threadIdx.x; i < rd.N; i += blockDim.x) {
+    const int i = blockIdx.y * blockDim.x + threadIdx.x;
+    if (i < rd.N) {
         const int c = i >= nh ? 1 : 0, k = i - c * nh;
         const int row = k / half, z = row / L, y = row - z * L;
         const int x = 2 * (k - row * half) + ((y + z + c) & 1), s = x + L * row;
@@ -3171,7 +3173,8 @@ hipError_t pa_query_lds(int *max_lds)
 
 hipError_t pa_b_sites(const PaBatchView &v)
 {
-    k_sites<<<v.nruns, kThreads, 0, v.stream>>>(v.runs);
+    const int most = *std::max_element(v.gN, v.gN + v.ngroups);
+    k_sites<<<dim3(v.nruns, (most + kThreads - 1) / kThreads), kThreads, 0, v.stream>>>(v.runs);
     return hipGetLastError();
 }
 
