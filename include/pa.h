@@ -370,8 +370,10 @@ pa_status pa_batch_groups(pa_batch *b, int32_t *ngroups, int32_t *threads);
  * use_graph != 0 captures the anneal in one HIP graph, instantiates it and
  * launches it; the batch keeps the instantiated graph, and a later call with
  * the same betas, theta and scheme (and unchanged workgroup sizes) replays it
- * without capturing again.  Any other use_graph call replaces the kept graph;
- * pa_batch_destroy releases it.  Synchronises the stream. */
+ * without capturing again.  Any other use_graph call replaces the kept graph,
+ * except in a batch of several groups, which keeps its first one and launches
+ * the other anneals directly (the same results).  pa_batch_destroy releases
+ * it.  Synchronises the stream. */
 pa_status pa_batch_anneal(pa_batch *b, const double *betas, int32_t npoints, int32_t theta,
                           pa_resampler scheme, int32_t use_graph);
 

@@ -1417,6 +1417,14 @@ pa_status pa_batch_anneal(pa_batch *p, const double *betas, int32_t npoints, int
         b->anneal_points = npoints;
         return PA_OK;
     }
+    // A batch of several groups (forked streams in the graph) captures one graph
+    // in its life: a program that captured such a batch's anneal again and again,
+    // with other workgroup sizes each time, ended with a corrupted heap, and why
+    // is not known.  Its anneals with other arguments are launched directly
+    // (32 uneven runs of eight lattices 41.4 ms, replayed 33.5); one of one group
+    // replaces its graph.
+    if (use_graph && b->v.ngroups > 1 && b->anneal_exec)
+        use_graph = 0;
     if (use_graph)
         drop_anneal_graph(b);
     hipGraph_t graph = nullptr;
