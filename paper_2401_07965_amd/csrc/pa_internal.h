@@ -19,7 +19,9 @@
 #define PA_ST_FROZEN 16u // batch mode: a failed step froze the run
 
 // Per-run scalars that live in device memory, written by the kernels.
-struct PaRecord {
+// A whole number of 16-byte units: its copy to the host, one per waited call,
+// then moves such units (536 bytes took 1.85 us, 544 1.50).
+struct alignas(16) PaRecord {
     int32_t cur;      // ping-pong buffer holding the population
     uint32_t status;  // PA_ST_* bits of the latest resampling (sticky when frozen)
     uint32_t skip;    // latest resampling was not applied
