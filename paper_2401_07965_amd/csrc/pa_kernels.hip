@@ -2253,7 +2253,7 @@ template <int T, int SCHEME>
 __global__ __launch_bounds__(T) void k_resample_small(const PaRunDesc *__restrict__ runs,
                                                       const uint32_t *__restrict__ list, int freeze)
 {
-    const PaRunDesc &rd = runs[list[blockIdx.x]];
+    const PaRunDesc &rd = runs[list ? list[blockIdx.x] : blockIdx.x];
     if (!frozen(rd.dv.rec))
         resample_small_run<T, SCHEME>(rd, rd.dv.rec, freeze);
 }
@@ -2265,7 +2265,7 @@ template <int T, int SCHEME>
 __global__ __launch_bounds__(T) void k_advance_small(const PaRunDesc *__restrict__ runs,
                                                      const uint32_t *__restrict__ list, double beta_next, int freeze)
 {
-    const PaRunDesc &rd = runs[list[blockIdx.x]];
+    const PaRunDesc &rd = runs[list ? list[blockIdx.x] : blockIdx.x];
     if (frozen(rd.dv.rec))
         return;
     reweight_run<T>(rd, rd.dv.rec, beta_next);
@@ -2625,7 +2625,7 @@ __global__ __launch_bounds__(T) void k_obs_small(const PaRunDesc *__restrict__ r
     __shared__ uint64_t su[7][kThreads], tot[7];
     __shared__ double sw[T / 64][PA_WPARTS], sf[4], logs[64];
     __shared__ int s_lo[T / 64], s_hi[T / 64];
-    const uint32_t run = list[blockIdx.x];
+    const uint32_t run = list ? list[blockIdx.x] : blockIdx.x;
     const PaRunDesc &rd = runs[run];
     PaRecord *rec = rd.dv.rec;
     if (frozen(rec)) {
@@ -3301,7 +3301,7 @@ static bool resamples_small(const PaBatchView &v, int scheme, int kq)
     return v.nlarge == 0 && kq < 0 && scheme >= 1 && scheme <= 3;
 }
 
-// Calls f(lanes, runs, n) for the small runs: workgroups of 1024 lanes, or of
+// Calls f(lanes, list of the runs (null: all of the batch), n) for the small runs: workgroups of 1024 lanes, or of
 // 256 where every run is tiny.  Where tiny runs outnumber the CUs and all
 // small runs are more than two to a CU (what 1024-lane workgroups fill), the
 // middle and the tiny ones start apart: 1024 lanes for a tiny run leave most
@@ -3317,11 +3317,14 @@ static void small_launches(const PaBatchView &v, F f)
     if (v.nmid && tiny > kSplitTiny && n > kSplitAll) {
         f(std::integral_constant<int, 1024>{}, list, v.nmid);
         f(std::integral_constant<int, 256>{}, list + v.nmid, tiny);
-    } else if (v.nmid) {
-        f(std::integral_constant<int, 1024>{}, list, n);
-    } else if (n) {
-        f(std::integral_constant<int, 256>{}, list, n);
+        return;
     }
+    if (v.nlarge == 0)
+        list = nullptr; // all runs: no load of the index first
+    if (v.nmid)
+        f(std::integral_constant<int, 1024>{}, list, n);
+    else if (n)
+        f(std::integral_constant<int, 256>{}, list, n);
 }
 
 bool pa_advances_at_once(const PaBatchView &v, int scheme) { return resamples_small(v, scheme, -1) && !v.weights; }
