@@ -222,11 +222,11 @@ __device__ __forceinline__ bool wolff_bond_of(const PlaneCtx &pc, uint32_t owner
 }
 
 // PX, PY (and in 3D PZ) divide L; a workgroup has a lane for each of the N / (PX PY PZ) patches, and
-// more that only decide bonds, recount and copy.
-template <int D, bool J, int PX, int PY, int PZ>
+// more that only decide bonds, recount and copy.  REST: the updates that k_cluster_list left.
+template <int D, bool J, int PX, int PY, int PZ, bool REST>
 __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(const PaRunDesc *__restrict__ runs,
                                                                           const PaBlk *__restrict__ map, int nsteps,
-                                                                          uint32_t t0, int listed)
+                                                                          uint32_t t0)
 {
     static_assert(D == 3 || PZ == 1, "flat patches in 2D");
     // dynamic LDS: lattice, then cluster, [N] | one axis's bonds [N] (at least 32 per wave, reused by
@@ -239,8 +239,8 @@ __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(cons
     const int64_t Rlive = (int64_t)rec->Rcur;
     if ((int64_t)w * 64 >= Rlive || frozen(rec))
         return;
-    const int first = listed ? uni((int)rd.dv.r[w]) : 0; // the updates k_cluster_list left
-    if (first >= nsteps)
+    const int first = REST ? uni((int)rd.dv.r[w]) : 0;
+    if (REST && first >= nsteps)
         return;
     const int L = uni(rd.L), N = uni(rd.N), LL = L * L;
     const int cur = uni(rec->cur);
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(cluster_lanes(D, PX * PY * PZ)) void k_cluster(cons
     }
     if (tid == 0 && w == 0) // once per run; no block reads it during the launch
         rec->sweeps = t0 + (uint32_t)nsteps;
-    recount_column<D, J>(lat, [&](int t, int, int, int) -> uint32_t { return jl[t]; }, g, xb, rd, cur, w, Rlive, L, N,
+    recount_column<D, J, false>(lat, [&](int t, int, int, int) -> uint32_t { return jl[t]; }, g, xb, rd, cur, w, Rlive, L, N,
                          LL, mL, 0ull);
 }
 
@@ -500,7 +500,7 @@ __global__ __launch_bounds__(1024) void k_cluster_list(const PaRunDesc *__restri
             rec->sweeps = t0 + (uint32_t)nsteps;
     }
     __syncthreads();
-    recount_column<D, J>(lat, [&](int t, int, int, int) -> uint32_t { return jl[t]; }, g, cl, rd, cur, w, Rlive, L, N,
+    recount_column<D, J, false>(lat, [&](int t, int, int, int) -> uint32_t { return jl[t]; }, g, cl, rd, cur, w, Rlive, L, N,
                          LL, mL, 0ull);
 }
 
@@ -3099,8 +3099,8 @@ static_assert(PA_CLUSTER_SITES / 16 <= cluster_lanes(2, 16) && PA_CLUSTER_SITES 
                   PA_CLUSTER_SITES / 8 <= cluster_lanes(3, 8),
               "a lane for each patch");
 
-template <int D, bool J, int PX, int PY, int PZ>
-hipError_t cluster_launch(const PaBatchView &v, int g, int nsteps, uint32_t t0, int listed)
+template <int D, bool J, int PX, int PY, int PZ, bool REST>
+hipError_t cluster_launch(const PaBatchView &v, int g, int nsteps, uint32_t t0)
 {
     constexpr int kMost = cluster_lanes(D, PX * PY * PZ);
     const int N = v.gN[g];
@@ -3111,8 +3111,8 @@ hipError_t cluster_launch(const PaBatchView &v, int g, int nsteps, uint32_t t0, 
     // critical point 69 -> 49 us, 3D L = 16 180 -> 169
     if (v.gncol[g] <= kFewColumns)
         threads = std::max(threads, std::min(kMost, (N + 63) / 64 * 64));
-    k_cluster<D, J, PX, PY, PZ>
-        <<<v.gncol[g], threads, cluster_lds(N, threads, J), v.stream>>>(v.runs, v.gcol[g], nsteps, t0, listed);
+    k_cluster<D, J, PX, PY, PZ, REST>
+        <<<v.gncol[g], threads, cluster_lds(N, threads, J), v.stream>>>(v.runs, v.gcol[g], nsteps, t0);
     return hipGetLastError();
 }
 
@@ -3125,19 +3125,15 @@ hipError_t cluster_launch(const PaBatchView &v, int g, int nsteps, uint32_t t0, 
     int L = 2;
     while ((D == 2 ? L * L : L * L * L) < N)
         ++L;
-    const int listed = N > kListSites && (2 * D - 1) * -std::expm1(-2.0 * beta) < kListBelow;
-    if (listed) {
+    if (N > kListSites && (2 * D - 1) * -std::expm1(-2.0 * beta) < kListBelow) {
         const int threads = std::min(v.gncol[g] <= kFewColumns ? 1024 : 512, (N / 4 + 63) / 64 * 64);
         k_cluster_list<D, J>
             <<<v.gncol[g], threads, cluster_lds(N, threads, J), v.stream>>>(v.runs, v.gcol[g], nsteps, t0);
+        return cluster_launch<D, J, 2, 2, D == 2 ? 1 : 2, true>(v, g, nsteps, t0);
     }
-    const bool wide = L % 4 == 0 && N >= 16 * 64;
-    if constexpr (D == 2)
-        return wide ? cluster_launch<2, J, 4, 4, 1>(v, g, nsteps, t0, listed)
-                    : cluster_launch<2, J, 2, 2, 1>(v, g, nsteps, t0, listed);
-    else
-        return wide ? cluster_launch<3, J, 4, 2, 2>(v, g, nsteps, t0, listed)
-                    : cluster_launch<3, J, 2, 2, 2>(v, g, nsteps, t0, listed);
+    if (L % 4 == 0 && N >= 16 * 64)
+        return cluster_launch<D, J, 4, D == 2 ? 4 : 2, D == 2 ? 1 : 2, false>(v, g, nsteps, t0);
+    return cluster_launch<D, J, 2, 2, D == 2 ? 1 : 2, false>(v, g, nsteps, t0);
 }
 
 } // namespace

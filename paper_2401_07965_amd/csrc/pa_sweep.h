@@ -416,13 +416,13 @@ __device__ __forceinline__ void wave_count2(const uint64_t (&a)[8], const uint64
 // writes the lattice back to g.  Per-lane counts stay below 2^8: at most
 // ceil(N / blockDim) sites per lane, d bonds each (the launch checks).
 // jbits(t, x, y, z): site t's bond bits (bit mu: to s + e_mu).
-// calls: the wave's Philox evaluations; the workgroup's are added to one of the
+// calls (COUNT): the wave's Philox evaluations; the workgroup's are added to one of the
 // run's counters here (PA_CALL_SLOTS).  An atomic per wave on the run's record
 // (and one per workgroup for the updates) took 12 to 14 ns each, one after the
 // other, and held the launch's end back:
 // two sweeps of 6200 columns of 2D L = 24 257 -> 106 us (128 lanes), of 4000 of
 // 3D L = 8 121 -> 55 (64 lanes), of 1536 of 3D L = 16 155 -> 135 (256).
-template <int D, bool J, typename JBits>
+template <int D, bool J, bool COUNT, typename JBits>
 __device__ __forceinline__ void recount_column(const uint64_t *lat, JBits jbits, uint64_t *g, uint64_t *red,
                                                const PaRunDesc &rd, int cur, uint32_t w, int64_t Rlive, int L,
                                                int N, int LL, uint32_t mL, uint64_t calls)
@@ -478,12 +478,12 @@ __device__ __forceinline__ void recount_column(const uint64_t *lat, JBits jbits,
 #pragma unroll
         for (int k = 0; k < 14; ++k)
             red32[wave * 64 + (lane & 1) * 32 + (lane >> 1) * 16 + k] = c[k];
-    if (lane == 0) // the places the 14 planes leave
+    if (COUNT && lane == 0) // the places the 14 planes leave
         red[wave * 32 + 7] = calls;
     __syncthreads();
     if (wave == 0) {
         uint32_t U = 0, nd = 0;
-        if (lane == 0) {
+        if (COUNT && lane == 0) {
             for (int v = 1; v < nw; ++v)
                 calls += red[v * 32 + 7];
             if (calls)
@@ -1102,7 +1102,7 @@ __device__ __forceinline__ void sweep_column(const PaRunDesc *__restrict__ runs,
         const int c = (x + y + z) & 1, k = (y + L * z) * half + (x >> 1); // the site's place in the walk
         return (tab[c * nh + k] >> kSiteJ) & 63u;
     };
-    recount_column<D, J>(lat, jbits, g, lat + N, rd, cur, w, Rlive, L, N, LL, mL,
+    recount_column<D, J, true>(lat, jbits, g, lat + N, rd, cur, w, Rlive, L, N, LL, mL,
                          theta > 0 ? pa_wave_sum_u64(calls) : 0ull);
 }
 
