@@ -136,7 +136,10 @@ __global__ __launch_bounds__(256) void k_mlp_grad(const float *__restrict__ P, c
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             d1s[4 * r + i][u] = d1[i] * (1.0f - h1[i] * h1[i]);
-        __builtin_amdgcn_wave_barrier(); // a wave reads back its own columns only
+        // a wave reads back its own columns only: no barrier, but what a lane reads other lanes wrote, and a
+        // lane's own addresses alone would let the loads pass the stores
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int s = 4 * k + r;
