@@ -2169,8 +2169,8 @@ __global__ __launch_bounds__(kThreads) void k_commit(const PaRunDesc *__restrict
 // each become one: R = 1000 6.2 + 3.8 + 2.6 us -> 9.5 and two launches less,
 // 1024 runs of R = 100 8.1 + 4.7 + 4.8 -> 9.6.  Every sum keeps the large
 // runs' order and every number their definition, so a run's results depend
-// neither on T (256 where every run fits one chunk, else 1024) nor on the
-// launches of its batch.
+// neither on T (256 only where the run fits one chunk: small_launches) nor on
+// the launches of its batch.
 template <int T, int SCHEME>
 __device__ __forceinline__ void resample_small_run(const PaRunDesc &rd, PaRecord *rec, int freeze)
 {
@@ -2611,8 +2611,8 @@ __global__ __launch_bounds__(kThreads) void k_obs_final(const PaRunDesc *__restr
 // each chunk (its replicas are loaded once, before anything waits); with
 // several chunks a group, R = 20011 took 30 us in one workgroup, as long as in
 // three passes.  Every floating-point sum keeps the large runs' order, so a
-// run's numbers depend neither on T (256 where every small run fits one chunk,
-// else 1024) nor on which side of PA_SMALL_CAP it is.
+// run's numbers depend neither on T (256 only where the run fits one chunk:
+// small_launches) nor on which side of PA_SMALL_CAP it is.
 template <int T>
 __global__ __launch_bounds__(T) void k_obs_small(const PaRunDesc *__restrict__ runs,
                                                  const uint32_t *__restrict__ list, int build_hist,
@@ -3297,13 +3297,13 @@ static bool resamples_small(const PaBatchView &v, int scheme, int kq)
     return v.nlarge == 0 && kq < 0 && scheme >= 1 && scheme <= 3;
 }
 
-// Calls f(lanes, list of the runs (null: all of the batch), n) for the small runs: workgroups of 1024 lanes, or of
-// 256 where every run is tiny.  Where tiny runs outnumber the CUs and all
-// small runs are more than two to a CU (what 1024-lane workgroups fill), the
-// middle and the tiny ones start apart: 1024 lanes for a tiny run leave most
-// idle but take their place.  2D L = 8, R = 100 with one run of R = 2000, a step:
-// 4001 runs 327 us in one launch each, 153 in two, 1001 runs 94 and 68, 501
-// runs 59 and 59, 301 runs 55 and 59.
+// Calls f(lanes, list of the runs (null: all of the batch), n) for the small
+// runs: workgroups of 1024 lanes, or of 256 where every run is tiny.  Where tiny
+// runs outnumber the CUs and all small runs are more than two to a CU (what
+// 1024-lane workgroups fill), the middle and the tiny ones start apart: 1024
+// lanes for a tiny run leave most idle but take their place.  2D L = 8, R = 100
+// with one run of R = 2000, a step: 4001 runs 327 us in one launch each, 153 in
+// two, 1001 runs 94 and 68, 501 runs 59 and 59, 301 runs 55 and 59.
 constexpr uint32_t kSplitTiny = 256, kSplitAll = 512;
 template <typename F>
 static void small_launches(const PaBatchView &v, F f)
